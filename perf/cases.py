@@ -159,22 +159,27 @@ def _apart(Ra, Rb, t, h):
     return ok
 
 
-def _orientations(rng, X, half, dims, walls):
-    """Random orientations, drawn again for bodies whose bounding boxes, grown
-    by 0.3 cells, overlap another's; (quaternions, bodies that fit)."""
+def _orientations(rng, X, half, dims, walls, sphere):
+    """Random orientations (spheres: none), drawn again for bodies whose
+    bounding boxes, grown by 0.3 cells, overlap another's; (quaternions,
+    bodies that fit)."""
     n, L = len(X), np.asarray(dims, float)
     h = half + 0.3
     d = X[None] - X[:, None]
     per = np.array([True, True, not walls])
     d -= np.where(per, L * np.round(d / L), 0.0)
-    i, j = np.nonzero((d * d).sum(-1) < 4.0 * (h * h).sum())
+    i, j = np.nonzero((d * d).sum(-1) < 4.0 * (h[0] * h[0] if sphere else (h * h).sum()))
     i, j = i[i < j], j[i < j]
+    keep = np.ones(n, bool)
+    if sphere:
+        keep[j] = False
+        return np.tile([1.0, 0.0, 0.0, 0.0], (n, 1)), keep
     t = d[i, j]
     q = W.random_quaternions(rng, n)
     R = _rotations(q)
     # the separation found for a pair holds until one of its bodies turns
     clash = ~_apart(R[i], R[j], t, h)
-    for _ in range(4000):
+    for _ in range(400):
         if not clash.any():
             break
         both = np.concatenate([i[clash], j[clash]])
@@ -196,7 +201,6 @@ def _orientations(rng, X, half, dims, walls):
         look = np.nonzero(turned[i] | turned[j])[0]
         new[look] = ~_apart(R2[i[look]], R2[j[look]], t[look], h)
         q, R, clash = q2, R2, new
-    keep = np.ones(n, bool)
     keep[j[clash]] = False
     return q, keep
 
@@ -217,11 +221,7 @@ def _inputs(case, seed):
     half = _half_extents(case["shape"], case["edge"])
     reach = float(np.linalg.norm(half)) + 1.0
     X = _centres(rng, dims, case["n"], walls, reach)
-    keep = np.ones(len(X), bool)
-    if case["shape"] == "sphere":
-        q = np.tile([1.0, 0.0, 0.0, 0.0], (len(X), 1))
-    else:
-        q, keep = _orientations(rng, X, half, dims, walls)
+    q, keep = _orientations(rng, X, half, dims, walls, case["shape"] == "sphere")
     X, q = X[keep], q[keep]
     n = len(X)
     code, size, types = {"sphere": (W.SPHERE, half[0], None), "cube": (W.CUBE, case["edge"], None),
