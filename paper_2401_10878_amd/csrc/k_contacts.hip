@@ -1,17 +1,17 @@
 // Discrete contact treatment (Sec. 3.3.1, eqs. (4)-(9)) and the per-step
 // bookkeeping of the pair tables.
 //
-// One wavefront treats one contact record (the wavefronts of a fixed grid
+// One workgroup treats one contact record (the workgroups of a fixed grid
 // take the table's occupied slots from its list in a stride):
 //   box      the carried (corrected) box of an established contact, or the
 //            rough box [min - 1/2, max + 1/2] of the flagged node images;
 //            kept in the frame of the lower-id particle a (Sec. 3.3.2)
 //   correct  faces -x,+x,-y,+y,-z,+z in turn; N_c x N_c midpoint samples of
-//            phi = max(d'_a, d'_b) on the face (one per lane); the face
-//            moves inwards by the wave minimum of phi
+//            phi = max(d'_a, d'_b) on the face; the face moves inwards by
+//            the minimum of phi
 //   integrate N_c^3 midpoint samples of the box; inside = both enlarged
-//            distances negative; wave sums of count, position and gradient
-//            difference, wave maximum of -(d'_a + d'_b)
+//            distances negative; sums of count, position and gradient
+//            difference, maximum of -(d'_a + d'_b)
 //   force    normal force (4, 5, 6) and friction (7-9) at the centroid,
 //            appended to both particles' contact slots; k_particles sums a
 //            particle's slots in the order of the partner id, so the
@@ -82,32 +82,28 @@ __global__ void k_keep(PairTable from, PairTable to, Counters* ctr) {
 struct Body {
   int shape;
   double size, X[3], R[9];
-  const PolyDev* poly;
 };
 
-// With a gradient, a point farther outside a polyhedron than far may return
-// a lower bound of the distance (far = delta: only points inside the
-// enlarged body need the exact value and gradient).
+// Signed distance of the member that a wavefront evaluates, its enlargement
+// taken off (particle), or the distance to the wall plane (-1 bottom, -2
+// top).  With a gradient, a point farther outside a polyhedron than far may
+// return a lower bound (far = delta: only points inside the enlarged body
+// need the exact value and gradient).
 template <bool ELL>
-__device__ inline double body_sdf(const Body& b, const double* y, double* g,
-                                  double far = 1e300) {
-  const double r[3] = {y[0] - b.X[0], y[1] - b.X[1], y[2] - b.X[2]};
-  if (g) return sdf_grad_exact<ELL>(b.shape, b.size, b.R, r, g, b.poly, far);
-  return sdf_exact<ELL>(b.shape, b.size, b.R, r[0], r[1], r[2], b.poly);
-}
-
-// enlarged distance of member b (particle, or wall -1 bottom / -2 top)
-template <bool ELL>
-__device__ inline double member_sdf(const Body& b, int bid, double delta,
+__device__ inline double member_sdf(const Body& b, int id, const PolyDev* poly, double delta,
                                     double nz, const double* y, double* g,
                                     double far = 1e300) {
-  if (bid >= 0) return body_sdf<ELL>(b, y, g, far) - delta;
-  if (bid == -1) {
-    if (g) { g[0] = 0.0; g[1] = 0.0; g[2] = 1.0; }
-    return y[2] + 0.5;
+  if (id >= 0) {
+    const double r[3] = {y[0] - b.X[0], y[1] - b.X[1], y[2] - b.X[2]};
+    if (g) return sdf_grad_exact<ELL>(b.shape, b.size, b.R, r, g, poly, far) - delta;
+    return sdf_exact<ELL>(b.shape, b.size, b.R, r[0], r[1], r[2], poly) - delta;
   }
-  if (g) { g[0] = 0.0; g[1] = 0.0; g[2] = -1.0; }
-  return (nz - 0.5) - y[2];
+  if (g) {
+    g[0] = 0.0;
+    g[1] = 0.0;
+    g[2] = id == -1 ? 1.0 : -1.0;
+  }
+  return id == -1 ? y[2] + 0.5 : (nz - 0.5) - y[2];
 }
 
 __device__ inline void cross3(const double* a, const double* b, double* o) {
@@ -132,49 +128,70 @@ __device__ void add_contact(Tiles tl, Counters* ctr, int p, int other,
   }
 }
 
+// One workgroup of four wavefronts per record: wavefronts 0 and 1 evaluate
+// the first member's distance, 2 and 3 the second's, 128 samples at a time,
+// and exchange them through LDS.  The treatment of a record is a chain of
+// dependent evaluations (six faces, then the integration samples of a lane)
+// and not a matter of throughput: two bodies at once and 128 samples a round
+// leave 10 single evaluations in the chain at n_c = 8 where one wavefront
+// per record had 28, and the rolled face loop (run-time axis, coordinates by
+// selects) keeps one copy of the distance in the instruction cache instead
+// of twelve.  Every wavefront forms the same minima and sums, so the box
+// corrections and exits are uniform over the workgroup; wavefront 0 forms
+// the forces.
+constexpr int TREAT_WAVES = 4;
+constexpr int TREAT_ROUND = 128;   // samples evaluated between two barriers
+struct TreatShared {
+  double d[2][2][TREAT_ROUND];     // [round parity][member][sample]
+  double red[TREAT_WAVES][8];      // sums of the integration per wavefront
+};
+
 template <bool POLY, bool ELL>
 __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g,
-                           const Phys& ph, const Tiles& tl, Counters* ctr, int slot) {
+                           const Phys& ph, const FastDiv& fnc, const Tiles& tl, Counters* ctr,
+                           int slot, TreatShared& sh, int& round) {
   const int lane = threadIdx.x % WAVE;
+  const int wave = (int)((unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x) / WAVE);
+  const int member = wave >> 1;                   // 0: particle a, 1: particle or wall b
+  const int at = (wave & 1) * WAVE + lane;        // sample of a round
   PairRec* rec = &t.rec[slot];
   const int a = __builtin_amdgcn_readfirstlane(rec->a);
   const int b = __builtin_amdgcn_readfirstlane(rec->b);
+  const bool carried = rec->carried != 0;
   const bool perz = g.periodic_z != 0;
   const double L[3] = {(double)g.nx, (double)g.ny, (double)g.nz};
   const bool per[3] = {true, true, perz};
   const int nc = ph.n_c;
   const double delta = ph.delta_c;
+  const PolyDev* poly = POLY ? P.poly : nullptr;
 
-  Body A, Bb;
-  A.poly = Bb.poly = POLY ? P.poly : nullptr;
-  A.shape = P.shape[a];
-  A.size = P.size[a];
-  for (int k = 0; k < 3; ++k) A.X[k] = P.X[3 * a + k];
-  for (int k = 0; k < 9; ++k) A.R[k] = P.R[9 * a + k];
-  Bb.shape = 0;
-  Bb.size = 0.0;
-  for (int k = 0; k < 3; ++k) Bb.X[k] = 0.0;
-  for (int k = 0; k < 9; ++k) Bb.R[k] = 0.0;
-  if (b >= 0) {
-    Bb.shape = P.shape[b];
-    Bb.size = P.size[b];
+  double XA[3];
+  for (int k = 0; k < 3; ++k) XA[k] = P.X[3 * a + k];
+  const int id = member == 0 ? a : b;
+  Body M;
+  M.shape = 0;
+  M.size = 0.0;
+  for (int k = 0; k < 3; ++k) M.X[k] = 0.0;
+  for (int k = 0; k < 9; ++k) M.R[k] = 0.0;
+  if (id >= 0) {
+    M.shape = P.shape[id];
+    M.size = P.size[id];
     // the higher-id particle is moved next to the lower-id one
     for (int k = 0; k < 3; ++k)
-      Bb.X[k] = A.X[k] + minimg(P.X[3 * b + k] - A.X[k], L[k], per[k]);
-    for (int k = 0; k < 9; ++k) Bb.R[k] = P.R[9 * b + k];
+      M.X[k] = member == 0 ? XA[k] : XA[k] + minimg(P.X[3 * id + k] - XA[k], L[k], per[k]);
+    for (int k = 0; k < 9; ++k) M.R[k] = P.R[9 * id + k];
   }
 
   double lo[3], hi[3];
-  const bool carried = rec->carried != 0;
   // a new particle-wall pair: the flagged nodes lie on the fluid side of
   // the wall plane and the overlap beyond it, so the wall-side face starts
   // at the far side of the enlarged body (half extent along z plus the
   // enlargement) and the correction moves it onto the body
   double wall_lo = 1e300, wall_hi = -1e300;
   if (!carried && b < 0) {
-    const double ez = half_extent(A.shape, A.size, A.R, 2, A.poly) + delta;
-    if (b == -1) wall_lo = A.X[2] - ez;
-    else wall_hi = A.X[2] + ez;
+    const double ez = half_extent(P.shape[a], P.size[a], P.R + 9 * a, 2, poly) + delta;
+    if (b == -1) wall_lo = XA[2] - ez;
+    else wall_hi = XA[2] + ez;
   }
   for (int k = 0; k < 3; ++k) {
     lo[k] = carried ? rec->lo[k] : (double)rec->rlo[k] - 0.5;
@@ -184,7 +201,7 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
       hi[k] = fmax(hi[k], wall_hi);
     }
     const double mid = 0.5 * (lo[k] + hi[k]);
-    const int sh = image_shift(mid - A.X[k], L[k], per[k]);
+    const int sh = image_shift(mid - XA[k], L[k], per[k]);
     lo[k] += (double)(sh * (int)L[k]);
     hi[k] += (double)(sh * (int)L[k]);
   }
@@ -192,35 +209,47 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
   // ---- box correction, one pass -----------------------------------------
   bool ok = true;
   int nfaces = 0;   // faces sampled (the box can empty on the way)
-  // fully unrolled, so that the face's axis k (and u, v) index registers
-#pragma unroll
+#pragma unroll 1
   for (int face = 0; face < 6; ++face) {
-    for (int k = 0; k < 3; ++k)
-      if (!(hi[k] > lo[k])) ok = false;
-    if (!ok) continue;
+    ok = ok && hi[0] > lo[0] && hi[1] > lo[1] && hi[2] > lo[2];
+    if (!ok) break;
     ++nfaces;
-    const int k = face / 2, plus = face % 2;
-    const int u = k == 0 ? 1 : 0, v = k == 2 ? 1 : 2;
-    const double hu = (hi[u] - lo[u]) / (double)nc;
-    const double hv = (hi[v] - lo[v]) / (double)nc;
+    const int k = face >> 1;
+    const bool plus = face & 1;
+    const double h0 = (hi[0] - lo[0]) / (double)nc, h1 = (hi[1] - lo[1]) / (double)nc,
+                 h2 = (hi[2] - lo[2]) / (double)nc;
     double smin = DBL_MAX;
-    for (int idx = lane; idx < nc * nc; idx += WAVE) {
-      const int j = idx / nc, l = idx % nc;
-      double y[3];
-      y[k] = plus ? hi[k] : lo[k];
-      y[u] = lo[u] + ((double)j + 0.5) * hu;
-      y[v] = lo[v] + ((double)l + 0.5) * hv;
-      const double da = body_sdf<ELL>(A, y, nullptr) - delta;
-      const double db = member_sdf<ELL>(Bb, b, delta, L[2], y, nullptr);
-      smin = fmin(smin, fmax(da, db));
+#pragma unroll 1
+    for (int base = 0; base < nc * nc; base += TREAT_ROUND) {
+      double (*d)[TREAT_ROUND] = sh.d[round & 1];
+      ++round;
+      const int idx = base + at;
+      if (idx < nc * nc) {
+        // sample (j, l) of the face: j along the first of its two axes
+        const int j = (int)fdiv((unsigned)idx, fnc), l = idx - j * nc;
+        const double sj = (double)j + 0.5, sl = (double)l + 0.5;
+        double y[3];
+        y[0] = k == 0 ? (plus ? hi[0] : lo[0]) : lo[0] + sj * h0;
+        y[1] = k == 1 ? (plus ? hi[1] : lo[1]) : lo[1] + (k == 0 ? sj : sl) * h1;
+        y[2] = k == 2 ? (plus ? hi[2] : lo[2]) : lo[2] + sl * h2;
+        d[member][at] = member_sdf<ELL>(M, id, poly, delta, L[2], y, nullptr);
+      }
+      __syncthreads();
+      if (base + lane < nc * nc) smin = fmin(smin, fmax(d[0][lane], d[1][lane]));
+      if (base + WAVE + lane < nc * nc)
+        smin = fmin(smin, fmax(d[0][WAVE + lane], d[1][WAVE + lane]));
     }
     smin = wave_min(smin);
-    if (plus) hi[k] = hi[k] - smin;
-    else lo[k] = lo[k] + smin;
+    for (int m = 0; m < 3; ++m) {
+      hi[m] = (k == m && plus) ? hi[m] - smin : hi[m];
+      lo[m] = (k == m && !plus) ? lo[m] + smin : lo[m];
+    }
   }
-  if (ok)
-    for (int k = 0; k < 3; ++k)
-      if (!(hi[k] > lo[k])) ok = false;
+  ok = ok && hi[0] > lo[0] && hi[1] > lo[1] && hi[2] > lo[2];
+  // midpoint samples of this record (each evaluates both members)
+  if (threadIdx.x == 0)
+    atomicAdd(&ctr->samples,
+              (unsigned long long)(nfaces * nc * nc + (ok ? nc * nc * nc : 0)));
 
   // ---- overlap integration ------------------------------------------------
   int n_in = 0;
@@ -230,36 +259,52 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
   if (ok) {
     for (int k = 0; k < 3; ++k) h[k] = (hi[k] - lo[k]) / (double)nc;
     const int ns = nc * nc * nc;
-    for (int idx = lane; idx < ns; idx += WAVE) {
-      const int j = idx % nc, kk = (idx / nc) % nc, l = idx / (nc * nc);
-      double y[3], ga[3], gb[3];
-      y[0] = lo[0] + ((double)j + 0.5) * h[0];
-      y[1] = lo[1] + ((double)kk + 0.5) * h[1];
-      y[2] = lo[2] + ((double)l + 0.5) * h[2];
-      // a sample counts when inside both enlarged bodies: beyond delta
-      // outside either, the lower bound decides
-      const double da = body_sdf<ELL>(A, y, ga, delta) - delta;
-      const double db = member_sdf<ELL>(Bb, b, delta, L[2], y, gb, delta);
-      if (fmax(da, db) < 0.0) {
+#pragma unroll 1
+    for (int base = 0; base < ns; base += TREAT_ROUND) {
+      double (*d)[TREAT_ROUND] = sh.d[round & 1];
+      ++round;
+      const int idx = base + at;
+      double y[3] = {0.0, 0.0, 0.0}, gr[3] = {0.0, 0.0, 0.0};
+      if (idx < ns) {
+        const int q = (int)fdiv((unsigned)idx, fnc), l = (int)fdiv((unsigned)q, fnc);
+        const int j = idx - q * nc, kk = q - l * nc;
+        y[0] = lo[0] + ((double)j + 0.5) * h[0];
+        y[1] = lo[1] + ((double)kk + 0.5) * h[1];
+        y[2] = lo[2] + ((double)l + 0.5) * h[2];
+        // a sample counts when inside both enlarged bodies: beyond delta
+        // outside either, a lower bound decides.  A body type's gradient
+        // comes with its distance; the built-in shapes' takes divisions and
+        // is formed below, for counted samples only
+        d[member][at] = member_sdf<ELL>(M, id, poly, delta, L[2], y, POLY ? gr : nullptr, delta);
+      }
+      __syncthreads();
+      const double da = d[0][at], db = d[1][at];
+      if (idx < ns && fmax(da, db) < 0.0) {
+        if (!POLY) member_sdf<ELL>(M, id, poly, delta, L[2], y, gr, delta);
+        for (int m = 0; m < 3; ++m) gs[m] += member == 0 ? gr[m] : -gr[m];
         n_in++;
         dmax = fmax(dmax, -(da + db));
-        for (int m = 0; m < 3; ++m) {
-          sy[m] += y[m];
-          gs[m] += ga[m] - gb[m];
-        }
+        for (int m = 0; m < 3; ++m) sy[m] += y[m];
       }
     }
-    n_in = wave_sum_i(n_in);
+    // the two wavefronts of each member hold the same samples: counts,
+    // positions and depths from the first member's, gradients from all
+    const double v[8] = {(double)wave_sum_i(n_in), wave_max(dmax), wave_sum(sy[0]),
+                         wave_sum(sy[1]),          wave_sum(sy[2]), wave_sum(gs[0]),
+                         wave_sum(gs[1]),          wave_sum(gs[2])};
+    if (lane == 0)
+      for (int k = 0; k < 8; ++k) sh.red[wave][k] = v[k];
+    __syncthreads();
+    n_in = (int)(sh.red[0][0] + sh.red[1][0]);
+    dmax = fmax(sh.red[0][1], sh.red[1][1]);
     for (int m = 0; m < 3; ++m) {
-      sy[m] = wave_sum(sy[m]);
-      gs[m] = wave_sum(gs[m]);
+      sy[m] = sh.red[0][2 + m] + sh.red[1][2 + m];
+      gs[m] = (sh.red[0][5 + m] + sh.red[1][5 + m]) + (sh.red[2][5 + m] + sh.red[3][5 + m]);
     }
-    dmax = wave_max(dmax);
   }
-  // midpoint samples of this record (each evaluates both members)
-  if (lane == 0)
-    atomicAdd(&ctr->samples,
-              (unsigned long long)(nfaces * nc * nc + (ok ? nc * nc * nc : 0)));
+  // (the other wavefronts go on to the next record; they write sh.red only
+  // after barriers that wavefront 0 reaches once it is done with this one)
+  if (wave != 0) return;
   if (!ok || n_in == 0) {
     if (lane == 0) {
       rec->keep = 0;
@@ -270,6 +315,10 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
   }
 
   // ---- results and forces (wave-uniform values) ----------------------------
+  double XB[3] = {0.0, 0.0, 0.0};
+  if (b >= 0)
+    for (int k = 0; k < 3; ++k)
+      XB[k] = XA[k] + minimg(P.X[3 * b + k] - XA[k], L[k], per[k]);
   const double V = (double)n_in * (h[0] * h[1] * h[2]);
   double xc[3], nrm[3] = {0.0, 0.0, 0.0};
   for (int m = 0; m < 3; ++m) xc[m] = sy[m] / (double)n_in;
@@ -279,7 +328,7 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
   } else {
     double dv[3];
     if (b >= 0) {
-      for (int m = 0; m < 3; ++m) dv[m] = Bb.X[m] - A.X[m];
+      for (int m = 0; m < 3; ++m) dv[m] = XB[m] - XA[m];
     } else {
       dv[0] = 0.0; dv[1] = 0.0; dv[2] = b == -1 ? -1.0 : 1.0;
     }
@@ -290,12 +339,12 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
   const double depth = dmax;
 
   double ra[3], t3[3], va[3], vb[3] = {0.0, 0.0, 0.0};
-  for (int m = 0; m < 3; ++m) ra[m] = xc[m] - A.X[m];
+  for (int m = 0; m < 3; ++m) ra[m] = xc[m] - XA[m];
   cross3(P.W + 3 * a, ra, t3);
   for (int m = 0; m < 3; ++m) va[m] = P.U[3 * a + m] + t3[m];
   double rb[3] = {0.0, 0.0, 0.0};
   if (b >= 0) {
-    for (int m = 0; m < 3; ++m) rb[m] = xc[m] - Bb.X[m];
+    for (int m = 0; m < 3; ++m) rb[m] = xc[m] - XB[m];
     cross3(P.W + 3 * b, rb, t3);
     for (int m = 0; m < 3; ++m) vb[m] = P.U[3 * b + m] + t3[m];
   }
@@ -324,16 +373,22 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
                       ph.mu_k / (a2 + 1.0);
     for (int m = 0; m < 3; ++m) ft[m] = -(vt[m] / vtn) * mu * fn;
   }
-  double Fa[3], Fb[3], Ta[3], Tb[3];
-  for (int m = 0; m < 3; ++m) {
-    Fa[m] = -fn * nrm[m] + ft[m];
-    Fb[m] = -Fa[m];
-  }
+  double Fa[3], Ta[3], Tb[3];
+  for (int m = 0; m < 3; ++m) Fa[m] = -fn * nrm[m] + ft[m];
   cross3(ra, Fa, Ta);
-  if (b >= 0) cross3(rb, Fb, Tb);
+  // lane 0 appends to particle a, lane 1 to particle b: one round trip of
+  // the slot counts
+  if (lane < (b >= 0 ? 2 : 1)) {
+    double F[3], T[3];
+    const double Fb[3] = {-Fa[0], -Fa[1], -Fa[2]};
+    cross3(rb, Fb, Tb);
+    for (int m = 0; m < 3; ++m) {
+      F[m] = lane == 0 ? Fa[m] : Fb[m];
+      T[m] = lane == 0 ? Ta[m] : Tb[m];
+    }
+    add_contact(tl, ctr, lane == 0 ? a : b, lane == 0 ? b : a, F, T);
+  }
   if (lane == 0) {
-    add_contact(tl, ctr, a, b, Fa, Ta);
-    if (b >= 0) add_contact(tl, ctr, b, a, Fb, Tb);
     rec->keep = 1;
     rec->carried = 1;
     rec->established = established;
@@ -353,15 +408,17 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
   }
 }
 
-
-constexpr int TREAT_BLOCKS = 512;   // 2048 wavefronts
+constexpr int TREAT_BLOCKS = 1024;
 template <bool POLY, bool ELL = false>
-__global__ __launch_bounds__(256) void k_treat(PairTable t, Particles P, Geom g,
-                                               Phys ph, Tiles tl, Counters* ctr) {
+__global__ __launch_bounds__(TREAT_WAVES* WAVE) void k_treat(PairTable t, Particles P, Geom g,
+                                                             Phys ph, FastDiv fnc, Tiles tl,
+                                                             Counters* ctr) {
+  __shared__ TreatShared sh;
   const int n = *t.nlist;
-  const int stride = (int)gridDim.x * 4;
-  for (int i = (int)blockIdx.x * 4 + (int)(threadIdx.x / WAVE); i < n; i += stride)
-    treat_slot<POLY, ELL>(t, P, g, ph, tl, ctr, __builtin_amdgcn_readfirstlane(t.list[i]));
+  int round = 0;
+  for (int i = (int)blockIdx.x; i < n; i += (int)gridDim.x)
+    treat_slot<POLY, ELL>(t, P, g, ph, fnc, tl, ctr,
+                          __builtin_amdgcn_readfirstlane(t.list[i]), sh, round);
 }
 
 }  // namespace
@@ -391,16 +448,16 @@ hipError_t launch_keep(Ctx& c, PairTable from, PairTable to) {
 }
 
 hipError_t launch_treat(Ctx& c, PairTable t, hipStream_t s) {
-  const unsigned nb = (unsigned)((t.cap + 3) / 4 < TREAT_BLOCKS ? (t.cap + 3) / 4 : TREAT_BLOCKS);
+  const dim3 nb((unsigned)(t.cap < TREAT_BLOCKS ? t.cap : TREAT_BLOCKS));
+  const dim3 nt(TREAT_WAVES * WAVE);
+  const FastDiv fnc = make_fastdiv((unsigned)c.ph.n_c);
   if (c.has_ellipsoid)
-    hipLaunchKernelGGL((k_treat<true, true>), dim3(nb), dim3(256), 0,
-                     s, t, c.part, c.g, c.ph, c.tl, c.counters);
+    hipLaunchKernelGGL((k_treat<true, true>), nb, nt, 0, s, t, c.part, c.g, c.ph, fnc, c.tl,
+                       c.counters);
   else if (c.has_poly)
-    hipLaunchKernelGGL(k_treat<true>, dim3(nb), dim3(256), 0,
-                     s, t, c.part, c.g, c.ph, c.tl, c.counters);
+    hipLaunchKernelGGL(k_treat<true>, nb, nt, 0, s, t, c.part, c.g, c.ph, fnc, c.tl, c.counters);
   else
-    hipLaunchKernelGGL(k_treat<false>, dim3(nb), dim3(256), 0,
-                     s, t, c.part, c.g, c.ph, c.tl, c.counters);
+    hipLaunchKernelGGL(k_treat<false>, nb, nt, 0, s, t, c.part, c.g, c.ph, fnc, c.tl, c.counters);
   return hipGetLastError();
 }
 
