@@ -110,11 +110,9 @@ void drop_graphs(Ctx& c) {
   for (int k = 0; k < 4; ++k) {
     if (c.graph_ready[k]) hipGraphExecDestroy(c.gexec[k]);
     c.graph_ready[k] = false;
-    for (int v = 0; v < 4; ++v) {
-      if (c.graph_n_ready[k][v]) hipGraphExecDestroy(c.gexec_n[k][v]);
-      c.graph_n_ready[k][v] = false;
-      c.graph_n_run[k][v] = false;
-    }
+    if (c.graph_n_ready[k]) hipGraphExecDestroy(c.gexec_n[k]);
+    c.graph_n_ready[k] = false;
+    c.graph_n_run[k] = false;
   }
 }
 
@@ -137,14 +135,18 @@ hlbm_status prologue(Ctx& c) {
   drop_graphs(c);
   const int p = c.tcur;
   const size_t nb = sizeof(double) * 3 * (c.np > 0 ? c.np : 1);
-  HIPCHECK(launch_clear_step(c, c.tab[p], CLEAR_CONTACT | CLEAR_TILES, c.stream));
+  HIPCHECK(launch_clear(c, c.tab[1 - p], CLEAR_TABLE));
+  HIPCHECK(launch_clear(c, c.tab[p], CLEAR_TABLE | CLEAR_RESULTS | CLEAR_TILES));
   HIPCHECK(hipMemsetAsync(c.Fh, 0, nb, c.stream));
   HIPCHECK(hipMemsetAsync(c.Th, 0, nb, c.stream));
   HIPCHECK(hipMemsetAsync(c.tl.ovf, 0, 2 * nb, c.stream));
-  HIPCHECK(launch_particles(c, 0));
+  HIPCHECK(launch_particles(c, 0, true));
   HIPCHECK(launch_detect(c, c.tab[p]));
   HIPCHECK(launch_mea(c, c.fbuf[c.cur]));
-  if (c.ph.bal_mode == 2) HIPCHECK(launch_balance(c, c.fbuf[c.cur], 1, c.stream));
+  if (c.ph.bal_mode == 2) {
+    HIPCHECK(launch_pop_moments(c, c.fbuf[c.cur]));
+    HIPCHECK(launch_balance(c, 1));
+  }
   c.step = 0;
   c.fluid_ready = true;
   const hlbm_status st = check_flags(c);
@@ -154,106 +156,70 @@ hlbm_status prologue(Ctx& c) {
 // The launch sequence of one time step with population parity p (buffers
 // p -> 1-p) starting from contact table t; the table parity flips once per
 // sub-step.  ev (optional): 3 + 5 n_sub events recorded around the launches.
-// Overlap (one sub-step only): the contact treatment of a step reads the
-// particle state and the pair table the previous step's detection left, and
-// nothing that the stream-collide or momentum-exchange pass writes, so it
-// can run beside them on the side stream.  pre & PRE_DONE: this step's
-// treatment already ran there (wait for it, then clear the tile counts the
-// previous momentum-exchange pass read); pre & PRE_NEXT: after detection,
-// start the next step's treatment on the side stream; pre & PRE_JOINED
-// (with PRE_DONE): that treatment, and the balance sums, are complete in
-// stream order already (a graph that started them joined them before its
-// end), so no event wait.
-constexpr int PRE_DONE = 1, PRE_NEXT = 2, PRE_JOINED = 4;
-hipError_t enqueue_step(Ctx& c, int p, int t, hipEvent_t* ev, int pre) {
+//
+// All kernels of a step run in order on one stream: contact treatment, motion
+// (with binning and the contact carry-over), detection, lattice pass, and
+// nothing between them, because each leaves its inputs as the next step needs
+// them: the carry-over clears the slots it reads, detection and the lattice
+// pass reset their counts, the motion kernel the particles' contact slots.
+// (Treating the next step's contacts on a second stream beside the lattice
+// pass had hidden a treatment of 33 us and cost two cross-stream waits of
+// about 10 us each, a bookkeeping launch of up to 25 us before it and a tail
+// of 15 us after the lattice pass.)
+//
+// Balance mode 2: the controller's sums of a lattice pass feed only the next
+// one.  flags & BAL_LATER leaves them to the next step of the same call,
+// which takes them along in its motion and detection launches (flags &
+// BAL_PENDING); otherwise they are two launches at the end of the step.
+constexpr int BAL_PENDING = 1, BAL_LATER = 2;
+hipError_t enqueue_step(Ctx& c, int p, int t, hipEvent_t* ev, int flags) {
   hipError_t e;
   int m = 0;
   auto mark = [&]() -> hipError_t {
     return ev ? hipEventRecord(ev[m++], c.stream) : hipSuccess;
   };
+  const bool bal = c.ph.bal_mode == 2;
   if ((e = mark())) return e;
   for (int s = 0; s < c.n_sub; ++s) {
-    if (s == 0 && (pre & PRE_DONE)) {
-      // (the tile counts need no clearing here: detection and the lattice
-      // pass reset the counts they read)
-      if (!(pre & PRE_JOINED) && (e = hipStreamWaitEvent(c.stream, c.ev_treat, 0))) return e;
-      if ((e = mark())) return e;
-    } else {
-      if ((e = launch_clear_step(c, c.tab[1 - t], CLEAR_CONTACT | CLEAR_TILES, c.stream)))
-        return e;
-      if ((e = mark())) return e;
-      if ((e = launch_treat(c, c.tab[t], c.stream))) return e;
-    }
+    const bool pend = bal && s == 0 && (flags & BAL_PENDING);
+    // (the timing slots of the clearing and of the carry-over stay empty)
     if ((e = mark())) return e;
-    // particle motion, tile binning and the contact carry-over in one launch
-    // (the carry-over's timing slot stays empty)
-    if ((e = launch_particles(c, s == 0 ? 1 : 2, &c.tab[t], &c.tab[1 - t]))) return e;
+    if ((e = launch_treat(c, c.tab[t]))) return e;
+    if ((e = mark())) return e;
+    if ((e = launch_particles(c, s == 0 ? 1 : 2, s + 1 == c.n_sub, &c.tab[t], &c.tab[1 - t],
+                              pend)))
+      return e;
     if ((e = mark())) return e;
     if ((e = mark())) return e;
-    if ((e = launch_detect(c, c.tab[1 - t]))) return e;
+    if ((e = launch_detect(c, c.tab[1 - t], &c.tab[t], pend))) return e;
     if ((e = mark())) return e;
     t = 1 - t;
   }
-  if (pre & PRE_NEXT) {
-    // the next step's clear of its contact state and its treatment of
-    // table t (the one detection just filled)
-    if ((e = hipEventRecord(c.ev_det, c.stream))) return e;
-    if ((e = hipStreamWaitEvent(c.side, c.ev_det, 0))) return e;
-    if ((e = launch_clear_step(c, c.tab[1 - t], CLEAR_CONTACT, c.side))) return e;
-    if ((e = launch_treat(c, c.tab[t], c.side))) return e;
-    if ((e = hipEventRecord(c.ev_treat, c.side))) return e;
-  }
   // the lattice pass also sums the momentum exchange of the next step (the
-  // last timing slot stays empty).
-  // The balance controller's sums feed only the next collision: with
-  // PRE_NEXT they run on the side stream, beside the next step's
-  // bookkeeping, particle motion and detection, and the next lattice pass
-  // waits for them.
-  const bool bal = c.ph.bal_mode == 2;
-  if (bal && (pre & PRE_DONE) && !(pre & PRE_JOINED) &&
-      (e = hipStreamWaitEvent(c.stream, c.ev_bal, 0)))
-    return e;
+  // last timing slot stays empty)
   if ((e = launch_lattice(c, c.fbuf[p], c.fbuf[1 - p]))) return e;
-  if (bal && (pre & PRE_NEXT)) {
-    if ((e = hipEventRecord(c.ev_lat, c.stream))) return e;
-    if ((e = hipStreamWaitEvent(c.side, c.ev_lat, 0))) return e;
-    if ((e = launch_balance(c, nullptr, 0, c.side))) return e;
-    if ((e = hipEventRecord(c.ev_bal, c.side))) return e;
-  } else if (bal && (e = launch_balance(c, nullptr, 0, c.stream))) {
-    return e;
-  }
+  if (bal && !(flags & BAL_LATER) && (e = launch_balance(c, 0))) return e;
   if ((e = mark())) return e;
   return mark();
 }
 
 // Capture and instantiate the graph of one step (multi = false) or of
-// GRAPH_STEPS steps with the overlapped contact treatment (multi = true,
-// variant v as in Ctx::gexec_n) starting from population parity key / 2 and
-// table parity key % 2.  Capturing runs nothing.
-hlbm_status capture_graph(Ctx& c, int key, bool multi, int v = 0) {
+// GRAPH_STEPS steps (multi = true) starting from population parity key / 2
+// and table parity key % 2.  Capturing runs nothing.
+hlbm_status capture_graph(Ctx& c, int key, bool multi) {
   const int p = key / 2, t = key % 2;
   hipGraph_t gr;
   HIPCHECK(hipStreamBeginCapture(c.stream, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
-  if (multi) {
-    const bool first_done = v & 1, last_next = v & 2;
-    for (int j = 0; j < GRAPH_STEPS && e == hipSuccess; ++j) {
-      const int pre = (j > 0 ? PRE_DONE : (first_done ? PRE_DONE | PRE_JOINED : 0)) |
-                      (j + 1 < GRAPH_STEPS || last_next ? PRE_NEXT : 0);
-      e = enqueue_step(c, p ^ (j & 1), t ^ (j & 1), nullptr, pre);
-    }
-    // the next step's treatment (and the balance sums after it) joined
-    // back, so that the graph ends with nothing pending
-    if (e == hipSuccess && last_next)
-      e = hipStreamWaitEvent(c.stream, c.ph.bal_mode == 2 ? c.ev_bal : c.ev_treat, 0);
-  } else {
-    e = enqueue_step(c, p, t, nullptr, 0);
-  }
+  const int n = multi ? GRAPH_STEPS : 1;
+  for (int j = 0; j < n && e == hipSuccess; ++j)
+    e = enqueue_step(c, p ^ (j & 1), t ^ (j & c.n_sub & 1), nullptr,
+                     (j > 0 ? BAL_PENDING : 0) | (j + 1 < n ? BAL_LATER : 0));
   hipError_t e2 = hipStreamEndCapture(c.stream, &gr);
   if (e != hipSuccess || e2 != hipSuccess)
     return fail(c, HLBM_E_DEVICE, "graph capture: %s",
                 hipGetErrorString(e != hipSuccess ? e : e2));
-  hipGraphExec_t* slot = multi ? &c.gexec_n[key][v] : &c.gexec[key];
+  hipGraphExec_t* slot = multi ? &c.gexec_n[key] : &c.gexec[key];
   e = hipGraphInstantiate(slot, gr, nullptr, nullptr, 0);
   hipGraphDestroy(gr);
   if (e != hipSuccess)
@@ -262,16 +228,16 @@ hlbm_status capture_graph(Ctx& c, int key, bool multi, int v = 0) {
   e = hipGraphUpload(*slot, c.stream);
   if (e != hipSuccess)
     return fail(c, HLBM_E_DEVICE, "graph upload: %s", hipGetErrorString(e));
-  if (multi) c.graph_n_ready[key][v] = true;
+  if (multi) c.graph_n_ready[key] = true;
   else c.graph_ready[key] = true;
   return HLBM_OK;
 }
 
 // Capture every graph that steps from the current parities can replay: the
 // single-step graphs of the current (population, table) parity and of the
-// one after a step, and, with one contact sub-step, the multi-step graphs of
-// both (a multi-step graph returns to its starting parities).  A timed window
-// of hlbm_step calls then launches graphs only.
+// one after a step, and the multi-step graphs of both (a multi-step graph
+// returns to its starting parities).  A timed window of hlbm_step calls then
+// launches graphs only.
 hlbm_status prepare_graphs(Ctx& c) {
   if (!c.use_graph || !c.fluid_ready) return HLBM_OK;
   const int k0 = 2 * c.cur + c.tcur;
@@ -281,18 +247,17 @@ hlbm_status prepare_graphs(Ctx& c) {
       const hlbm_status st = capture_graph(c, key, false);
       if (st != HLBM_OK) return st;
     }
-    for (int v = 0; v < 4 && c.n_sub == 1 && c.side; ++v)
-      if (!c.graph_n_ready[key][v]) {
-        const hlbm_status st = capture_graph(c, key, true, v);
-        if (st != HLBM_OK) return st;
-      }
+    if (!c.graph_n_ready[key]) {
+      const hlbm_status st = capture_graph(c, key, true);
+      if (st != HLBM_OK) return st;
+    }
   }
   return HLBM_OK;
 }
 
 // the step that the next hlbm_step would run, and the parities after it
-hipError_t run_step(Ctx& c, hipEvent_t* ev, int pre = 0) {
-  hipError_t e = enqueue_step(c, c.cur, c.tcur, ev, pre);
+hipError_t run_step(Ctx& c, hipEvent_t* ev, int flags = 0) {
+  hipError_t e = enqueue_step(c, c.cur, c.tcur, ev, flags);
   c.cur = 1 - c.cur;
   c.tcur = (c.n_sub & 1) ? 1 - c.tcur : c.tcur;
   c.step++;
@@ -478,20 +443,6 @@ hlbm_status hlbm_create(const hlbm_params* params, void* stream, hlbm_ctx** out)
       return HLBM_E_DEVICE;
     }
   }
-  if (hipStreamCreate(&c.side) != hipSuccess ||
-      hipEventCreateWithFlags(&c.ev_det, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&c.ev_treat, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&c.ev_lat, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&c.ev_bal, hipEventDisableTiming) != hipSuccess) {
-    if (c.side) hipStreamDestroy(c.side);
-    if (c.ev_det) hipEventDestroy(c.ev_det);
-    if (c.ev_treat) hipEventDestroy(c.ev_treat);
-    if (c.ev_lat) hipEventDestroy(c.ev_lat);
-    if (c.ev_bal) hipEventDestroy(c.ev_bal);
-    if (c.own_stream) hipStreamDestroy(c.stream);
-    delete h;
-    return HLBM_E_DEVICE;
-  }
   const long long ndt = (long long)c.g.dtx * c.g.dty * c.g.dtz;
   const long long nlt = (long long)c.g.ltx * c.g.lty * c.g.ltz;
   const int cap = next_pow2(2LL * P.max_pairs);
@@ -500,7 +451,7 @@ hlbm_status hlbm_create(const hlbm_params* params, void* stream, hlbm_ctx** out)
   c.tile_bytes = tbytes;
   bool okm = hipMalloc(&c.owner, sizeof(int) * ncell) == hipSuccess &&
              hipMalloc(&c.tile_block, tbytes) == hipSuccess &&
-             hipMalloc(&c.counters, sizeof(Counters)) == hipSuccess &&
+             hipMalloc(&c.counters, COUNTER_BYTES) == hipSuccess &&
              hipMalloc(&c.scratch, sizeof(double) * ncell) == hipSuccess &&
              (P.balance != 2 ||
               hipMalloc(&c.bal_part, sizeof(double) * 4 * ((size_t)nlt + BAL_PARTS)) == hipSuccess);
@@ -524,11 +475,11 @@ hlbm_status hlbm_create(const hlbm_params* params, void* stream, hlbm_ctx** out)
     c.tl.llist = t; t += nlt * P.tile_capacity;
     c.tl.lent = t;
   }
-  hipMemsetAsync(c.counters, 0, sizeof(Counters), c.stream);
+  hipMemsetAsync(c.counters, 0, COUNTER_BYTES, c.stream);
   hipMemsetAsync(c.owner, 0xff, sizeof(int) * ncell, c.stream);
   for (int k = 0; k < 2; ++k) {
     hipMemsetAsync(c.tab[k].list, 0, sizeof(int) * ((size_t)cap + 2), c.stream);
-    launch_clear_step(c, c.tab[k], CLEAR_ALL_SLOTS, c.stream);
+    launch_clear(c, c.tab[k], CLEAR_ALL_SLOTS);
   }
   if (hipStreamSynchronize(c.stream) != hipSuccess) {
     hlbm_destroy(h);
@@ -963,37 +914,28 @@ hlbm_status hlbm_step(hlbm_ctx* h, int nsteps) {
   Ctx& c = h->c;
   if (!c.fluid_ready) return fail(c, HLBM_E_STATE, "initialise particles and fluid first");
   if (nsteps < 0) return fail(c, HLBM_E_ARG, "nsteps must be >= 0");
-  // With graphs on (one contact sub-step), a call of two or more steps
-  // replays multi-step graphs first and runs the remaining steps as stream
-  // launches; the contact treatment overlaps the previous lattice pass at
-  // every step but the call's first, across graph boundaries too (a graph
-  // followed by more steps starts the next step's treatment and joins it
-  // before it ends; the step after it takes it as done).  The same bits as
-  // stream launches.  A single step replays its single-step graph.
-  const bool chain = c.use_graph && !c.timing && c.n_sub == 1 && c.side != nullptr;
-  bool after_graph = false;   // the previous step ended a graph that joined
-  bool streamed = false;      // a stream launch of this call may have left the
-                              // next step's treatment pending: no graph after it
+  // With graphs on, a call replays multi-step graphs while GRAPH_STEPS steps
+  // remain, a call of one step its single-step graph, and the remaining steps
+  // are stream launches; the same kernels in the same order either way.
+  bool pending = false;   // the previous step left its balance sums to this one
   for (int s = 0; s < nsteps; ++s) {
     const int key = 2 * c.cur + c.tcur;
-    const int v = (s > 0 ? 1 : 0) | (s + GRAPH_STEPS < nsteps ? 2 : 0);
     if (c.timing) {
       if (c.tused >= c.tcap)
         return fail(c, HLBM_E_CAPACITY, "timing window of %d steps is full", c.tcap);
       HIPCHECK(run_step(c, c.tev + (size_t)c.tused * c.ev_per_step));
       c.tused++;
-    } else if (chain && !streamed && nsteps - s >= GRAPH_STEPS &&
-               (c.graph_n_run[key][v] || nsteps >= GRAPH_COLD_CALL)) {
-      if (!c.graph_n_ready[key][v]) {
-        const hlbm_status st = capture_graph(c, key, true, v);
+    } else if (c.use_graph && !pending && nsteps - s >= GRAPH_STEPS &&
+               (c.graph_n_run[key] || nsteps >= GRAPH_COLD_CALL)) {
+      if (!c.graph_n_ready[key]) {
+        const hlbm_status st = capture_graph(c, key, true);
         if (st != HLBM_OK) return st;
       }
-      HIPCHECK(hipGraphLaunch(c.gexec_n[key][v], c.stream));
-      c.graph_n_run[key][v] = true;
+      HIPCHECK(hipGraphLaunch(c.gexec_n[key], c.stream));
+      c.graph_n_run[key] = true;
       c.step += GRAPH_STEPS;
       s += GRAPH_STEPS - 1;
-      after_graph = true;
-    } else if (c.use_graph && !(chain && nsteps >= 2)) {
+    } else if (c.use_graph && nsteps == 1) {
       if (!c.graph_ready[key]) {
         const hlbm_status st = capture_graph(c, key, false);
         if (st != HLBM_OK) return st;
@@ -1003,20 +945,10 @@ hlbm_status hlbm_step(hlbm_ctx* h, int nsteps) {
       c.tcur = (c.n_sub & 1) ? 1 - c.tcur : c.tcur;
       c.step++;
     } else {
-      // steps of one call after the first overlap their contact treatment
-      // with the previous step's lattice passes; the last step leaves none
-      // pending, so the state after the call is that of whole steps
-      const bool ovl = c.n_sub == 1 && c.side != nullptr;
-      const int pre = (ovl && s > 0 ? PRE_DONE | (after_graph ? PRE_JOINED : 0) : 0) |
-                      (ovl && s + 1 < nsteps ? PRE_NEXT : 0);
-      after_graph = false;
-      streamed = true;
-      const hipError_t e = run_step(c, nullptr, pre);
-      if (e != hipSuccess) {
-        // whatever the side stream has queued is joined before reporting
-        if (ovl) (void)hipStreamWaitEvent(c.stream, c.ev_treat, 0);
-        return fail(c, HLBM_E_DEVICE, "step: %s", hipGetErrorString(e));
-      }
+      const bool later = s + 1 < nsteps;
+      const hipError_t e = run_step(c, nullptr, (pending ? BAL_PENDING : 0) | (later ? BAL_LATER : 0));
+      if (e != hipSuccess) return fail(c, HLBM_E_DEVICE, "step: %s", hipGetErrorString(e));
+      pending = later;
     }
   }
   return HLBM_OK;
@@ -1392,6 +1324,9 @@ hlbm_status hlbm_set_state(hlbm_ctx* h, const void* blob, size_t bytes) {
   }
   HIPCHECK(put(c.owner, sizeof(int) * (size_t)c.g.ncell));
   HIPCHECK(put(c.counters, sizeof(Counters)));
+  // what a step leaves empty (states saved by earlier builds left these to
+  // the next step's start)
+  HIPCHECK(launch_clear(c, c.tab[1 - c.tcur], CLEAR_TABLE | CLEAR_TILES));
   HIPCHECK(hipStreamSynchronize(c.stream));
   free_adjoint(c);
   c.fluid_ready = true;
@@ -1580,14 +1515,6 @@ void hlbm_destroy(hlbm_ctx* h) {
     if (c.tab[k].keys) hipFree(c.tab[k].keys);
     if (c.tab[k].rec) hipFree(c.tab[k].rec);
   }
-  if (c.side) {
-    hipStreamSynchronize(c.side);
-    hipStreamDestroy(c.side);
-  }
-  if (c.ev_det) hipEventDestroy(c.ev_det);
-  if (c.ev_treat) hipEventDestroy(c.ev_treat);
-  if (c.ev_lat) hipEventDestroy(c.ev_lat);
-  if (c.ev_bal) hipEventDestroy(c.ev_bal);
   if (c.own_stream && c.stream) hipStreamDestroy(c.stream);
   delete h;
 }

@@ -64,14 +64,31 @@ struct Counters {
   double bal_b[3], bal_P[3], bal_M, bal_a[3];
 };
 
-// Carry-over of slot s of the pair table `from` into `to` when its record
-// is marked to be kept (an established contact that continues, Sec. 3.3.2):
-// the key is inserted by linear probing and the record's contact state
-// copied; a full table raises pair_overflow.
+// The counter block is followed by the midpoint samples of the treatment that
+// is running; the motion kernel moves them into Counters::samples, so they
+// are zero between steps (and not part of a saved state).
+__host__ __device__ inline unsigned long long* running_samples(Counters* c) {
+  return (unsigned long long*)(c + 1);
+}
+constexpr size_t COUNTER_BYTES = sizeof(Counters) + sizeof(unsigned long long);
+
+__device__ inline void clear_slot(const PairTable& t, long long i) {
+  t.keys[i] = EMPTY_KEY;
+  PairRec r = {};
+  for (int k = 0; k < 3; ++k) {
+    r.rlo[k] = 0x7fffffff;
+    r.rhi[k] = (int)0x80000000;
+  }
+  t.rec[i] = r;
+}
+
+// Carry-over of occupied slot s of the pair table `from` into `to` when its
+// record is marked to be kept (an established contact that continues, Sec.
+// 3.3.2): the key is inserted by linear probing and the record's contact
+// state copied; a full table raises pair_overflow.
 __device__ inline void keep_slot(const PairTable& from, const PairTable& to, long long s,
                                  Counters* ctr) {
   const uint64_t key = from.keys[s];
-  if (key == EMPTY_KEY) return;
   const PairRec& r = from.rec[s];
   if (!r.keep) return;
   const uint32_t mask = (uint32_t)to.cap - 1u;
@@ -218,14 +235,6 @@ struct Ctx {
   Phys ph;
   hipStream_t stream;
   bool own_stream;
-  // second stream for the next step's contact treatment, which overlaps the
-  // stream-collide and momentum-exchange passes (ev_det: detection done on
-  // `stream`; ev_treat: treatment done on `side`)
-  hipStream_t side = nullptr;
-  hipEvent_t ev_det = nullptr, ev_treat = nullptr;
-  // balance sums of a step on the side stream: after its lattice pass
-  // (ev_lat), before the next step's lattice pass (ev_bal)
-  hipEvent_t ev_lat = nullptr, ev_bal = nullptr;
   int precision;
   size_t bytes_per_value;
   // populations (two buffers, ping-pong); fbuf[cur] holds f* of the last step
@@ -274,17 +283,13 @@ struct Ctx {
   size_t part_bytes = 0, tile_bytes = 0, psum_bytes = 0;
   Adjoint adj;
   // graphs: one per (population parity, contact-table parity) for a single
-  // step, and (one contact sub-step) GRAPH_STEPS steps with the overlapped
-  // contact treatment inside, in four variants v: v & 1, the first step's
-  // treatment already ran (the previous graph's last step started it);
-  // v & 2, the last step starts the next step's treatment and the graph
-  // joins it before it ends
+  // step and one for GRAPH_STEPS steps
   bool use_graph;
   hipGraphExec_t gexec[4];
   bool graph_ready[4];
-  hipGraphExec_t gexec_n[4][4];
-  bool graph_n_ready[4][4] = {};
-  bool graph_n_run[4][4] = {};   // replayed at least once (its one-time
+  hipGraphExec_t gexec_n[4];
+  bool graph_n_ready[4] = {};
+  bool graph_n_run[4] = {};      // replayed at least once (its one-time
                                  // setup on the device is done)
   int n_sub;
   int ev_per_step;        // timing events per step: 2 + 5 n_sub
@@ -292,29 +297,37 @@ struct Ctx {
 };
 
 // ---- launch wrappers (kernels live in the .hip files) --------------------
-// what: CLEAR_CONTACT (next pair table, contact forces and slots, detection
-// counters) and/or CLEAR_TILES (detection-tile and lattice-block counts)
-constexpr int CLEAR_CONTACT = 1, CLEAR_TILES = 2;
-// CLEAR_ALL_SLOTS: every slot of the table (once, after allocation; later
-// clears visit the listed slots only)
-constexpr int CLEAR_ALL_SLOTS = 4;
-hipError_t launch_clear_step(Ctx& c, PairTable next, int what, hipStream_t s);
+// Bookkeeping outside the steps (a step leaves everything as the next one
+// needs it): CLEAR_TABLE the listed slots of a pair table and the particles'
+// contact slots, CLEAR_TILES the detection-tile and lattice-block counts,
+// CLEAR_RESULTS the contact forces and the detection and sample counters,
+// CLEAR_ALL_SLOTS every slot of the table (once, after allocation)
+constexpr int CLEAR_TABLE = 1, CLEAR_TILES = 2, CLEAR_RESULTS = 4, CLEAR_ALL_SLOTS = 8;
+hipError_t launch_clear(Ctx& c, PairTable table, int what);
 // move: 0 bin only, 1 gather the hydrodynamic force and move, 2 move with
-// the stored hydrodynamic force (later sub-steps)
+// the stored hydrodynamic force (later sub-steps).  bin_blocks: also bin into
+// lattice blocks (the last binning before a lattice pass).
 // keep_from / keep_to (optional, both or neither): the contact carry-over
-// from one pair table to the next runs in the same launch
-hipError_t launch_particles(Ctx& c, int move, const PairTable* keep_from = nullptr,
-                            const PairTable* keep_to = nullptr);
-hipError_t launch_keep(Ctx& c, PairTable from, PairTable to);
-hipError_t launch_detect(Ctx& c, PairTable to);
+// from one pair table to the next, and the clearing of the slots it read,
+// run in the same launch; so do (balance) the first stage of the balance
+// sums of the last lattice pass
+hipError_t launch_particles(Ctx& c, int move, bool bin_blocks,
+                            const PairTable* keep_from = nullptr,
+                            const PairTable* keep_to = nullptr, bool balance = false);
+// from (optional): the table whose list the carry-over is done with; balance:
+// the second stage of the balance sums
+hipError_t launch_detect(Ctx& c, PairTable to, const PairTable* from = nullptr,
+                         bool balance = false);
 // stream-collide src -> dst with the coupling of the current owner map
 hipError_t launch_lattice(Ctx& c, const void* src, void* dst);
 // momentum exchange over the collided populations fstar (force of the next step)
 hipError_t launch_mea(Ctx& c, const void* fstar);
-// balance mode 2: lattice mass and momentum of f at the start (init = 1), or
-// the controller update after a collision from the lattice pass's block sums
-hipError_t launch_balance(Ctx& c, const void* f, int init, hipStream_t st);
-hipError_t launch_treat(Ctx& c, PairTable t, hipStream_t s);
+// balance mode 2: the lattice blocks' mass and momentum of f (initial state),
+// then the controller (init = 1 at the start, 0 after a collision) from the
+// block sums
+hipError_t launch_pop_moments(Ctx& c, const void* f);
+hipError_t launch_balance(Ctx& c, int init);
+hipError_t launch_treat(Ctx& c, PairTable t);
 hipError_t launch_fill_equilibrium(Ctx& c, void* f, double rho,
                                    const double u[3]);
 hipError_t launch_store_direction(Ctx& c, void* f, int i, const double* src);

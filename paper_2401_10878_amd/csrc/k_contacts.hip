@@ -1,5 +1,5 @@
-// Discrete contact treatment (Sec. 3.3.1, eqs. (4)-(9)) and the per-step
-// bookkeeping of the pair tables.
+// Discrete contact treatment (Sec. 3.3.1, eqs. (4)-(9)) and the clearing of
+// the pair tables and counters outside the steps.
 //
 // One workgroup treats one contact record (the workgroups of a fixed grid
 // take the table's occupied slots from its list in a stride):
@@ -24,19 +24,9 @@ namespace hlbm {
 
 namespace {
 
-__device__ inline void clear_slot(const PairTable& t, long long i) {
-  t.keys[i] = EMPTY_KEY;
-  PairRec r = {};
-  for (int k = 0; k < 3; ++k) {
-    r.rlo[k] = 0x7fffffff;
-    r.rhi[k] = (int)0x80000000;
-  }
-  t.rec[i] = r;
-}
-
 // Tile counts (CLEAR_TILES) and, once after allocation, every slot of a
 // table (CLEAR_ALL_SLOTS), over a grid.
-__global__ void k_clear_step(PairTable next, int* dcount, long long ndt, int* lcount,
+__global__ void k_clear_grid(PairTable table, int* dcount, long long ndt, int* lcount,
                              long long nlt, int what) {
   const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const long long stride = (long long)gridDim.x * blockDim.x;
@@ -45,38 +35,39 @@ __global__ void k_clear_step(PairTable next, int* dcount, long long ndt, int* lc
     for (long long i = tid; i < nlt; i += stride) lcount[i] = 0;
   }
   if (what & CLEAR_ALL_SLOTS)
-    for (long long i = tid; i < next.cap; i += stride) clear_slot(next, i);
+    for (long long i = tid; i < table.cap; i += stride) clear_slot(table, i);
 }
 
-// The next step's contact state (CLEAR_CONTACT), one workgroup: the slots
-// the table's list names, the contact forces and slots, and the detection
-// counters; the list count is reset after the workgroup barrier, when
-// every thread has read it.
+// The slots a table's list names and the particles' contact slots
+// (CLEAR_TABLE), the contact forces and the counters (CLEAR_RESULTS), one
+// workgroup: the list count is reset after the workgroup barrier, when every
+// thread has read it.
 constexpr int CLEAR_THREADS = 1024;
-__global__ __launch_bounds__(CLEAR_THREADS) void k_clear_contact(PairTable next, double* Fc,
-                                                                 double* Tc, int np,
-                                                                 int* ccount, Counters* ctr) {
+__global__ __launch_bounds__(CLEAR_THREADS) void k_clear_state(PairTable table, double* Fc,
+                                                               double* Tc, int np, int* ccount,
+                                                               Counters* ctr, int what) {
   const int tid = (int)threadIdx.x;
-  const int nl = *next.nlist;
-  for (int i = tid; i < nl; i += CLEAR_THREADS) clear_slot(next, next.list[i]);
-  for (long long i = tid; i < 3LL * np; i += CLEAR_THREADS) {
-    Fc[i] = 0.0;
-    Tc[i] = 0.0;
+  if (what & CLEAR_TABLE) {
+    const int nl = *table.nlist;
+    for (int i = tid; i < nl; i += CLEAR_THREADS) clear_slot(table, table.list[i]);
+    for (int i = tid; i < np; i += CLEAR_THREADS) ccount[i] = 0;
   }
-  for (int i = tid; i < np; i += CLEAR_THREADS) ccount[i] = 0;
-  if (tid == 0) {
-    ctr->det_pairs = 0;
-    ctr->det_cells = 0;
-    ctr->samples = 0;
+  if (what & CLEAR_RESULTS) {
+    for (long long i = tid; i < 3LL * np; i += CLEAR_THREADS) {
+      Fc[i] = 0.0;
+      Tc[i] = 0.0;
+    }
+    if (tid == 0) {
+      ctr->det_pairs = 0;
+      ctr->det_cells = 0;
+      ctr->samples = 0;
+    }
   }
   __syncthreads();
-  if (tid == 0) *next.nlist = 0;
-}
-
-__global__ void k_keep(PairTable from, PairTable to, Counters* ctr) {
-  const long long s = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= from.cap) return;
-  keep_slot(from, to, s, ctr);
+  if (tid == 0) {
+    if (what & CLEAR_TABLE) *table.nlist = 0;
+    *running_samples(ctr) = 0;
+  }
 }
 
 struct Body {
@@ -248,7 +239,7 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
   ok = ok && hi[0] > lo[0] && hi[1] > lo[1] && hi[2] > lo[2];
   // midpoint samples of this record (each evaluates both members)
   if (threadIdx.x == 0)
-    atomicAdd(&ctr->samples,
+    atomicAdd(running_samples(ctr),
               (unsigned long long)(nfaces * nc * nc + (ok ? nc * nc * nc : 0)));
 
   // ---- overlap integration ------------------------------------------------
@@ -423,41 +414,35 @@ __global__ __launch_bounds__(TREAT_WAVES* WAVE) void k_treat(PairTable t, Partic
 
 }  // namespace
 
-hipError_t launch_clear_step(Ctx& c, PairTable next, int what, hipStream_t s) {
+hipError_t launch_clear(Ctx& c, PairTable table, int what) {
   const long long ndt = (long long)c.g.dtx * c.g.dty * c.g.dtz;
   const long long nlt = (long long)c.g.ltx * c.g.lty * c.g.ltz;
   if (what & (CLEAR_TILES | CLEAR_ALL_SLOTS)) {
-    long long work = (what & CLEAR_ALL_SLOTS) ? next.cap : 0;
+    long long work = (what & CLEAR_ALL_SLOTS) ? table.cap : 0;
     if ((what & CLEAR_TILES) && ndt > work) work = ndt;
     long long blocks = (work + 255) / 256;
     if (blocks > 4096) blocks = 4096;
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_clear_step, dim3((unsigned)blocks), dim3(256), 0, s, next,
+    hipLaunchKernelGGL(k_clear_grid, dim3((unsigned)blocks), dim3(256), 0, c.stream, table,
                        c.tl.dcount, ndt, c.tl.lcount, nlt, what);
   }
-  if (what & CLEAR_CONTACT)
-    hipLaunchKernelGGL(k_clear_contact, dim3(1), dim3(CLEAR_THREADS), 0, s, next, c.Fc,
-                       c.Tc, c.np, c.tl.ccount, c.counters);
+  if (what & (CLEAR_TABLE | CLEAR_RESULTS))
+    hipLaunchKernelGGL(k_clear_state, dim3(1), dim3(CLEAR_THREADS), 0, c.stream, table, c.Fc,
+                       c.Tc, c.np, c.tl.ccount, c.counters, what);
   return hipGetLastError();
 }
 
-hipError_t launch_keep(Ctx& c, PairTable from, PairTable to) {
-  hipLaunchKernelGGL(k_keep, dim3((unsigned)((from.cap + 255) / 256)), dim3(256),
-                     0, c.stream, from, to, c.counters);
-  return hipGetLastError();
-}
-
-hipError_t launch_treat(Ctx& c, PairTable t, hipStream_t s) {
+hipError_t launch_treat(Ctx& c, PairTable t) {
   const dim3 nb((unsigned)(t.cap < TREAT_BLOCKS ? t.cap : TREAT_BLOCKS));
   const dim3 nt(TREAT_WAVES * WAVE);
   const FastDiv fnc = make_fastdiv((unsigned)c.ph.n_c);
   if (c.has_ellipsoid)
-    hipLaunchKernelGGL((k_treat<true, true>), nb, nt, 0, s, t, c.part, c.g, c.ph, fnc, c.tl,
+    hipLaunchKernelGGL((k_treat<true, true>), nb, nt, 0, c.stream, t, c.part, c.g, c.ph, fnc, c.tl,
                        c.counters);
   else if (c.has_poly)
-    hipLaunchKernelGGL(k_treat<true>, nb, nt, 0, s, t, c.part, c.g, c.ph, fnc, c.tl, c.counters);
+    hipLaunchKernelGGL(k_treat<true>, nb, nt, 0, c.stream, t, c.part, c.g, c.ph, fnc, c.tl, c.counters);
   else
-    hipLaunchKernelGGL(k_treat<false>, nb, nt, 0, s, t, c.part, c.g, c.ph, fnc, c.tl, c.counters);
+    hipLaunchKernelGGL(k_treat<false>, nb, nt, 0, c.stream, t, c.part, c.g, c.ph, fnc, c.tl, c.counters);
   return hipGetLastError();
 }
 

@@ -12,6 +12,7 @@
 // (count of flagged nodes, bounding box of their images in the frame of the
 // lower-id particle) and then committed with one set of atomics per pair
 // and tile into the open-addressing pair table.
+#include "balance.h"
 #include "context.h"
 
 namespace hlbm {
@@ -63,8 +64,17 @@ __device__ void commit_pair(PairTable t, Counters* ctr, int a, int b,
 template <bool POLY, bool ELL = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? (ELL ? 4 : 5) : 8, 8))) void k_detect(Particles P, Geom g, Phys ph,
                                                 Tiles tl, int* __restrict__ owner,
-                                                PairTable tab, Counters* ctr) {
+                                                PairTable tab, Counters* ctr,
+                                                int* from_nlist,
+                                                const double* __restrict__ bal_parts) {
   const int lane = threadIdx.x % WAVE;
+  if (bal_parts && blockIdx.x == gridDim.x - 1) {
+    // one workgroup past the tiles: the balance controller
+    if (threadIdx.x < WAVE) balance_stage2(bal_parts, ctr, ph, 0);
+    return;
+  }
+  // the previous table's list: carried over and cleared by the motion kernel
+  if (from_nlist && blockIdx.x == 0 && threadIdx.x == 0) *from_nlist = 0;
   // tile id, uniform over the wavefront (fewer than 2^31 tiles: the cell
   // count is bounded on the host)
   const unsigned ntiles = (unsigned)g.dtx * (unsigned)g.dty * (unsigned)g.dtz;
@@ -250,18 +260,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? (ELL
 
 }  // namespace
 
-hipError_t launch_detect(Ctx& c, PairTable to) {
+hipError_t launch_detect(Ctx& c, PairTable to, const PairTable* from, bool balance) {
   const long long ntiles = (long long)c.g.dtx * c.g.dty * c.g.dtz;
-  const unsigned blocks = (unsigned)((ntiles + 3) / 4);
+  const size_t nlt = (size_t)c.g.ltx * c.g.lty * c.g.ltz;
+  const dim3 nb((unsigned)((ntiles + 3) / 4) + (balance ? 1u : 0u)), nt(256);
+  int* nlist = from ? from->nlist : nullptr;
+  const double* parts = balance ? c.bal_part + 4 * nlt : nullptr;
   if (c.has_ellipsoid)
-    hipLaunchKernelGGL((k_detect<true, true>), dim3(blocks), dim3(256), 0, c.stream, c.part,
-                     c.g, c.ph, c.tl, c.owner, to, c.counters);
+    hipLaunchKernelGGL((k_detect<true, true>), nb, nt, 0, c.stream, c.part, c.g, c.ph, c.tl,
+                       c.owner, to, c.counters, nlist, parts);
   else if (c.has_poly)
-    hipLaunchKernelGGL(k_detect<true>, dim3(blocks), dim3(256), 0, c.stream, c.part,
-                     c.g, c.ph, c.tl, c.owner, to, c.counters);
+    hipLaunchKernelGGL(k_detect<true>, nb, nt, 0, c.stream, c.part, c.g, c.ph, c.tl, c.owner, to,
+                       c.counters, nlist, parts);
   else
-    hipLaunchKernelGGL(k_detect<false>, dim3(blocks), dim3(256), 0, c.stream, c.part,
-                     c.g, c.ph, c.tl, c.owner, to, c.counters);
+    hipLaunchKernelGGL(k_detect<false>, nb, nt, 0, c.stream, c.part, c.g, c.ph, c.tl, c.owner, to,
+                       c.counters, nlist, parts);
   return hipGetLastError();
 }
 

@@ -1021,6 +1021,8 @@ __global__ __launch_bounds__(256) void k_mea(const S* __restrict__ fs,
   }
   commit_group(o, s, t, lid, red[nd.wave], tl.ovf);
   store_block(red, list, ent, cnt, g, tl.part);
+  // (as in the lattice pass: every wavefront has read the count)
+  if (threadIdx.x == 0) tl.lcount[tile] = 0;
 }
 
 // Mass and momentum of a population field, per lattice block (the initial
@@ -1043,64 +1045,6 @@ __global__ __launch_bounds__(256) void k_pop_moments(const S* __restrict__ f, Ge
     }
   }
   block_sums4(m, j0, j1, j2, nd, out);
-}
-
-// Zero-net-flux balance controller (balance mode 2).  The lattice blocks'
-// (mass, momentum) sums are added in two fixed-order stages: BAL_PARTS
-// workgroups each sum one contiguous range of blocks (thread t takes
-// entries t, t + 256, .. of the range, then a fixed tree), then one
-// workgroup sums the BAL_PARTS results the same way, giving the lattice mass
-// M and momentum P.  init: M, P_{-1} = P, b_0 = -P / M.  Update after the
-// collision of step t (which used b_t): C_t = P_t - P_{t-1} - b_t M,
-// b_{t+1} = -(P_t + C_t) / M.  The acceleration in use is a = fluid_accel + b.
-__device__ void tree_sum4(double (*sh)[4], double* acc) {
-  for (int k = 0; k < 4; ++k) sh[threadIdx.x][k] = acc[k];
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w)
-      for (int k = 0; k < 4; ++k) sh[threadIdx.x][k] += sh[threadIdx.x + w][k];
-    __syncthreads();
-  }
-}
-
-__global__ __launch_bounds__(256) void k_balance_part(const double* __restrict__ part,
-                                                      unsigned nblocks,
-                                                      double* __restrict__ out) {
-  __shared__ double sh[256][4];
-  const unsigned chunk = (nblocks + BAL_PARTS - 1) / BAL_PARTS;
-  const unsigned b0 = blockIdx.x * chunk;
-  const unsigned b1 = b0 + chunk < nblocks ? b0 + chunk : nblocks;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (unsigned b = b0 + threadIdx.x; b < b1; b += 256)
-    for (int k = 0; k < 4; ++k) acc[k] += part[4 * (size_t)b + k];
-  tree_sum4(sh, acc);
-  if (threadIdx.x < 4) out[4 * blockIdx.x + threadIdx.x] = sh[0][threadIdx.x];
-}
-
-__global__ __launch_bounds__(256) void k_balance(const double* __restrict__ parts,
-                                                 Counters* ctr, Phys ph, int init) {
-  __shared__ double sh[256][4];
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (unsigned b = threadIdx.x; b < BAL_PARTS; b += 256)
-    for (int k = 0; k < 4; ++k) acc[k] += parts[4 * (size_t)b + k];
-  tree_sum4(sh, acc);
-  if (threadIdx.x == 0) {
-    if (init) ctr->bal_M = sh[0][0];
-    const double M = ctr->bal_M;
-    for (int k = 0; k < 3; ++k) {
-      const double P = sh[0][1 + k];
-      double b;
-      if (init) {
-        b = -P / M;
-      } else {
-        const double Ct = P - ctr->bal_P[k] - ctr->bal_b[k] * M;
-        b = -(P + Ct) / M;
-      }
-      ctr->bal_b[k] = b;
-      ctr->bal_P[k] = P;
-      ctr->bal_a[k] = ph.a_ext[k] + b;
-    }
-  }
 }
 
 template <typename S>
@@ -1201,14 +1145,8 @@ static void run_pop_moments(Ctx& c, const void* f) {
                      c.stream, (const S*)f, c.g, c.bal_part);
 }
 
-hipError_t launch_balance(Ctx& c, const void* f, int init, hipStream_t st) {
-  if (init) DISPATCH(c, run_pop_moments, (c, f));
-  const unsigned nb = tile_blocks(c.g);
-  double* parts = c.bal_part + 4 * (size_t)nb;
-  hipLaunchKernelGGL(k_balance_part, dim3(BAL_PARTS), dim3(256), 0, st, c.bal_part,
-                     nb, parts);
-  hipLaunchKernelGGL(k_balance, dim3(1), dim3(256), 0, st, parts, c.counters, c.ph,
-                     init);
+hipError_t launch_pop_moments(Ctx& c, const void* f) {
+  DISPATCH(c, run_pop_moments, (c, f));
   return hipGetLastError();
 }
 

@@ -8,6 +8,7 @@
 //     wave-uniform) and lane 0 stores it;
 //  3. the lanes enumerate the tiles the particle's reach box touches and
 //     append (particle id, enumeration index) to each tile's candidate list.
+#include "balance.h"
 #include "context.h"
 
 namespace hlbm {
@@ -73,21 +74,46 @@ __device__ TileSpan axis_tiles(double c, double e, int n, int nt, int ts,
 }
 
 constexpr int UB = 4;   // binning: tiles per lane and round
+constexpr unsigned KEEP_BLOCKS = 64;   // workgroups of the contact carry-over
 
 __global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
                                                   double* __restrict__ Fh,
                                                   double* __restrict__ Th,
                                                   double* __restrict__ Fc,
                                                   double* __restrict__ Tc,
-                                                  int move, Tiles tl, Counters* ctr,
-                                                  PairTable keep_from, PairTable keep_to) {
+                                                  int move, int bin_blocks, Tiles tl,
+                                                  Counters* ctr, PairTable keep_from,
+                                                  PairTable keep_to, int keep_blocks,
+                                                  const double* __restrict__ bal_part,
+                                                  unsigned bal_blocks,
+                                                  double* __restrict__ bal_out) {
   const int ip = blockIdx.x;
   if (ip >= P.n) {
-    // blocks past the particles: the contact carry-over of the pair table,
-    // one slot per thread (independent of this kernel's particle work; the
-    // detection that follows inserts into the same next table)
-    const long long s = (long long)(ip - P.n) * WAVE + threadIdx.x;
-    if (s < keep_from.cap) keep_slot(keep_from, keep_to, s, ctr);
+    // blocks past the particles (independent of this kernel's particle work)
+    const int k = ip - P.n;
+    if (k >= keep_blocks) {
+      balance_stage1(bal_part, bal_blocks, (unsigned)(k - keep_blocks), bal_out);
+      return;
+    }
+    // the contact carry-over of the pair table, one listed slot per thread
+    // and round (the detection that follows inserts into the same next
+    // table); the slot is then cleared, so that this table is empty when it
+    // is the next one again (its list count is reset by the detection)
+    const int n = *keep_from.nlist;
+    for (int i = k * WAVE + (int)threadIdx.x; i < n; i += keep_blocks * WAVE) {
+      const int s = keep_from.list[i];
+      keep_slot(keep_from, keep_to, s, ctr);
+      clear_slot(keep_from, s);
+    }
+    if (k == 0 && threadIdx.x == 0) {
+      // the treatment's sample count, and the counters of the detection
+      // that follows
+      unsigned long long* run = running_samples(ctr);
+      ctr->samples = *run;
+      *run = 0;
+      ctr->det_pairs = 0;
+      ctr->det_cells = 0;
+    }
     return;
   }
   const int lane = threadIdx.x;
@@ -129,6 +155,8 @@ __global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
     double Fcp[3] = {0.0, 0.0, 0.0}, Tcp[3] = {0.0, 0.0, 0.0};
     {
       int nc = tl.ccount[ip];
+      // (read by this wavefront alone: empty again for the next treatment)
+      if (nc && lane == 0) tl.ccount[ip] = 0;
       nc = nc < MAXC ? nc : MAXC;
       const size_t e0 = (size_t)ip * MAXC;
       // every slot's values are loaded at once (lane k: slot k) and then
@@ -327,7 +355,7 @@ __global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
     }
   }
   // lattice blocks, with the particle's own enumeration index
-  {
+  if (bin_blocks) {
     const int nt3[3] = {g.ltx, g.lty, g.ltz};
     const int ts3[3] = {LX, LY, LZ};
     TileSpan sp[3];
@@ -369,17 +397,42 @@ __global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
   }
 }
 
+__global__ __launch_bounds__(64) void k_balance_part(const double* __restrict__ part,
+                                                     unsigned nblocks,
+                                                     double* __restrict__ out) {
+  balance_stage1(part, nblocks, blockIdx.x, out);
+}
+
+__global__ __launch_bounds__(64) void k_balance(const double* __restrict__ parts, Counters* ctr,
+                                                Phys ph, int init) {
+  balance_stage2(parts, ctr, ph, init);
+}
+
 }  // namespace
 
-hipError_t launch_particles(Ctx& c, int move, const PairTable* keep_from,
-                            const PairTable* keep_to) {
+hipError_t launch_particles(Ctx& c, int move, bool bin_blocks, const PairTable* keep_from,
+                            const PairTable* keep_to, bool balance) {
   PairTable none = {nullptr, nullptr, 0, nullptr, nullptr};
   const PairTable from = keep_from ? *keep_from : none;
   const PairTable to = keep_to ? *keep_to : none;
-  const unsigned kb = (unsigned)((from.cap + WAVE - 1) / WAVE);
-  if (c.np + kb == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_particles, dim3(c.np + kb), dim3(64), 0, c.stream, c.part,
-                     c.g, c.ph, c.Fh, c.Th, c.Fc, c.Tc, move, c.tl, c.counters, from, to);
+  unsigned kb = (unsigned)((from.cap + WAVE - 1) / WAVE);
+  if (kb > KEEP_BLOCKS) kb = KEEP_BLOCKS;
+  const unsigned bb = balance ? BAL_PARTS : 0;
+  if (c.np + kb + bb == 0) return hipSuccess;
+  const unsigned nlt = (unsigned)c.g.ltx * (unsigned)c.g.lty * (unsigned)c.g.ltz;
+  hipLaunchKernelGGL(k_particles, dim3(c.np + kb + bb), dim3(64), 0, c.stream, c.part, c.g,
+                     c.ph, c.Fh, c.Th, c.Fc, c.Tc, move, bin_blocks ? 1 : 0, c.tl, c.counters,
+                     from, to, (int)kb, c.bal_part, nlt,
+                     c.bal_part ? c.bal_part + 4 * (size_t)nlt : nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_balance(Ctx& c, int init) {
+  const unsigned nlt = (unsigned)c.g.ltx * (unsigned)c.g.lty * (unsigned)c.g.ltz;
+  double* parts = c.bal_part + 4 * (size_t)nlt;
+  hipLaunchKernelGGL(k_balance_part, dim3(BAL_PARTS), dim3(WAVE), 0, c.stream, c.bal_part, nlt,
+                     parts);
+  hipLaunchKernelGGL(k_balance, dim3(1), dim3(WAVE), 0, c.stream, parts, c.counters, c.ph, init);
   return hipGetLastError();
 }
 
