@@ -135,8 +135,8 @@ hlbm_status prologue(Ctx& c) {
   drop_graphs(c);
   const int p = c.tcur;
   const size_t nb = sizeof(double) * 3 * (c.np > 0 ? c.np : 1);
-  HIPCHECK(launch_clear(c, c.tab[1 - p], CLEAR_TABLE));
-  HIPCHECK(launch_clear(c, c.tab[p], CLEAR_TABLE | CLEAR_RESULTS | CLEAR_TILES));
+  HIPCHECK(launch_clear(c, c.tab[1 - p], CLEAR_TABLE | CLEAR_COUNT));
+  HIPCHECK(launch_clear(c, c.tab[p], CLEAR_TABLE | CLEAR_COUNT | CLEAR_RESULTS | CLEAR_TILES));
   HIPCHECK(hipMemsetAsync(c.Fh, 0, nb, c.stream));
   HIPCHECK(hipMemsetAsync(c.Th, 0, nb, c.stream));
   HIPCHECK(hipMemsetAsync(c.tl.ovf, 0, 2 * nb, c.stream));
@@ -1188,11 +1188,12 @@ hlbm_status hlbm_counters(hlbm_ctx* h, long long* pairs, long long* cells,
   if (!h) return HLBM_E_ARG;
   Ctx& c = h->c;
   Counters k;
+  HIPCHECK(launch_count(c, c.tab[c.tcur]));
   HIPCHECK(hipMemcpyAsync(&k, c.counters, sizeof k, hipMemcpyDeviceToHost, c.stream));
   HIPCHECK(hipStreamSynchronize(c.stream));
   if (pairs) *pairs = (long long)k.det_pairs;
   if (cells) *cells = (long long)k.det_cells;
-  if (total_cells) *total_cells = (long long)k.total_cells;
+  if (total_cells) *total_cells = (long long)(k.total_cells + k.det_cells);
   if (steps) *steps = c.step;
   if (samples) *samples = (long long)k.samples;
   return HLBM_OK;
@@ -1263,6 +1264,7 @@ hlbm_status hlbm_get_state(hlbm_ctx* h, void* blob, size_t* bytes) {
   hd.psum_bytes = c.psum_bytes;
   hd.tab_bytes = key_block_bytes((int)cap) + cap * sizeof(PairRec);
   hd.owner_bytes = sizeof(int) * (size_t)c.g.ncell;
+  HIPCHECK(launch_count(c, c.tab[c.tcur]));
   char* o = (char*)blob;
   memcpy(o, &hd, sizeof hd);
   o += sizeof hd;
@@ -1282,6 +1284,11 @@ hlbm_status hlbm_get_state(hlbm_ctx* h, void* blob, size_t* bytes) {
   HIPCHECK(get(c.owner, sizeof(int) * (size_t)c.g.ncell));
   HIPCHECK(get(c.counters, sizeof(Counters)));
   HIPCHECK(hipStreamSynchronize(c.stream));
+  // (a saved state's total includes the latest detection)
+  Counters k;
+  memcpy(&k, o - sizeof k, sizeof k);
+  k.total_cells += k.det_cells;
+  memcpy(o - sizeof k, &k, sizeof k);
   *bytes = (size_t)need;
   return HLBM_OK;
 }
@@ -1323,6 +1330,10 @@ hlbm_status hlbm_set_state(hlbm_ctx* h, const void* blob, size_t bytes) {
     HIPCHECK(put(c.tab[k].rec, sizeof(PairRec) * cap));
   }
   HIPCHECK(put(c.owner, sizeof(int) * (size_t)c.g.ncell));
+  Counters k;
+  memcpy(&k, o, sizeof k);
+  k.total_cells -= k.det_cells;
+  o = (const char*)&k;
   HIPCHECK(put(c.counters, sizeof(Counters)));
   // what a step leaves empty (states saved by earlier builds left these to
   // the next step's start)

@@ -19,7 +19,8 @@ struct PairRec {
   int a, b;
   int count;
   int rlo[3], rhi[3];
-  int carried, established, age, n_in, keep, pad;
+  int carried, established, age, n_in, keep;
+  int samples;   // midpoint samples of the latest treatment
   double lo[3], hi[3];
   double damping;
   double volume, centroid[3], normal[3], depth, fn, force_a[3];
@@ -49,9 +50,11 @@ __device__ inline void list_slot(const PairTable& t, uint32_t h) {
 
 // Device counters and flags (one small block of device memory).
 struct Counters {
-  unsigned long long det_pairs;    // keys with count > 0 (latest detection)
-  unsigned long long det_cells;    // sum of counts (latest detection)
-  unsigned long long total_cells;  // sum over all detections
+  // keys with count > 0 and sum of their counts, latest detection: formed
+  // from the records when asked for (launch_count)
+  unsigned long long det_pairs;
+  unsigned long long det_cells;
+  unsigned long long total_cells;  // sum over the detections before the latest
   unsigned long long steps;
   unsigned long long samples;      // midpoint samples of the latest treatment
   int tile_overflow;
@@ -64,9 +67,10 @@ struct Counters {
   double bal_b[3], bal_P[3], bal_M, bal_a[3];
 };
 
-// The counter block is followed by the midpoint samples of the treatment that
-// is running; the motion kernel moves them into Counters::samples, so they
-// are zero between steps (and not part of a saved state).
+// The counter block is followed by a running sum of the treatment's midpoint
+// samples: the carry-over adds the records' (one atomic per wavefront),
+// detection moves the sum into Counters::samples.  It is zero between steps
+// (and not part of a saved state).
 __host__ __device__ inline unsigned long long* running_samples(Counters* c) {
   return (unsigned long long*)(c + 1);
 }
@@ -300,10 +304,17 @@ struct Ctx {
 // Bookkeeping outside the steps (a step leaves everything as the next one
 // needs it): CLEAR_TABLE the listed slots of a pair table and the particles'
 // contact slots, CLEAR_TILES the detection-tile and lattice-block counts,
-// CLEAR_RESULTS the contact forces and the detection and sample counters,
-// CLEAR_ALL_SLOTS every slot of the table (once, after allocation)
-constexpr int CLEAR_TABLE = 1, CLEAR_TILES = 2, CLEAR_RESULTS = 4, CLEAR_ALL_SLOTS = 8;
+// CLEAR_RESULTS the contact forces and the sample counter, CLEAR_ALL_SLOTS
+// every slot of the table (once, after allocation); CLEAR_COUNT adds the
+// cells of the slots that CLEAR_TABLE empties to the total
+constexpr int CLEAR_TABLE = 1, CLEAR_TILES = 2, CLEAR_RESULTS = 4, CLEAR_ALL_SLOTS = 8,
+              CLEAR_COUNT = 16;
 hipError_t launch_clear(Ctx& c, PairTable table, int what);
+// pairs and cells of the detection that filled a table.  The records hold the
+// counts already; an atomic per committed tile on shared counters had cost
+// detection more than all the rest of it where contacts are many (120^3 nodes,
+// 905 settling spheres in contact: 99 us, 14 us without)
+hipError_t launch_count(Ctx& c, PairTable table);
 // move: 0 bin only, 1 gather the hydrodynamic force and move, 2 move with
 // the stored hydrodynamic force (later sub-steps).  bin_blocks: also bin into
 // lattice blocks (the last binning before a lattice pass).

@@ -39,8 +39,8 @@ __global__ void k_clear_grid(PairTable table, int* dcount, long long ndt, int* l
 }
 
 // The slots a table's list names and the particles' contact slots
-// (CLEAR_TABLE), the contact forces and the counters (CLEAR_RESULTS), one
-// workgroup: the list count is reset after the workgroup barrier, when every
+// (CLEAR_TABLE), the contact forces and the sample counter (CLEAR_RESULTS),
+// one workgroup: the list count is reset after the workgroup barrier, when every
 // thread has read it.
 constexpr int CLEAR_THREADS = 1024;
 __global__ __launch_bounds__(CLEAR_THREADS) void k_clear_state(PairTable table, double* Fc,
@@ -49,7 +49,12 @@ __global__ __launch_bounds__(CLEAR_THREADS) void k_clear_state(PairTable table, 
   const int tid = (int)threadIdx.x;
   if (what & CLEAR_TABLE) {
     const int nl = *table.nlist;
-    for (int i = tid; i < nl; i += CLEAR_THREADS) clear_slot(table, table.list[i]);
+    for (int i = tid; i < nl; i += CLEAR_THREADS) {
+      const int s = table.list[i];
+      if (what & CLEAR_COUNT)
+        atomicAdd(&ctr->total_cells, (unsigned long long)table.rec[s].count);
+      clear_slot(table, s);
+    }
     for (int i = tid; i < np; i += CLEAR_THREADS) ccount[i] = 0;
   }
   if (what & CLEAR_RESULTS) {
@@ -57,16 +62,34 @@ __global__ __launch_bounds__(CLEAR_THREADS) void k_clear_state(PairTable table, 
       Fc[i] = 0.0;
       Tc[i] = 0.0;
     }
-    if (tid == 0) {
-      ctr->det_pairs = 0;
-      ctr->det_cells = 0;
-      ctr->samples = 0;
-    }
+    if (tid == 0) ctr->samples = 0;
   }
   __syncthreads();
   if (tid == 0) {
     if (what & CLEAR_TABLE) *table.nlist = 0;
     *running_samples(ctr) = 0;
+  }
+}
+
+__global__ __launch_bounds__(CLEAR_THREADS) void k_count(PairTable table, Counters* ctr) {
+  __shared__ unsigned long long sum[2];
+  if (threadIdx.x == 0) sum[0] = sum[1] = 0;
+  __syncthreads();
+  const int n = *table.nlist;
+  unsigned long long pairs = 0, cells = 0;
+  for (int i = (int)threadIdx.x; i < n; i += CLEAR_THREADS) {
+    const int c = table.rec[table.list[i]].count;
+    pairs += c > 0 ? 1 : 0;
+    cells += (unsigned)c;
+  }
+  if (pairs) {
+    atomicAdd(&sum[0], pairs);
+    atomicAdd(&sum[1], cells);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    ctr->det_pairs = sum[0];
+    ctr->det_cells = sum[1];
   }
 }
 
@@ -238,9 +261,7 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
   }
   ok = ok && hi[0] > lo[0] && hi[1] > lo[1] && hi[2] > lo[2];
   // midpoint samples of this record (each evaluates both members)
-  if (threadIdx.x == 0)
-    atomicAdd(running_samples(ctr),
-              (unsigned long long)(nfaces * nc * nc + (ok ? nc * nc * nc : 0)));
+  if (threadIdx.x == 0) rec->samples = nfaces * nc * nc + (ok ? nc * nc * nc : 0);
 
   // ---- overlap integration ------------------------------------------------
   int n_in = 0;
@@ -429,6 +450,11 @@ hipError_t launch_clear(Ctx& c, PairTable table, int what) {
   if (what & (CLEAR_TABLE | CLEAR_RESULTS))
     hipLaunchKernelGGL(k_clear_state, dim3(1), dim3(CLEAR_THREADS), 0, c.stream, table, c.Fc,
                        c.Tc, c.np, c.tl.ccount, c.counters, what);
+  return hipGetLastError();
+}
+
+hipError_t launch_count(Ctx& c, PairTable table) {
+  hipLaunchKernelGGL(k_count, dim3(1), dim3(CLEAR_THREADS), 0, c.stream, table, c.counters);
   return hipGetLastError();
 }
 

@@ -49,14 +49,11 @@ __device__ void commit_pair(PairTable t, Counters* ctr, int a, int b,
       PairRec* r = &t.rec[s];
       r->a = a;
       r->b = b;
-      const int old = atomicAdd(&r->count, cnt);
-      if (old == 0) atomicAdd(&ctr->det_pairs, 1ull);
+      atomicAdd(&r->count, cnt);
       for (int k = 0; k < 3; ++k) {
         atomicMin(&r->rlo[k], lo[k]);
         atomicMax(&r->rhi[k], hi[k]);
       }
-      atomicAdd(&ctr->det_cells, (unsigned long long)cnt);
-      atomicAdd(&ctr->total_cells, (unsigned long long)cnt);
     }
   }
 }
@@ -68,19 +65,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? (ELL
                                                 int* from_nlist,
                                                 const double* __restrict__ bal_parts) {
   const int lane = threadIdx.x % WAVE;
-  if (bal_parts && blockIdx.x == gridDim.x - 1) {
-    // one workgroup past the tiles: the balance controller
-    if (threadIdx.x < WAVE) balance_stage2(bal_parts, ctr, ph, 0);
-    return;
-  }
-  // the previous table's list: carried over and cleared by the motion kernel
-  if (from_nlist && blockIdx.x == 0 && threadIdx.x == 0) *from_nlist = 0;
   // tile id, uniform over the wavefront (fewer than 2^31 tiles: the cell
   // count is bounded on the host)
   const unsigned ntiles = (unsigned)g.dtx * (unsigned)g.dty * (unsigned)g.dtz;
   const unsigned tile =
       blockIdx.x * 4u + (unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x) / WAVE;
-  if (tile >= ntiles) return;                     // whole wavefront exits
+  if (tile >= ntiles) {                           // whole wavefront exits
+    // the first wavefront past the tiles (there is always one; the check of
+    // the tile's range is the only one the others pay): the list of the
+    // previous table, carried over and cleared by the motion kernel, the
+    // samples that it summed, and the balance controller
+    if (tile == ntiles) {
+      if (from_nlist && lane == 0) {
+        *from_nlist = 0;
+        unsigned long long* run = running_samples(ctr);
+        ctr->samples = *run;
+        *run = 0;
+      }
+      if (bal_parts) balance_stage2(bal_parts, ctr, ph, 0);
+    }
+    return;
+  }
   const unsigned tyz = fdiv(tile, g.fdtx);
   const unsigned utz = fdiv(tyz, g.fdty);
   const int tx = (int)(tile - tyz * (unsigned)g.dtx);
@@ -263,7 +268,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? (ELL
 hipError_t launch_detect(Ctx& c, PairTable to, const PairTable* from, bool balance) {
   const long long ntiles = (long long)c.g.dtx * c.g.dty * c.g.dtz;
   const size_t nlt = (size_t)c.g.ltx * c.g.lty * c.g.ltz;
-  const dim3 nb((unsigned)((ntiles + 3) / 4) + (balance ? 1u : 0u)), nt(256);
+  const dim3 nb((unsigned)(ntiles / 4 + 1)), nt(256);
   int* nlist = from ? from->nlist : nullptr;
   const double* parts = balance ? c.bal_part + 4 * nlt : nullptr;
   if (c.has_ellipsoid)

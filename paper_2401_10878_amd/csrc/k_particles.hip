@@ -100,19 +100,23 @@ __global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
     // table); the slot is then cleared, so that this table is empty when it
     // is the next one again (its list count is reset by the detection)
     const int n = *keep_from.nlist;
+    int cells = 0;
+    long long samples = 0;
     for (int i = k * WAVE + (int)threadIdx.x; i < n; i += keep_blocks * WAVE) {
       const int s = keep_from.list[i];
+      samples += keep_from.rec[s].samples;
+      cells += keep_from.rec[s].count;
       keep_slot(keep_from, keep_to, s, ctr);
       clear_slot(keep_from, s);
     }
-    if (k == 0 && threadIdx.x == 0) {
-      // the treatment's sample count, and the counters of the detection
-      // that follows
-      unsigned long long* run = running_samples(ctr);
-      ctr->samples = *run;
-      *run = 0;
-      ctr->det_pairs = 0;
-      ctr->det_cells = 0;
+    if (k * WAVE >= n) return;                    // uniform over the wavefront
+    // the treatment's samples (below 2^53: exact) and the cells of the
+    // detection that filled this table
+    const double sum = wave_sum((double)samples);
+    const int csum = wave_sum_i(cells);
+    if (threadIdx.x == 0) {
+      atomicAdd(running_samples(ctr), (unsigned long long)sum);
+      atomicAdd(&ctr->total_cells, (unsigned long long)csum);
     }
     return;
   }
