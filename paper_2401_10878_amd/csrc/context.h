@@ -156,6 +156,7 @@ struct Geom {
   FastDiv fltx, flty;     // divisions by ltx, lty
   int tile_cap;           // particles per candidate list (both tilings)
   int maxent;             // lattice blocks per particle (partial-sum slots)
+  int cached;             // both population buffers fit the Infinity Cache
   long long ncell;
 };
 

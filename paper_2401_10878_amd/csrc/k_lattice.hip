@@ -41,11 +41,7 @@ namespace {
 // Storage of the populations.  FP64 stores f itself; FP32 and binary16
 // store the deviation h = f - w_i from the rest weights ("shifted"), so that
 // rounding acts on the small part of f.  ld/st move the stored value h (or
-// f), full() turns it into f.  Stores, and the stream-collide pass's loads
-// (ldn), are non-temporal: each population is written once and read by the
-// next pass, and the arrays are hundreds of times the size of the caches
-// (6% less time for the stream-collide pass; the momentum-exchange pass,
-// which reads the same lines for neighbouring nodes, keeps ordinary loads).
+// f), full() turns it into f.
 template <typename S>
 struct Store;
 template <>
@@ -57,7 +53,6 @@ struct Store<double> {
     return *(const double*)((const char*)p + k * 8u);
   }
   __device__ static void st(double* p, int k, C v) { __builtin_nontemporal_store(v, p + k); }
-  __device__ static C ldn(const double* p, int k) { return __builtin_nontemporal_load(p + k); }
   __device__ static C as_stored(C v) { return v; }
 };
 template <>
@@ -69,7 +64,6 @@ struct Store<float> {
     return *(const float*)((const char*)p + k * 4u);
   }
   __device__ static void st(float* p, int k, C v) { __builtin_nontemporal_store(v, p + k); }
-  __device__ static C ldn(const float* p, int k) { return __builtin_nontemporal_load(p + k); }
   __device__ static C as_stored(C v) { return v; }
 };
 template <>
@@ -83,9 +77,6 @@ struct Store<__half> {
   __device__ static void st(__half* p, int k, C v) {
     __builtin_nontemporal_store(__half_as_ushort(__float2half_rn(v)), reinterpret_cast<unsigned short*>(p) + k);
   }
-  __device__ static C ldn(const __half* p, int k) {
-    return __half2float(__ushort_as_half(__builtin_nontemporal_load(reinterpret_cast<const unsigned short*>(p) + k)));
-  }
   // the value st writes, read back (round to nearest even)
   __device__ static C as_stored(C v) { return __half2float(__float2half_rn(v)); }
 };
@@ -95,31 +86,40 @@ __device__ inline int owner_at(const int* owner, unsigned b) {
 // Loads and stores at byte offset b of an array as raw buffer operations: a
 // scalar resource over the array from p (no range check is relied on; every
 // offset lies inside the array) and a 32-bit per-lane byte offset, which the
-// hardware adds without vector address arithmetic.  Populations
-// non-temporal, owner entries cached.
+// hardware adds without vector address arithmetic.
 __device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00020000);
 }
+// Access policy of the populations.  A pass reads what the pass before it
+// wrote: where both buffers fit the Infinity Cache (256 MB, on the memory
+// side) together, plain accesses find most of it there.  A larger lattice
+// keeps nothing either way, and its accesses are non-temporal, so that they
+// do not displace what is used again: the owner map, the candidate lists and
+// the particle records.  Measured, us per launch, non-temporal against plain:
+// 120^3 FP32 (263 MB) 82.5, 72.5; 151 x 89 x 67 binary16 (68 MB) 35.4, 30.6;
+// 256^3 FP64 (5.1 GB) 1043, 1156, and detection 89, 105.  The policy is a
+// template parameter: a branch between the two forms inside one kernel cost
+// 256^3 binary16 401 -> 448 us.
 constexpr int BUF_NT = 2;
-template <typename S>
+template <typename S, int AUX>
 __device__ inline typename Store<S>::C ld_buf(const S* base, unsigned b) {
   const __amdgpu_buffer_rsrc_t r = rsrc_of(base);
   if constexpr (sizeof(S) == 2)
-    return __half2float(__ushort_as_half(__builtin_amdgcn_raw_buffer_load_b16(r, b, 0, BUF_NT)));
+    return __half2float(__ushort_as_half(__builtin_amdgcn_raw_buffer_load_b16(r, b, 0, AUX)));
   else if constexpr (sizeof(S) == 4)
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, b, 0, BUF_NT));
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, b, 0, AUX));
   else
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, b, 0, BUF_NT));
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, b, 0, AUX));
 }
-template <typename S>
+template <typename S, int AUX>
 __device__ inline void st_buf(S* base, unsigned b, typename Store<S>::C v) {
   const __amdgpu_buffer_rsrc_t r = rsrc_of(base);
   if constexpr (sizeof(S) == 2)
-    __builtin_amdgcn_raw_buffer_store_b16(__half_as_ushort(__float2half_rn(v)), r, b, 0, BUF_NT);
+    __builtin_amdgcn_raw_buffer_store_b16(__half_as_ushort(__float2half_rn(v)), r, b, 0, AUX);
   else if constexpr (sizeof(S) == 4)
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, b, 0, BUF_NT);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, b, 0, AUX);
   else
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0)), v), r, b, 0, BUF_NT);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0)), v), r, b, 0, AUX);
 }
 __device__ inline int ld_owner_buf(const int* base, unsigned b) {
   return (int)__builtin_amdgcn_raw_buffer_load_b32(rsrc_of(base), b, 0, 0);
@@ -503,7 +503,7 @@ __device__ inline void commit_round(int q, const C* G, const C* T, int lid,
 // or f_i - w_i (FP64).  Blocks whose candidate list is empty (no particle
 // owns a node within one node of the block), and wavefronts without an owned
 // node or a neighbour of one, skip it.
-template <typename S, bool POLY, bool BAL, bool WALL, bool ELL = false>
+template <typename S, int POLICY, bool POLY, bool BAL, bool WALL, bool ELL = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     sizeof(S) == 8 ? 4 : (ELL ? 5 : (POLY && BAL ? 6 : 7)), 8))) void k_lattice(const S* __restrict__ src,
                                                  S* __restrict__ dst,
@@ -557,7 +557,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
       const bool bw = beyond(-cz(i)) != 0;
       const S* base = src + (size_t)(bw ? opp(i) : i) * (size_t)n +
                       (bw ? rowpl(0, 0) : rowpl(-cy(i), -cz(i)));
-      f[i] = ld_buf<S>(base, bw ? xo[1] : xo[1 - cx(i)]);
+      f[i] = ld_buf<S, POLICY>(base, bw ? xo[1] : xo[1 - cx(i)]);
     }
     if (wallm || wallp) {
 #pragma unroll
@@ -670,7 +670,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   }
   if (valid) {
 #pragma unroll
-    for (int i = 0; i < Q; ++i) st_buf<S>(dst + (size_t)i * (size_t)n + rowpl(0, 0), xo[1], f[i]);
+    for (int i = 0; i < Q; ++i)
+      st_buf<S, POLICY>(dst + (size_t)i * (size_t)n + rowpl(0, 0), xo[1], f[i]);
   }
   if (BAL) {
     // mass and momentum of the collided populations, per block in fixed
@@ -1107,20 +1108,27 @@ static unsigned tile_blocks(const Geom& g) {
   return (unsigned)g.ltx * (unsigned)g.lty * (unsigned)g.ltz;
 }
 
-template <typename S>
-static void run_lattice(Ctx& c, const void* src, void* dst) {
+template <typename S, int POLICY>
+static void run_lattice_policy(Ctx& c, const void* src, void* dst) {
   const bool bal = c.ph.bal_mode == 2, wall = c.g.periodic_z == 0;
   auto k = c.has_ellipsoid
-               ? (bal ? k_lattice<S, true, true, false, true>
-                      : (wall ? k_lattice<S, true, false, true, true>
-                              : k_lattice<S, true, false, false, true>))
+               ? (bal ? k_lattice<S, POLICY, true, true, false, true>
+                      : (wall ? k_lattice<S, POLICY, true, false, true, true>
+                              : k_lattice<S, POLICY, true, false, false, true>))
            : c.has_poly
-               ? (bal ? k_lattice<S, true, true, false>
-                      : (wall ? k_lattice<S, true, false, true> : k_lattice<S, true, false, false>))
-               : (bal ? k_lattice<S, false, true, false>
-                      : (wall ? k_lattice<S, false, false, true> : k_lattice<S, false, false, false>));
+               ? (bal ? k_lattice<S, POLICY, true, true, false>
+                      : (wall ? k_lattice<S, POLICY, true, false, true>
+                              : k_lattice<S, POLICY, true, false, false>))
+               : (bal ? k_lattice<S, POLICY, false, true, false>
+                      : (wall ? k_lattice<S, POLICY, false, false, true>
+                              : k_lattice<S, POLICY, false, false, false>));
   hipLaunchKernelGGL(k, dim3(tile_blocks(c.g)), dim3(256), 0, c.stream, (const S*)src,
                      (S*)dst, c.owner, c.part, c.g, c.ph, c.counters, c.bal_part, c.tl);
+}
+template <typename S>
+static void run_lattice(Ctx& c, const void* src, void* dst) {
+  if (c.g.cached) run_lattice_policy<S, 0>(c, src, dst);
+  else run_lattice_policy<S, BUF_NT>(c, src, dst);
 }
 
 hipError_t launch_lattice(Ctx& c, const void* src, void* dst) {
