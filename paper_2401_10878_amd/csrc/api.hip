@@ -160,8 +160,9 @@ hlbm_status prologue(Ctx& c) {
 // All kernels of a step run in order on one stream: contact treatment, motion
 // (with binning and the contact carry-over), detection, lattice pass, and
 // nothing between them, because each leaves its inputs as the next step needs
-// them: the carry-over clears the slots it reads, detection and the lattice
-// pass reset their counts, the motion kernel the particles' contact slots.
+// them: the carry-over clears the slots it reads (the next treatment resets
+// their list), detection and the lattice pass reset their counts, the motion
+// kernel the particles' contact slots.
 // (Treating the next step's contacts on a second stream beside the lattice
 // pass had hidden a treatment of 33 us and cost two cross-stream waits of
 // about 10 us each, a bookkeeping launch of up to 25 us before it and a tail
@@ -169,7 +170,7 @@ hlbm_status prologue(Ctx& c) {
 //
 // Balance mode 2: the controller's sums of a lattice pass feed only the next
 // one.  flags & BAL_LATER leaves them to the next step of the same call,
-// which takes them along in its motion and detection launches (flags &
+// which takes them along in its treatment and motion launches (flags &
 // BAL_PENDING); otherwise they are two launches at the end of the step.
 constexpr int BAL_PENDING = 1, BAL_LATER = 2;
 hipError_t enqueue_step(Ctx& c, int p, int t, hipEvent_t* ev, int flags) {
@@ -184,14 +185,14 @@ hipError_t enqueue_step(Ctx& c, int p, int t, hipEvent_t* ev, int flags) {
     const bool pend = bal && s == 0 && (flags & BAL_PENDING);
     // (the timing slots of the clearing and of the carry-over stay empty)
     if ((e = mark())) return e;
-    if ((e = launch_treat(c, c.tab[t]))) return e;
+    if ((e = launch_treat(c, c.tab[t], c.tab[1 - t], pend))) return e;
     if ((e = mark())) return e;
     if ((e = launch_particles(c, s == 0 ? 1 : 2, s + 1 == c.n_sub, &c.tab[t], &c.tab[1 - t],
                               pend)))
       return e;
     if ((e = mark())) return e;
     if ((e = mark())) return e;
-    if ((e = launch_detect(c, c.tab[1 - t], &c.tab[t], pend))) return e;
+    if ((e = launch_detect(c, c.tab[1 - t]))) return e;
     if ((e = mark())) return e;
     t = 1 - t;
   }
@@ -453,7 +454,7 @@ hlbm_status hlbm_create(const hlbm_params* params, void* stream, hlbm_ctx** out)
   c.tile_bytes = tbytes;
   bool okm = hipMalloc(&c.owner, sizeof(int) * ncell) == hipSuccess &&
              hipMalloc(&c.tile_block, tbytes) == hipSuccess &&
-             hipMalloc(&c.counters, COUNTER_BYTES) == hipSuccess &&
+             hipMalloc(&c.counters, sizeof(Counters)) == hipSuccess &&
              hipMalloc(&c.scratch, sizeof(double) * ncell) == hipSuccess &&
              (P.balance != 2 ||
               hipMalloc(&c.bal_part, sizeof(double) * 4 * ((size_t)nlt + BAL_PARTS)) == hipSuccess);
@@ -477,7 +478,7 @@ hlbm_status hlbm_create(const hlbm_params* params, void* stream, hlbm_ctx** out)
     c.tl.llist = t; t += nlt * P.tile_capacity;
     c.tl.lent = t;
   }
-  hipMemsetAsync(c.counters, 0, COUNTER_BYTES, c.stream);
+  hipMemsetAsync(c.counters, 0, sizeof(Counters), c.stream);
   hipMemsetAsync(c.owner, 0xff, sizeof(int) * ncell, c.stream);
   for (int k = 0; k < 2; ++k) {
     hipMemsetAsync(c.tab[k].list, 0, sizeof(int) * ((size_t)cap + 2), c.stream);

@@ -56,7 +56,9 @@ struct Counters {
   unsigned long long det_cells;
   unsigned long long total_cells;  // sum over the detections before the latest
   unsigned long long steps;
-  unsigned long long samples;      // midpoint samples of the latest treatment
+  // midpoint samples of the latest treatment (reset by it, summed by the
+  // carry-over that follows it)
+  unsigned long long samples;
   int tile_overflow;
   int pair_overflow;
   int unstable;
@@ -66,15 +68,6 @@ struct Counters {
   // lattice mass M, and the acceleration a = fluid_accel + b in use
   double bal_b[3], bal_P[3], bal_M, bal_a[3];
 };
-
-// The counter block is followed by a running sum of the treatment's midpoint
-// samples: the carry-over adds the records' (one atomic per wavefront),
-// detection moves the sum into Counters::samples.  It is zero between steps
-// (and not part of a saved state).
-__host__ __device__ inline unsigned long long* running_samples(Counters* c) {
-  return (unsigned long long*)(c + 1);
-}
-constexpr size_t COUNTER_BYTES = sizeof(Counters) + sizeof(unsigned long long);
 
 __device__ inline void clear_slot(const PairTable& t, long long i) {
   t.keys[i] = EMPTY_KEY;
@@ -321,15 +314,12 @@ hipError_t launch_count(Ctx& c, PairTable table);
 // lattice blocks (the last binning before a lattice pass).
 // keep_from / keep_to (optional, both or neither): the contact carry-over
 // from one pair table to the next, and the clearing of the slots it read,
-// run in the same launch; so do (balance) the first stage of the balance
+// run in the same launch; so does (balance) the second stage of the balance
 // sums of the last lattice pass
 hipError_t launch_particles(Ctx& c, int move, bool bin_blocks,
                             const PairTable* keep_from = nullptr,
                             const PairTable* keep_to = nullptr, bool balance = false);
-// from (optional): the table whose list the carry-over is done with; balance:
-// the second stage of the balance sums
-hipError_t launch_detect(Ctx& c, PairTable to, const PairTable* from = nullptr,
-                         bool balance = false);
+hipError_t launch_detect(Ctx& c, PairTable to);
 // stream-collide src -> dst with the coupling of the current owner map
 hipError_t launch_lattice(Ctx& c, const void* src, void* dst);
 // momentum exchange over the collided populations fstar (force of the next step)
@@ -339,7 +329,10 @@ hipError_t launch_mea(Ctx& c, const void* fstar);
 // block sums
 hipError_t launch_pop_moments(Ctx& c, const void* f);
 hipError_t launch_balance(Ctx& c, int init);
-hipError_t launch_treat(Ctx& c, PairTable t);
+// treatment of table t; next: the table that the carry-over and detection will
+// fill (its slots are clear already; its list count is reset here); balance:
+// the first stage of the balance sums in the same launch
+hipError_t launch_treat(Ctx& c, PairTable t, PairTable next, bool balance);
 hipError_t launch_fill_equilibrium(Ctx& c, void* f, double rho,
                                    const double u[3]);
 hipError_t launch_store_direction(Ctx& c, void* f, int i, const double* src);

@@ -18,6 +18,7 @@
 //            result does not depend on the order the pairs ran in.
 #include <float.h>
 
+#include "balance.h"
 #include "context.h"
 
 namespace hlbm {
@@ -67,7 +68,6 @@ __global__ __launch_bounds__(CLEAR_THREADS) void k_clear_state(PairTable table, 
   __syncthreads();
   if (tid == 0) {
     if (what & CLEAR_TABLE) *table.nlist = 0;
-    *running_samples(ctr) = 0;
   }
 }
 
@@ -424,11 +424,25 @@ constexpr int TREAT_BLOCKS = 1024;
 template <bool POLY, bool ELL = false>
 __global__ __launch_bounds__(TREAT_WAVES* WAVE) void k_treat(PairTable t, Particles P, Geom g,
                                                              Phys ph, FastDiv fnc, Tiles tl,
-                                                             Counters* ctr) {
+                                                             Counters* ctr, int* next_nlist,
+                                                             unsigned blocks,
+                                                             const double* __restrict__ bal_part,
+                                                             unsigned bal_blocks,
+                                                             double* __restrict__ bal_out) {
+  if (blockIdx.x >= blocks) {
+    // workgroups past the treatment's: the first stage of the balance sums
+    balance_stage1(bal_part, bal_blocks,
+                   (blockIdx.x - blocks) * TREAT_WAVES + threadIdx.x / WAVE, bal_out);
+    return;
+  }
   __shared__ TreatShared sh;
   const int n = *t.nlist;
   int round = 0;
-  for (int i = (int)blockIdx.x; i < n; i += (int)gridDim.x)
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *next_nlist = 0;
+    ctr->samples = 0;
+  }
+  for (int i = (int)blockIdx.x; i < n; i += (int)blocks)
     treat_slot<POLY, ELL>(t, P, g, ph, fnc, tl, ctr,
                           __builtin_amdgcn_readfirstlane(t.list[i]), sh, round);
 }
@@ -458,17 +472,15 @@ hipError_t launch_count(Ctx& c, PairTable table) {
   return hipGetLastError();
 }
 
-hipError_t launch_treat(Ctx& c, PairTable t) {
-  const dim3 nb((unsigned)(t.cap < TREAT_BLOCKS ? t.cap : TREAT_BLOCKS));
-  const dim3 nt(TREAT_WAVES * WAVE);
+hipError_t launch_treat(Ctx& c, PairTable t, PairTable next, bool balance) {
+  const unsigned blocks = (unsigned)(t.cap < TREAT_BLOCKS ? t.cap : TREAT_BLOCKS);
+  const dim3 nb(blocks + (balance ? BAL_PARTS / TREAT_WAVES : 0)), nt(TREAT_WAVES * WAVE);
   const FastDiv fnc = make_fastdiv((unsigned)c.ph.n_c);
-  if (c.has_ellipsoid)
-    hipLaunchKernelGGL((k_treat<true, true>), nb, nt, 0, c.stream, t, c.part, c.g, c.ph, fnc, c.tl,
-                       c.counters);
-  else if (c.has_poly)
-    hipLaunchKernelGGL(k_treat<true>, nb, nt, 0, c.stream, t, c.part, c.g, c.ph, fnc, c.tl, c.counters);
-  else
-    hipLaunchKernelGGL(k_treat<false>, nb, nt, 0, c.stream, t, c.part, c.g, c.ph, fnc, c.tl, c.counters);
+  const unsigned nlt = (unsigned)c.g.ltx * (unsigned)c.g.lty * (unsigned)c.g.ltz;
+  auto k = c.has_ellipsoid ? k_treat<true, true> : (c.has_poly ? k_treat<true> : k_treat<false>);
+  hipLaunchKernelGGL(k, nb, nt, 0, c.stream, t, c.part, c.g, c.ph, fnc, c.tl, c.counters,
+                     next.nlist, blocks, c.bal_part, nlt,
+                     c.bal_part ? c.bal_part + 4 * (size_t)nlt : nullptr);
   return hipGetLastError();
 }
 

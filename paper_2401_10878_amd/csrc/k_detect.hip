@@ -12,7 +12,6 @@
 // (count of flagged nodes, bounding box of their images in the frame of the
 // lower-id particle) and then committed with one set of atomics per pair
 // and tile into the open-addressing pair table.
-#include "balance.h"
 #include "context.h"
 
 namespace hlbm {
@@ -61,31 +60,14 @@ __device__ void commit_pair(PairTable t, Counters* ctr, int a, int b,
 template <bool POLY, bool ELL = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? (ELL ? 4 : 5) : 8, 8))) void k_detect(Particles P, Geom g, Phys ph,
                                                 Tiles tl, int* __restrict__ owner,
-                                                PairTable tab, Counters* ctr,
-                                                int* from_nlist,
-                                                const double* __restrict__ bal_parts) {
+                                                PairTable tab, Counters* ctr) {
   const int lane = threadIdx.x % WAVE;
   // tile id, uniform over the wavefront (fewer than 2^31 tiles: the cell
   // count is bounded on the host)
   const unsigned ntiles = (unsigned)g.dtx * (unsigned)g.dty * (unsigned)g.dtz;
   const unsigned tile =
       blockIdx.x * 4u + (unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x) / WAVE;
-  if (tile >= ntiles) {                           // whole wavefront exits
-    // the first wavefront past the tiles (there is always one; the check of
-    // the tile's range is the only one the others pay): the list of the
-    // previous table, carried over and cleared by the motion kernel, the
-    // samples that it summed, and the balance controller
-    if (tile == ntiles) {
-      if (from_nlist && lane == 0) {
-        *from_nlist = 0;
-        unsigned long long* run = running_samples(ctr);
-        ctr->samples = *run;
-        *run = 0;
-      }
-      if (bal_parts) balance_stage2(bal_parts, ctr, ph, 0);
-    }
-    return;
-  }
+  if (tile >= ntiles) return;                     // whole wavefront exits
   const unsigned tyz = fdiv(tile, g.fdtx);
   const unsigned utz = fdiv(tyz, g.fdty);
   const int tx = (int)(tile - tyz * (unsigned)g.dtx);
@@ -265,21 +247,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? (ELL
 
 }  // namespace
 
-hipError_t launch_detect(Ctx& c, PairTable to, const PairTable* from, bool balance) {
+hipError_t launch_detect(Ctx& c, PairTable to) {
   const long long ntiles = (long long)c.g.dtx * c.g.dty * c.g.dtz;
-  const size_t nlt = (size_t)c.g.ltx * c.g.lty * c.g.ltz;
-  const dim3 nb((unsigned)(ntiles / 4 + 1)), nt(256);
-  int* nlist = from ? from->nlist : nullptr;
-  const double* parts = balance ? c.bal_part + 4 * nlt : nullptr;
+  const dim3 nb((unsigned)((ntiles + 3) / 4)), nt(256);
   if (c.has_ellipsoid)
     hipLaunchKernelGGL((k_detect<true, true>), nb, nt, 0, c.stream, c.part, c.g, c.ph, c.tl,
-                       c.owner, to, c.counters, nlist, parts);
+                       c.owner, to, c.counters);
   else if (c.has_poly)
     hipLaunchKernelGGL(k_detect<true>, nb, nt, 0, c.stream, c.part, c.g, c.ph, c.tl, c.owner, to,
-                       c.counters, nlist, parts);
+                       c.counters);
   else
     hipLaunchKernelGGL(k_detect<false>, nb, nt, 0, c.stream, c.part, c.g, c.ph, c.tl, c.owner, to,
-                       c.counters, nlist, parts);
+                       c.counters);
   return hipGetLastError();
 }
 

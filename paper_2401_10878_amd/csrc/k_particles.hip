@@ -84,21 +84,19 @@ __global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
                                                   int move, int bin_blocks, Tiles tl,
                                                   Counters* ctr, PairTable keep_from,
                                                   PairTable keep_to, int keep_blocks,
-                                                  const double* __restrict__ bal_part,
-                                                  unsigned bal_blocks,
-                                                  double* __restrict__ bal_out) {
+                                                  const double* __restrict__ bal_parts) {
   const int ip = blockIdx.x;
   if (ip >= P.n) {
     // blocks past the particles (independent of this kernel's particle work)
     const int k = ip - P.n;
     if (k >= keep_blocks) {
-      balance_stage1(bal_part, bal_blocks, (unsigned)(k - keep_blocks), bal_out);
+      balance_stage2(bal_parts, ctr, ph, 0);
       return;
     }
     // the contact carry-over of the pair table, one listed slot per thread
     // and round (the detection that follows inserts into the same next
     // table); the slot is then cleared, so that this table is empty when it
-    // is the next one again (its list count is reset by the detection)
+    // is the next one again (its list count is reset by the treatment before)
     const int n = *keep_from.nlist;
     int cells = 0;
     long long samples = 0;
@@ -115,7 +113,7 @@ __global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
     const double sum = wave_sum((double)samples);
     const int csum = wave_sum_i(cells);
     if (threadIdx.x == 0) {
-      atomicAdd(running_samples(ctr), (unsigned long long)sum);
+      atomicAdd(&ctr->samples, (unsigned long long)sum);
       atomicAdd(&ctr->total_cells, (unsigned long long)csum);
     }
     return;
@@ -421,13 +419,12 @@ hipError_t launch_particles(Ctx& c, int move, bool bin_blocks, const PairTable* 
   const PairTable to = keep_to ? *keep_to : none;
   unsigned kb = (unsigned)((from.cap + WAVE - 1) / WAVE);
   if (kb > KEEP_BLOCKS) kb = KEEP_BLOCKS;
-  const unsigned bb = balance ? BAL_PARTS : 0;
+  const unsigned bb = balance ? 1 : 0;
   if (c.np + kb + bb == 0) return hipSuccess;
   const unsigned nlt = (unsigned)c.g.ltx * (unsigned)c.g.lty * (unsigned)c.g.ltz;
   hipLaunchKernelGGL(k_particles, dim3(c.np + kb + bb), dim3(64), 0, c.stream, c.part, c.g,
                      c.ph, c.Fh, c.Th, c.Fc, c.Tc, move, bin_blocks ? 1 : 0, c.tl, c.counters,
-                     from, to, (int)kb, c.bal_part, nlt,
-                     c.bal_part ? c.bal_part + 4 * (size_t)nlt : nullptr);
+                     from, to, (int)kb, c.bal_part ? c.bal_part + 4 * (size_t)nlt : nullptr);
   return hipGetLastError();
 }
 
