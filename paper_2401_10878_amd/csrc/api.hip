@@ -6,7 +6,9 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "context.h"
@@ -75,10 +77,7 @@ void poly_inverse_inertia(const Ctx::PolyHost& P, double s, double dens, double*
   Ii[8] = (I[0] * I[4] - I[1] * I[3]) / det;
 }
 
-hlbm_status check_flags(Ctx& c) {
-  Counters h;
-  HIPCHECK(hipMemcpyAsync(&h, c.counters, sizeof h, hipMemcpyDeviceToHost, c.stream));
-  HIPCHECK(hipStreamSynchronize(c.stream));
+hlbm_status flags_of(Ctx& c, const Counters& h) {
   if (h.tile_overflow)
     return fail(c, HLBM_E_CAPACITY,
                 "tile candidate list overflow: more than tile_capacity=%d particles reach one 4x4x4 tile",
@@ -91,6 +90,71 @@ hlbm_status check_flags(Ctx& c) {
   if (h.unstable)
     return fail(c, HLBM_E_UNSTABLE, "non-finite or non-positive density on the lattice");
   return HLBM_OK;
+}
+
+// Wait for the stream, with n doubles of the particle block in c.host_part
+// and the error flags raised: one kernel writes both to pinned host memory,
+// so that a read-out is one launch and one wait (a small device-to-host copy
+// is 15 to 40 us of host time each; the state came in four and the flags in a
+// fifth with a wait of its own: 32^3 nodes, two particles, a step and a
+// read-out 185 us).
+hlbm_status read_back(Ctx& c, const double* src, long long n) {
+  if (!c.host_ctr) {                               // no particles yet
+    Counters h;
+    HIPCHECK(hipMemcpyAsync(&h, c.counters, sizeof h, hipMemcpyDeviceToHost, c.stream));
+    HIPCHECK(hipStreamSynchronize(c.stream));
+    return flags_of(c, h);
+  }
+  HIPCHECK(launch_export(c, src, n, c.host_part, c.host_ctr));
+  HIPCHECK(hipStreamSynchronize(c.stream));
+  return flags_of(c, *c.host_ctr);
+}
+hlbm_status check_flags(Ctx& c) { return read_back(c, nullptr, 0); }
+
+// Read `total` units (nodes or values) of `unit` bytes through pinned chunks:
+// launch(begin, count, chunk) has the device fill a chunk, copy(begin, count,
+// chunk) moves it to the caller's arrays.  Up to READ_WORKERS threads, each
+// with a chunk of its own, take the chunks in turn: the copies into (often
+// untouched) caller memory are the longest part and run side by side.
+template <typename Launch, typename Copy>
+hlbm_status read_chunks(Ctx& c, long long total, size_t unit, Launch launch, Copy copy) {
+  const long long per = (long long)(READ_CHUNK / unit) / 256 * 256;
+  const long long nch = (total + per - 1) / per;
+  const int nw = (int)std::min<long long>(READ_WORKERS, nch);
+  for (int w = 0; w < nw; ++w) {
+    if (c.chunk[w]) continue;
+    if (!c.chunk_ev[w])
+      HIPCHECK(hipEventCreateWithFlags(&c.chunk_ev[w], hipEventDisableTiming));
+    if (hipHostMalloc(&c.chunk[w], READ_CHUNK) != hipSuccess) {
+      c.chunk[w] = nullptr;
+      return fail(c, HLBM_E_NOMEM, "read-out chunk of %zu bytes", READ_CHUNK);
+    }
+  }
+  std::atomic<int> err{(int)hipSuccess};
+  auto work = [&](int w) {
+    // (a new thread starts on device 0; the caller's own is left as it is)
+    hipError_t e = w > 0 ? hipSetDevice(c.device) : hipSuccess;
+    for (long long k = w; k < nch && e == hipSuccess; k += nw) {
+      const long long begin = k * per, count = std::min(per, total - begin);
+      if ((e = launch(begin, count, c.chunk[w])) == hipSuccess &&
+          (e = hipEventRecord(c.chunk_ev[w], c.stream)) == hipSuccess &&
+          (e = hipEventSynchronize(c.chunk_ev[w])) == hipSuccess)
+        copy(begin, count, c.chunk[w]);
+    }
+    if (e != hipSuccess) err = (int)e;
+  };
+  std::thread th[READ_WORKERS];
+  int started = 1;
+  try {
+    for (; started < nw; ++started) th[started] = std::thread(work, started);
+  } catch (...) {                                  // no more threads: run the rest here
+  }
+  work(0);
+  for (int w = started; w < nw; ++w) work(w);      // (hipSetDevice: this context's)
+  for (int w = 1; w < started; ++w) th[w].join();
+  if (err != (int)hipSuccess)
+    return fail(c, HLBM_E_DEVICE, "read-out: %s", hipGetErrorString((hipError_t)err.load()));
+  return check_flags(c);
 }
 
 hlbm_status ensure_populations(Ctx& c) {
@@ -297,6 +361,9 @@ void free_adjoint(Ctx& c) {
 
 void free_particles(Ctx& c) {
   free_adjoint(c);
+  if (c.host_ctr) hipHostFree(c.host_ctr);
+  c.host_ctr = nullptr;
+  c.host_part = nullptr;
   if (c.part_block) hipFree(c.part_block);
   c.part_block = nullptr;
   if (c.part_sums) hipFree(c.part_sums);
@@ -446,6 +513,7 @@ hlbm_status hlbm_create(const hlbm_params* params, void* stream, hlbm_ctx** out)
       return HLBM_E_DEVICE;
     }
   }
+  (void)hipGetDevice(&c.device);
   const long long ndt = (long long)c.g.dtx * c.g.dty * c.g.dtz;
   const long long nlt = (long long)c.g.ltx * c.g.lty * c.g.ltz;
   const int cap = next_pow2(2LL * P.max_pairs);
@@ -787,6 +855,12 @@ hlbm_status hlbm_init_particles(hlbm_ctx* h, int n, const int* shape, const doub
   const size_t bytes = nd * sizeof(double) + nn * sizeof(int);
   c.part_bytes = bytes;
   HIPCHECK(hipMalloc(&c.part_block, bytes));
+  {
+    void* hp = nullptr;
+    HIPCHECK(hipHostMalloc(&hp, sizeof(Counters) + sizeof(double) * PART_OUT * nn));
+    c.host_ctr = (Counters*)hp;
+    c.host_part = (double*)(c.host_ctr + 1);
+  }
   HIPCHECK(hipMemsetAsync(c.part_block, 0, bytes, c.stream));
   double* d = (double*)c.part_block;
   auto take = [&](size_t k) { double* p = d; d += k * nn; return p; };
@@ -1014,39 +1088,38 @@ hlbm_status hlbm_timing_end(hlbm_ctx* h, double* kernel_ms, int* nsteps) {
 
 hlbm_status hlbm_sync(hlbm_ctx* h) {
   if (!h) return HLBM_E_ARG;
-  Ctx& c = h->c;
-  HIPCHECK(hipStreamSynchronize(c.stream));
-  return check_flags(c);
+  return check_flags(h->c);
 }
 
 hlbm_status hlbm_read_forces(hlbm_ctx* h, double* Fh, double* Th, double* Fc, double* Tc) {
   if (!h) return HLBM_E_ARG;
   Ctx& c = h->c;
   if (!c.particles_ready) return fail(c, HLBM_E_STATE, "no particles");
-  const size_t b = sizeof(double) * 3 * c.np;
-  if (c.np > 0) {
-    if (Fh) HIPCHECK(hipMemcpyAsync(Fh, c.Fh, b, hipMemcpyDeviceToHost, c.stream));
-    if (Th) HIPCHECK(hipMemcpyAsync(Th, c.Th, b, hipMemcpyDeviceToHost, c.stream));
-    if (Fc) HIPCHECK(hipMemcpyAsync(Fc, c.Fc, b, hipMemcpyDeviceToHost, c.stream));
-    if (Tc) HIPCHECK(hipMemcpyAsync(Tc, c.Tc, b, hipMemcpyDeviceToHost, c.stream));
-  }
-  HIPCHECK(hipStreamSynchronize(c.stream));
-  return check_flags(c);
+  // F_h, T_h, F_c, T_c lie one after another in the particle block
+  const size_t np = c.np, nn = c.np > 0 ? c.np : 1;
+  const hlbm_status st = read_back(c, c.Fh, c.np > 0 ? (long long)(FORCE_OUT * nn) : 0);
+  double* out[4] = {Fh, Th, Fc, Tc};
+  for (int k = 0; k < 4; ++k)
+    if (out[k] && np && st != HLBM_E_DEVICE)
+      memcpy(out[k], c.host_part + 3 * nn * k, sizeof(double) * 3 * np);
+  return st;
 }
 
 hlbm_status hlbm_read_particles(hlbm_ctx* h, double* X, double* q, double* U, double* W) {
   if (!h) return HLBM_E_ARG;
   Ctx& c = h->c;
   if (!c.particles_ready) return fail(c, HLBM_E_STATE, "no particles");
-  const size_t b = sizeof(double) * c.np;
-  if (c.np > 0) {
-    if (X) HIPCHECK(hipMemcpyAsync(X, c.part.X, 3 * b, hipMemcpyDeviceToHost, c.stream));
-    if (q) HIPCHECK(hipMemcpyAsync(q, c.part.q, 4 * b, hipMemcpyDeviceToHost, c.stream));
-    if (U) HIPCHECK(hipMemcpyAsync(U, c.part.U, 3 * b, hipMemcpyDeviceToHost, c.stream));
-    if (W) HIPCHECK(hipMemcpyAsync(W, c.part.W, 3 * b, hipMemcpyDeviceToHost, c.stream));
+  // X, q, U, omega lie one after another in the particle block
+  const size_t np = c.np, nn = c.np > 0 ? c.np : 1;
+  const hlbm_status st = read_back(c, c.part.X, c.np > 0 ? (long long)(PART_OUT * nn) : 0);
+  if (np && st != HLBM_E_DEVICE) {
+    const double* o = c.host_part;
+    if (X) memcpy(X, o, sizeof(double) * 3 * np);
+    if (q) memcpy(q, o + 3 * nn, sizeof(double) * 4 * np);
+    if (U) memcpy(U, o + 7 * nn, sizeof(double) * 3 * np);
+    if (W) memcpy(W, o + 10 * nn, sizeof(double) * 3 * np);
   }
-  HIPCHECK(hipStreamSynchronize(c.stream));
-  return check_flags(c);
+  return st;
 }
 
 hlbm_status hlbm_read_contacts(hlbm_ctx* h, int capacity, hlbm_contact* out, int* n_out) {
@@ -1100,49 +1173,38 @@ hlbm_status hlbm_read_fields(hlbm_ctx* h, double* rho, double* u, int* owner) {
   if (!h) return HLBM_E_ARG;
   Ctx& c = h->c;
   if (!c.fluid_ready) return fail(c, HLBM_E_STATE, "not initialised");
-  const size_t n = (size_t)c.g.ncell;
-  if (rho) {
-    HIPCHECK(launch_moment(c, c.fbuf[c.cur], -1, c.scratch));
-    HIPCHECK(hipMemcpyAsync(rho, c.scratch, sizeof(double) * n, hipMemcpyDeviceToHost, c.stream));
-    HIPCHECK(hipStreamSynchronize(c.stream));
-  }
-  if (u) {
-    std::vector<double> tmp(n);
-    for (int k = 0; k < 3; ++k) {
-      HIPCHECK(launch_moment(c, c.fbuf[c.cur], k, c.scratch));
-      HIPCHECK(hipMemcpyAsync(tmp.data(), c.scratch, sizeof(double) * n,
-                              hipMemcpyDeviceToHost, c.stream));
-      HIPCHECK(hipStreamSynchronize(c.stream));
-      for (size_t i = 0; i < n; ++i) u[3 * i + k] = tmp[i];
-    }
-  }
-  if (owner)
-    HIPCHECK(hipMemcpyAsync(owner, c.owner, sizeof(int) * n, hipMemcpyDeviceToHost, c.stream));
-  HIPCHECK(hipStreamSynchronize(c.stream));
-  return check_flags(c);
+  // a chunk: velocities, densities, owners
+  return read_chunks(
+      c, c.g.ncell, 36,
+      [&](long long begin, long long count, void* chunk) {
+        double* o = (double*)chunk;
+        return launch_moments(c, c.fbuf[c.cur], begin, count, rho ? o + 3 * count : nullptr,
+                              u ? o : nullptr, owner ? (int*)(o + 4 * count) : nullptr);
+      },
+      [&](long long begin, long long count, const void* chunk) {
+        const double* o = (const double*)chunk;
+        if (u) memcpy(u + 3 * begin, o, sizeof(double) * 3 * count);
+        if (rho) memcpy(rho + begin, o + 3 * count, sizeof(double) * count);
+        if (owner) memcpy(owner + begin, o + 4 * count, sizeof(int) * count);
+      });
 }
 
 hlbm_status hlbm_read_coupling(hlbm_ctx* h, double* B, double* up) {
   if (!h) return HLBM_E_ARG;
   Ctx& c = h->c;
   if (!c.fluid_ready) return fail(c, HLBM_E_STATE, "not initialised");
-  const size_t n = (size_t)c.g.ncell;
-  std::vector<double> tmp(up ? n : 0);
-  if (B) {
-    HIPCHECK(launch_coupling_field(c, -1, c.scratch, 1));
-    HIPCHECK(hipMemcpyAsync(B, c.scratch, sizeof(double) * n, hipMemcpyDeviceToHost, c.stream));
-  }
-  if (up) {
-    for (int k = 0; k < 3; ++k) {
-      HIPCHECK(launch_coupling_field(c, k, c.scratch, 1));
-      HIPCHECK(hipMemcpyAsync(tmp.data(), c.scratch, sizeof(double) * n,
-                              hipMemcpyDeviceToHost, c.stream));
-      HIPCHECK(hipStreamSynchronize(c.stream));
-      for (size_t i = 0; i < n; ++i) up[3 * i + k] = tmp[i];
-    }
-  }
-  HIPCHECK(hipStreamSynchronize(c.stream));
-  return check_flags(c);
+  return read_chunks(
+      c, c.g.ncell, 32,
+      [&](long long begin, long long count, void* chunk) {
+        double* o = (double*)chunk;
+        return launch_coupling_field(c, begin, count, B ? o + 3 * count : nullptr,
+                                     up ? o : nullptr);
+      },
+      [&](long long begin, long long count, const void* chunk) {
+        const double* o = (const double*)chunk;
+        if (up) memcpy(up + 3 * begin, o, sizeof(double) * 3 * count);
+        if (B) memcpy(B + begin, o + 3 * count, sizeof(double) * count);
+      });
 }
 
 // The same read-out staged through the fixed device array: no allocation
@@ -1159,14 +1221,10 @@ hlbm_status hlbm_read_coupling_noalloc(hlbm_ctx* h, double* B, double* up) {
   if (!c.fixed_scratch) return fail(c, HLBM_E_STATE, "no staging array address");
   double* sB = c.fixed_scratch;
   double* sU = c.fixed_scratch + n;
-  if (B) {
-    HIPCHECK(launch_coupling_field(c, -1, sB, 1));
-    HIPCHECK(hipMemcpyAsync(B, sB, sizeof(double) * n, hipMemcpyDeviceToHost, c.stream));
-  }
-  if (up) {
-    for (int k = 0; k < 3; ++k) HIPCHECK(launch_coupling_field(c, k, sU + k, 3));
+  HIPCHECK(launch_coupling_field(c, 0, n, B ? sB : nullptr, up ? sU : nullptr));
+  if (B) HIPCHECK(hipMemcpyAsync(B, sB, sizeof(double) * n, hipMemcpyDeviceToHost, c.stream));
+  if (up)
     HIPCHECK(hipMemcpyAsync(up, sU, sizeof(double) * 3 * n, hipMemcpyDeviceToHost, c.stream));
-  }
   HIPCHECK(hipStreamSynchronize(c.stream));
   return check_flags(c);
 }
@@ -1175,14 +1233,14 @@ hlbm_status hlbm_read_populations(hlbm_ctx* h, double* f) {
   if (!h || !f) return HLBM_E_ARG;
   Ctx& c = h->c;
   if (!c.fluid_ready) return fail(c, HLBM_E_STATE, "not initialised");
-  const size_t n = (size_t)c.g.ncell;
-  for (int i = 0; i < Q; ++i) {
-    HIPCHECK(launch_load_direction(c, c.fbuf[c.cur], i, c.scratch));
-    HIPCHECK(hipMemcpyAsync(f + (size_t)i * n, c.scratch, sizeof(double) * n,
-                            hipMemcpyDeviceToHost, c.stream));
-    HIPCHECK(hipStreamSynchronize(c.stream));
-  }
-  return check_flags(c);
+  return read_chunks(
+      c, (long long)Q * c.g.ncell, sizeof(double),
+      [&](long long begin, long long count, void* chunk) {
+        return launch_load_populations(c, c.fbuf[c.cur], begin, count, (double*)chunk);
+      },
+      [&](long long begin, long long count, const void* chunk) {
+        memcpy(f + begin, chunk, sizeof(double) * count);
+      });
 }
 
 hlbm_status hlbm_counters(hlbm_ctx* h, long long* pairs, long long* cells,
@@ -1525,6 +1583,10 @@ void hlbm_destroy(hlbm_ctx* h) {
   if (c.bal_part) hipFree(c.bal_part);
   if (c.poly_dev) hipFree(c.poly_dev);
   if (c.scratch) hipFree(c.scratch);
+  for (int w = 0; w < READ_WORKERS; ++w) {
+    if (c.chunk[w]) hipHostFree(c.chunk[w]);
+    if (c.chunk_ev[w]) hipEventDestroy(c.chunk_ev[w]);
+  }
   for (int k = 0; k < 2; ++k) {
     if (c.tab[k].keys) hipFree(c.tab[k].keys);
     if (c.tab[k].rec) hipFree(c.tab[k].rec);

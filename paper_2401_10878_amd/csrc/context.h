@@ -69,6 +69,20 @@ struct Counters {
   double bal_b[3], bal_P[3], bal_M, bal_a[3];
 };
 
+// Three values per thread of a 256-thread workgroup, stored as consecutive
+// triples from out[3 * first] on, limited to n triples: through LDS, so that
+// the lanes write consecutive words (the target is host memory, where every
+// partial line is a transaction of its own).
+__device__ inline void store_rows3(double* sh, const double* v, long long first, long long n,
+                                   double* out) {
+  for (int k = 0; k < 3; ++k) sh[3 * threadIdx.x + k] = v[k];
+  __syncthreads();
+  for (int k = 0; k < 3; ++k) {
+    const long long i = 3 * first + k * 256 + (int)threadIdx.x;
+    if (i < 3 * n) out[i] = sh[k * 256 + threadIdx.x];
+  }
+}
+
 __device__ inline void clear_slot(const PairTable& t, long long i) {
   t.keys[i] = EMPTY_KEY;
   PairRec r = {};
@@ -192,6 +206,14 @@ struct Phys {
   double dt_sub;          // length of a contact sub-step (1 / n_sub)
 };
 
+// Field read-outs go through pinned chunks of this size, one per worker
+// thread, in turn: the device writes one worker's chunk while the others copy
+// theirs into the caller's array.
+constexpr int READ_WORKERS = 8;
+constexpr size_t READ_CHUNK = (size_t)65536 * 36;   // 65536 nodes of density,
+                                                    // velocity and owner
+constexpr int PART_OUT = 13, FORCE_OUT = 12;        // doubles per particle
+
 constexpr int NKERN = 7;   // clear, treat, particles, keep, detect, lattice, mea
 
 // Device copy of the whole step state (populations f*, particle block,
@@ -269,6 +291,14 @@ struct Ctx {
   Counters* counters;     // device
   double* scratch;        // [ncell] FP64 staging for host conversions
   double* fixed_scratch;  // device address of the fixed staging array
+  int device = 0;
+  // pinned host memory of the read-outs: the counters and a particle
+  // read-out (allocated with the particles), and the chunks of the field
+  // read-outs (allocated by the first that needs them), one per worker
+  Counters* host_ctr = nullptr;
+  double* host_part = nullptr;
+  void* chunk[READ_WORKERS] = {};
+  hipEvent_t chunk_ev[READ_WORKERS] = {};
   double* bal_part = nullptr;  // per-block (mass, momentum) sums, balance mode 2
   // state
   bool particles_ready, fluid_ready;
@@ -336,11 +366,18 @@ hipError_t launch_treat(Ctx& c, PairTable t, PairTable next, bool balance);
 hipError_t launch_fill_equilibrium(Ctx& c, void* f, double rho,
                                    const double u[3]);
 hipError_t launch_store_direction(Ctx& c, void* f, int i, const double* src);
-hipError_t launch_load_direction(Ctx& c, const void* f, int i, double* dst);
-// comp = -1: density, 0..2: velocity component of f* (FP64, into out[ncell])
-hipError_t launch_moment(Ctx& c, const void* f, int comp, double* out);
-// coupling field: comp = -1 weight B, 0..2 particle velocity component
-hipError_t launch_coupling_field(Ctx& c, int comp, double* out, int stride);
+// Read-outs of the nodes (populations: values) begin .. begin + count into
+// host or device memory; null pointers skip.
+// populations f* as FP64, all directions one after another
+hipError_t launch_load_populations(Ctx& c, const void* f, long long begin, long long count,
+                                   double* dst);
+// density, velocity (three per node) and owner
+hipError_t launch_moments(Ctx& c, const void* f, long long begin, long long count, double* rho,
+                          double* u, int* owner);
+// coupling weight and particle velocity (three per node)
+hipError_t launch_coupling_field(Ctx& c, long long begin, long long count, double* B, double* up);
+// n doubles and the counters
+hipError_t launch_export(Ctx& c, const double* src, long long n, double* dst, Counters* dst_ctr);
 // nodes the fixed staging array of hlbm_read_coupling_noalloc holds
 constexpr long long NOALLOC_MAX_CELLS = 1LL << 21;
 hipError_t noalloc_scratch(double** out);

@@ -1,5 +1,6 @@
-// Read-out of the coupling field (Sec. 3.2) for tests and diagnostics, and
-// the fixed device staging array of the read-out that allocates nothing.
+// Read-out kernels: the coupling field (Sec. 3.2), the particle state and the
+// counters; and the fixed device staging array of the read-out that allocates
+// nothing.
 #include <mutex>
 
 #include "context.h"
@@ -19,39 +20,64 @@ constexpr int MAX_DEVICES = 64;
 std::mutex g_scratch_mu;
 double* g_scratch_ptr[MAX_DEVICES] = {};
 
-// Coupling field at the current particle state (Sec. 3.2), FP64: comp = -1
-// writes B(d_owner), 0..2 the component of u_p = U + w x r of the owner
-// (0 where no particle owns the node), at out[stride * node].
-__global__ void k_coupling_field(const int* __restrict__ owner, Particles P,
-                                 Geom g, Phys ph, int comp, double* __restrict__ out,
-                                 int stride) {
-  const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (id >= g.ncell) return;
-  const int o = owner_id(owner[id]);
-  double v = 0.0;
+// Coupling field at the current particle state (Sec. 3.2), FP64, of the nodes
+// begin .. begin + count: the weight B(d_owner) to B (may be null) and u_p =
+// U + w x r of the owner, three per node, to up (may be null); 0 where no
+// particle owns the node.
+__global__ __launch_bounds__(256) void k_coupling_field(const int* __restrict__ owner,
+                                                        Particles P, Geom g, Phys ph,
+                                                        long long begin, long long count,
+                                                        double* __restrict__ B,
+                                                        double* __restrict__ up) {
+  __shared__ double sh[3 * 256];
+  const long long at = (long long)blockIdx.x * 256 + threadIdx.x;
+  const long long id = begin + at;
+  const int o = at < count ? owner_id(owner[id]) : -1;
+  double b = 0.0, v[3] = {0.0, 0.0, 0.0};
   if (o >= 0) {
     const int x = (int)(id % g.nx), y = (int)((id / g.nx) % g.ny);
     const int z = (int)(id / ((long long)g.nx * g.ny));
     const double r[3] = {minimg((double)x - P.X[3 * o], (double)g.nx, true),
                          minimg((double)y - P.X[3 * o + 1], (double)g.ny, true),
                          minimg((double)z - P.X[3 * o + 2], (double)g.nz, g.periodic_z != 0)};
-    if (comp < 0) {
-      v = weight(sdf<true>(P.shape[o], P.size[o], P.R + 9 * o, r[0], r[1], r[2], P.poly), ph.eps);
-    } else {
-      const double* W = P.W + 3 * o;
-      const double wr[3] = {W[1] * r[2] - W[2] * r[1], W[2] * r[0] - W[0] * r[2],
-                            W[0] * r[1] - W[1] * r[0]};
-      v = P.U[3 * o + comp] + wr[comp == 0 ? 0 : (comp == 1 ? 1 : 2)];
-    }
+    if (B)
+      b = weight(sdf<true>(P.shape[o], P.size[o], P.R + 9 * o, r[0], r[1], r[2], P.poly), ph.eps);
+    const double* W = P.W + 3 * o;
+    v[0] = P.U[3 * o] + (W[1] * r[2] - W[2] * r[1]);
+    v[1] = P.U[3 * o + 1] + (W[2] * r[0] - W[0] * r[2]);
+    v[2] = P.U[3 * o + 2] + (W[0] * r[1] - W[1] * r[0]);
   }
-  out[stride * id] = v;
+  if (B && at < count) B[at] = b;
+  if (up) store_rows3(sh, v, (long long)blockIdx.x * 256, count, up);
 }
+
+// n doubles and the counters to host memory.
+__global__ __launch_bounds__(256) void k_export(const double* __restrict__ src, long long n,
+                                                const Counters* __restrict__ ctr,
+                                                double* __restrict__ dst,
+                                                Counters* __restrict__ dst_ctr) {
+  const long long stride = (long long)gridDim.x * 256;
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += stride)
+    dst[i] = src[i];
+  const unsigned words = sizeof(Counters) / sizeof(unsigned long long);
+  if (blockIdx.x == 0 && threadIdx.x < words)
+    ((unsigned long long*)dst_ctr)[threadIdx.x] =
+        ((const unsigned long long*)ctr)[threadIdx.x];
+}
+static_assert(sizeof(Counters) % sizeof(unsigned long long) == 0, "counters copied by words");
 
 }  // namespace
 
-hipError_t launch_coupling_field(Ctx& c, int comp, double* out, int stride) {
-  hipLaunchKernelGGL(k_coupling_field, dim3((unsigned)((c.g.ncell + 255) / 256)), dim3(256), 0,
-                     c.stream, c.owner, c.part, c.g, c.ph, comp, out, stride);
+hipError_t launch_coupling_field(Ctx& c, long long begin, long long count, double* B, double* up) {
+  hipLaunchKernelGGL(k_coupling_field, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,
+                     c.stream, c.owner, c.part, c.g, c.ph, begin, count, B, up);
+  return hipGetLastError();
+}
+
+hipError_t launch_export(Ctx& c, const double* src, long long n, double* dst, Counters* dst_ctr) {
+  const long long blocks = (n + 1023) / 1024;
+  hipLaunchKernelGGL(k_export, dim3((unsigned)(blocks < 1 ? 1 : (blocks > 256 ? 256 : blocks))),
+                     dim3(256), 0, c.stream, src, n, c.counters, dst, dst_ctr);
   return hipGetLastError();
 }
 

@@ -1071,26 +1071,48 @@ __global__ void k_store_dir(S* f, size_t n, int i, const double* srcv) {
                (typename Store<S>::C)(Store<S>::shifted ? srcv[id] - wgt(i) : srcv[id]));
 }
 
+// Values begin .. begin + count of the 19 directions, one after another.
 template <typename S>
-__global__ void k_load_dir(const S* f, size_t n, int i, double* out) {
-  const size_t id = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (id >= n) return;
-  out[id] = full_f<S>(Store<S>::ld(f, (int)(i * n + id)), i);
+__global__ void k_load_pops(const S* f, size_t n, long long begin, long long count, double* out) {
+  const long long at = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (at >= count) return;
+  const long long k = begin + at;
+  const int i = (int)(k / (long long)n);
+  const double w = i == 0 ? 1.0 / 3.0 : (i < 7 ? 1.0 / 18.0 : 1.0 / 36.0);
+  const double v = (double)Store<S>::ld(f, (int)k);
+  out[at] = Store<S>::shifted ? w + v : v;
 }
 
-// comp = -1: density; 0..2: velocity component (FP64 moments of f*)
+// FP64 moments of f* (eq. (11)) and the owners of the nodes begin .. begin +
+// count, the populations read once for all of them.
 template <typename S>
-__global__ void k_moment(const S* f, size_t n, int comp, double* out) {
-  const size_t id = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (id >= n) return;
-  double rho = 0.0, J = 0.0;
-  for (int i = 0; i < Q; ++i) {
-    const double v = full_f<S>(Store<S>::ld(f, (int)(i * n + id)), i);
-    rho += v;
-    const int c = comp == 0 ? cx(i) : (comp == 1 ? cy(i) : cz(i));
-    J += c * v;
+__global__ __launch_bounds__(256) void k_moments(const S* f, const int* owner, size_t n,
+                                                 long long begin, long long count,
+                                                 double* __restrict__ rho_out,
+                                                 double* __restrict__ u_out,
+                                                 int* __restrict__ owner_out) {
+  __shared__ double sh[3 * 256];
+  const long long at = (long long)blockIdx.x * 256 + threadIdx.x;
+  const bool valid = at < count;
+  double u[3] = {0.0, 0.0, 0.0};
+  if (valid) {
+    const size_t id = (size_t)(begin + at);
+    if (rho_out || u_out) {
+      double rho = 0.0, J[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        const double v = full_f<S>(Store<S>::ld(f, (int)(i * n + id)), i);
+        rho += v;
+        J[0] += cx(i) * v;
+        J[1] += cy(i) * v;
+        J[2] += cz(i) * v;
+      }
+      if (rho_out) rho_out[at] = rho;
+      for (int k = 0; k < 3; ++k) u[k] = J[k] / rho;
+    }
+    if (owner_out) owner_out[at] = owner[id];
   }
-  out[id] = comp < 0 ? rho : J / rho;
+  if (u_out) store_rows3(sh, u, (long long)blockIdx.x * 256, count, u_out);
 }
 
 unsigned blocks_for(size_t n) { return (unsigned)((n + 255) / 256); }
@@ -1181,24 +1203,27 @@ hipError_t launch_store_direction(Ctx& c, void* f, int i, const double* srcv) {
 }
 
 template <typename S>
-static void run_load(Ctx& c, const void* f, int i, double* out) {
-  hipLaunchKernelGGL(k_load_dir<S>, dim3(blocks_for(c.g.ncell)), dim3(256), 0,
-                     c.stream, (const S*)f, (size_t)c.g.ncell, i, out);
+static void run_load(Ctx& c, const void* f, long long begin, long long count, double* out) {
+  hipLaunchKernelGGL(k_load_pops<S>, dim3(blocks_for(count)), dim3(256), 0, c.stream,
+                     (const S*)f, (size_t)c.g.ncell, begin, count, out);
 }
 
-hipError_t launch_load_direction(Ctx& c, const void* f, int i, double* dst) {
-  DISPATCH(c, run_load, (c, f, i, dst));
+hipError_t launch_load_populations(Ctx& c, const void* f, long long begin, long long count,
+                                   double* dst) {
+  DISPATCH(c, run_load, (c, f, begin, count, dst));
   return hipGetLastError();
 }
 
 template <typename S>
-static void run_moment(Ctx& c, const void* f, int comp, double* out) {
-  hipLaunchKernelGGL(k_moment<S>, dim3(blocks_for(c.g.ncell)), dim3(256), 0,
-                     c.stream, (const S*)f, (size_t)c.g.ncell, comp, out);
+static void run_moments(Ctx& c, const void* f, long long begin, long long count, double* rho,
+                        double* u, int* owner) {
+  hipLaunchKernelGGL(k_moments<S>, dim3(blocks_for(count)), dim3(256), 0, c.stream, (const S*)f,
+                     c.owner, (size_t)c.g.ncell, begin, count, rho, u, owner);
 }
 
-hipError_t launch_moment(Ctx& c, const void* f, int comp, double* out) {
-  DISPATCH(c, run_moment, (c, f, comp, out));
+hipError_t launch_moments(Ctx& c, const void* f, long long begin, long long count, double* rho,
+                          double* u, int* owner) {
+  DISPATCH(c, run_moments, (c, f, begin, count, rho, u, owner));
   return hipGetLastError();
 }
 
