@@ -342,12 +342,21 @@ hlbm_status hlbm_set_state(hlbm_ctx *ctx, const void *blob, size_t bytes);
    a device snapshot of the whole state every `ckpt_every` steps (plus the
    end state); the context then stands at the end of the window, as after
    hlbm_step(ksteps).  Memory: ceil(ksteps / ckpt_every) + 1 snapshots of
-   about 19 x 8 B per node each.
+   about 19 x 8 B per node each, and, if there is room for them, the
+   gradient's ckpt_every + 3 population fields, which then hold the last
+   segment already (else the gradient allocates them and runs it again).
+
+   hlbm_adjoint_bytes, hlbm_bind_adjoint: the device memory of such a window,
+   snapshots and fields together, and lending it.  A caller that takes many
+   gradients lends one block instead of having gigabytes allocated and freed
+   in each; the context never frees it, and it must stay until the context is
+   destroyed or another (or none: NULL) is bound.  Binding drops a recorded
+   window; a window that does not fit the block is allocated.
 
    hlbm_adjoint_gradient: for J = sum_p dJ_dU[p] . U_p (the particle
    velocities at the end of the window; dJ_dU is 3n, host), recomputes each
    segment from its checkpoint (keeping ckpt_every + 1 population fields on
-   the device) and sweeps it in reverse.  Outputs (host, any may be NULL):
+   the device, plus two for the sweep) and sweeps it in reverse.  Outputs (host, any may be NULL):
      dJ_ds[n]         derivative by each particle's density ratio s_p (mass,
                       inertia, gravity-buoyancy, and the balance acceleration
                       of a balanced box);
@@ -365,6 +374,9 @@ hlbm_status hlbm_set_state(hlbm_ctx *ctx, const void *blob, size_t bytes);
    autograd wrapper): ksteps steps from the current state with checkpoints
    every ckpt_every steps, then dJ_ds and dJ_dq0 of
    J = sum_p dJ_dU[p] . U_p. */
+hlbm_status hlbm_adjoint_bytes(hlbm_ctx *ctx, int ksteps, int ckpt_every,
+                               size_t *bytes);
+hlbm_status hlbm_bind_adjoint(hlbm_ctx *ctx, void *dev, size_t bytes);
 hlbm_status hlbm_adjoint_record(hlbm_ctx *ctx, int ksteps, int ckpt_every);
 hlbm_status hlbm_adjoint_gradient(hlbm_ctx *ctx, const double *dJ_dU,
                                   double *dJ_ds, double *dJ_dtheta0,

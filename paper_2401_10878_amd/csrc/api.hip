@@ -339,22 +339,11 @@ void free_timing(Ctx& c) {
   c.timing = false;
 }
 
-void free_snapshot(Snapshot& s) {
-  void* p[] = {s.f, s.part, s.tiles, s.psums, s.keys[0], s.keys[1], s.rec[0],
-               s.rec[1], s.owner, s.ctr};
-  for (void* q : p)
-    if (q) hipFree(q);
-  s = Snapshot();
-}
-
 void free_adjoint(Ctx& c) {
   Adjoint& a = c.adj;
   if (c.stream) hipStreamSynchronize(c.stream);
-  for (int k = 0; k < a.nseg; ++k) free_snapshot(a.ck[k]);
   delete[] a.ck;
-  free_snapshot(a.end);
-  void* p[] = {a.fst, a.ost, a.pst, a.frc, a.gbar, a.hbar, a.pbar, a.sbar, a.work};
-  for (void* q : p)
+  for (void* q : a.block)
     if (q) hipFree(q);
   a = Adjoint();
 }
@@ -373,19 +362,29 @@ void free_particles(Ctx& c) {
 // ---- state snapshots (device-to-device copies on the context stream) ------
 size_t pop_bytes(const Ctx& c) { return (size_t)Q * (size_t)c.g.ncell * c.bytes_per_value; }
 
-hipError_t snapshot_alloc(Ctx& c, Snapshot& s) {
-  hipError_t e;
-  const size_t cap = (size_t)c.tab[0].cap;
-  if ((e = hipMalloc(&s.f, pop_bytes(c)))) return e;
-  if ((e = hipMalloc(&s.part, c.part_bytes))) return e;
-  if ((e = hipMalloc(&s.tiles, c.tile_bytes))) return e;
-  if ((e = hipMalloc(&s.psums, c.psum_bytes))) return e;
-  for (int k = 0; k < 2; ++k) {
-    if ((e = hipMalloc(&s.keys[k], key_block_bytes((int)cap)))) return e;
-    if ((e = hipMalloc(&s.rec[k], sizeof(PairRec) * cap))) return e;
+// Rows of one allocation, 256-byte aligned: with a null base only the size.
+struct Arena {
+  char* base = nullptr;
+  size_t used = 0;
+  template <typename T>
+  void take(T** p, size_t count) {
+    if (base) *p = (T*)(base + used);
+    used += (sizeof(T) * count + 255) / 256 * 256;
   }
-  if ((e = hipMalloc(&s.owner, sizeof(int) * (size_t)c.g.ncell))) return e;
-  return hipMalloc(&s.ctr, sizeof(Counters));
+};
+
+void lay_snapshot(const Ctx& c, Snapshot& s, Arena& m) {
+  const size_t cap = (size_t)c.tab[0].cap;
+  m.take((char**)&s.f, pop_bytes(c));
+  m.take((char**)&s.part, c.part_bytes);
+  m.take((char**)&s.tiles, c.tile_bytes);
+  m.take((char**)&s.psums, c.psum_bytes);
+  for (int k = 0; k < 2; ++k) {
+    m.take((char**)&s.keys[k], key_block_bytes((int)cap));
+    m.take(&s.rec[k], cap);
+  }
+  m.take(&s.owner, (size_t)c.g.ncell);
+  m.take(&s.ctr, 1);
 }
 
 // dir = 0: context -> snapshot, 1: snapshot -> context
@@ -415,6 +414,97 @@ hipError_t snapshot_copy(Ctx& c, Snapshot& s, int dir) {
   }
   if ((e = cp(s.owner, c.owner, sizeof(int) * (size_t)c.g.ncell))) return e;
   return cp(s.ctr, c.counters, sizeof(Counters));
+}
+
+void adjoint_window(Adjoint& a, int ksteps, int ckpt_every) {
+  a.K = ksteps;
+  a.L = ckpt_every < ksteps ? ckpt_every : ksteps;
+  a.nseg = (a.K + a.L - 1) / a.L;
+}
+
+void lay_snapshots(Ctx& c, Arena& m) {
+  for (int k = 0; k < c.adj.nseg; ++k) lay_snapshot(c, c.adj.ck[k], m);
+  lay_snapshot(c, c.adj.end, m);
+}
+
+// The store of one segment of the adjoint's window (f*, owners and particle
+// states at each of its L + 1 steps, the forces of its L) and the work arrays
+// of the reverse sweep.
+void lay_store(const Ctx& c, Adjoint& a, Arena& m) {
+  const size_t n = (size_t)c.g.ncell, npp = c.np > 0 ? c.np : 1, L = a.L;
+  m.take(&a.fst, (L + 1) * Q * n);
+  m.take(&a.ost, (L + 1) * n);
+  m.take(&a.pst, (L + 1) * npp * adjoint_record_doubles());
+  m.take(&a.frc, L * npp * 12);
+  for (int k = 0; k < 2; ++k) m.take(&a.hbar[k], Q * n);
+  m.take(&a.pbar, npp * adjoint_slots());
+  m.take(&a.sbar, npp);
+  m.take(&a.work, adjoint_work_doubles(c));
+}
+
+// Place what `lay` lays out as the adjoint's block k: in the lent memory if it
+// is large enough (the first block only), else in an allocation.
+template <typename Lay>
+bool adjoint_block(Ctx& c, int k, Lay lay) {
+  Arena m;
+  lay(m);
+  void* p = k == 0 && m.used <= c.adj_mem_bytes ? c.adj_mem : nullptr;
+  if (!p) {
+    if (hipMalloc(&p, m.used) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    c.adj.block[k] = p;
+  }
+  m.base = (char*)p;
+  m.used = 0;
+  lay(m);
+  return true;
+}
+
+// Run the n steps of segment seg from its checkpoint (restore) or from the
+// current state, every step's populations and owners written straight into
+// the store: the context's population and owner pointers stand on the store's
+// rows meanwhile, and nothing is copied per step.  Without restore the end
+// state is copied back to the context's own buffers.
+hipError_t run_stored(Ctx& c, int seg, int n, bool restore) {
+  Adjoint& a = c.adj;
+  void* const fb[2] = {c.fbuf[0], c.fbuf[1]};
+  int* const ow = c.owner;
+  const size_t fs = (size_t)Q * (size_t)c.g.ncell, os = (size_t)c.g.ncell;
+  const size_t ps = (size_t)(c.np > 0 ? c.np : 1) * adjoint_record_doubles();
+  const size_t rs = (size_t)(c.np > 0 ? c.np : 1) * 12;
+  a.stored = -1;
+  hipError_t e = hipSuccess;
+  if (restore) {
+    c.fbuf[0] = c.fbuf[1] = a.fst;
+    c.owner = a.ost;
+    e = snapshot_copy(c, a.ck[seg], 1);
+  } else {
+    if ((e = hipMemcpyAsync(a.fst, c.fbuf[c.cur], sizeof(double) * fs, hipMemcpyDeviceToDevice,
+                            c.stream)) == hipSuccess)
+      e = hipMemcpyAsync(a.ost, c.owner, sizeof(int) * os, hipMemcpyDeviceToDevice, c.stream);
+  }
+  if (e == hipSuccess) e = launch_record(c, a.pst, nullptr);
+  for (int k = 0; k < n && e == hipSuccess; ++k) {
+    c.fbuf[c.cur] = a.fst + (size_t)k * fs;
+    c.fbuf[1 - c.cur] = a.fst + (size_t)(k + 1) * fs;
+    c.owner = a.ost + (size_t)(k + 1) * os;
+    e = run_step(c, nullptr);
+    if (e == hipSuccess) e = launch_record(c, a.pst + (k + 1) * ps, a.frc + k * rs);
+  }
+  c.fbuf[0] = fb[0];
+  c.fbuf[1] = fb[1];
+  c.owner = ow;
+  if (!restore && e == hipSuccess) {
+    e = hipMemcpyAsync(c.fbuf[c.cur], a.fst + (size_t)n * fs, sizeof(double) * fs,
+                       hipMemcpyDeviceToDevice, c.stream);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(c.owner, a.ost + (size_t)n * os, sizeof(int) * os,
+                         hipMemcpyDeviceToDevice, c.stream);
+  }
+  if (e == hipSuccess) a.stored = seg;
+  return e;
 }
 
 }  // namespace
@@ -1406,6 +1496,31 @@ hlbm_status hlbm_set_state(hlbm_ctx* h, const void* blob, size_t bytes) {
   return st != HLBM_OK ? st : prepare_graphs(c);
 }
 
+hlbm_status hlbm_adjoint_bytes(hlbm_ctx* h, int ksteps, int ckpt_every, size_t* bytes) {
+  if (!h || !bytes) return HLBM_E_ARG;
+  Ctx& c = h->c;
+  if (!c.particles_ready) return fail(c, HLBM_E_STATE, "initialise the particles first");
+  if (ksteps < 1 || ckpt_every < 1)
+    return fail(c, HLBM_E_ARG, "ksteps and ckpt_every must be >= 1");
+  Adjoint a;
+  adjoint_window(a, ksteps, ckpt_every);
+  Arena one, store;
+  Snapshot snap;
+  lay_snapshot(c, snap, one);
+  lay_store(c, a, store);
+  *bytes = one.used * (size_t)(a.nseg + 1) + store.used;
+  return HLBM_OK;
+}
+
+hlbm_status hlbm_bind_adjoint(hlbm_ctx* h, void* dev, size_t bytes) {
+  if (!h) return HLBM_E_ARG;
+  Ctx& c = h->c;
+  free_adjoint(c);                                 // (waits for the stream)
+  c.adj_mem = bytes ? dev : nullptr;
+  c.adj_mem_bytes = dev ? bytes : 0;
+  return HLBM_OK;
+}
+
 hlbm_status hlbm_adjoint_record(hlbm_ctx* h, int ksteps, int ckpt_every) {
   if (!h) return HLBM_E_ARG;
   Ctx& c = h->c;
@@ -1430,24 +1545,28 @@ hlbm_status hlbm_adjoint_record(hlbm_ctx* h, int ksteps, int ckpt_every) {
     return fail(c, HLBM_E_ARG, "ksteps and ckpt_every must be >= 1");
   free_adjoint(c);
   Adjoint& a = c.adj;
-  a.K = ksteps;
-  a.L = ckpt_every < ksteps ? ckpt_every : ksteps;
-  a.nseg = (a.K + a.L - 1) / a.L;
+  adjoint_window(a, ksteps, ckpt_every);
   a.ck = new (std::nothrow) Snapshot[a.nseg];
   if (!a.ck) return fail(c, HLBM_E_NOMEM, "checkpoint table");
-  for (int k = 0; k < a.nseg; ++k)
-    if (snapshot_alloc(c, a.ck[k]) != hipSuccess) {
-      free_adjoint(c);
-      return fail(c, HLBM_E_NOMEM, "checkpoint %d of %d", k, a.nseg);
-    }
-  if (snapshot_alloc(c, a.end) != hipSuccess) {
+  // the last segment goes straight into the store if there is memory for it
+  // (the gradient then need not run it again)
+  const bool store = adjoint_block(c, 0, [&](Arena& m) {
+    lay_snapshots(c, m);
+    lay_store(c, a, m);
+  });
+  if (!store && !adjoint_block(c, 0, [&](Arena& m) { lay_snapshots(c, m); })) {
+    const int nseg = a.nseg;
     free_adjoint(c);
-    return fail(c, HLBM_E_NOMEM, "end-state snapshot");
+    return fail(c, HLBM_E_NOMEM, "%d checkpoints and the end state", nseg);
   }
   for (int seg = 0; seg < a.nseg; ++seg) {
     HIPCHECK(snapshot_copy(c, a.ck[seg], 0));
     const int n = std::min(a.L, a.K - seg * a.L);
-    for (int s = 0; s < n; ++s) HIPCHECK(run_step(c, nullptr));
+    if (store && seg == a.nseg - 1) {
+      HIPCHECK(run_stored(c, seg, n, false));
+    } else {
+      for (int s = 0; s < n; ++s) HIPCHECK(run_step(c, nullptr));
+    }
   }
   HIPCHECK(snapshot_copy(c, a.end, 0));
   hlbm_status st = check_flags(c);
@@ -1469,18 +1588,8 @@ hlbm_status hlbm_adjoint_gradient(hlbm_ctx* h, const double* dJ_dU, double* dJ_d
   const size_t npp = np > 0 ? np : 1;
   const long long n = c.g.ncell;
   const int PR = adjoint_record_doubles(), PB = adjoint_slots();
-  if (!a.fst) {
-    bool ok = hipMalloc(&a.fst, sizeof(double) * (size_t)(a.L + 1) * Q * n) == hipSuccess &&
-              hipMalloc(&a.ost, sizeof(int) * (size_t)(a.L + 1) * n) == hipSuccess &&
-              hipMalloc(&a.pst, sizeof(double) * (size_t)(a.L + 1) * npp * PR) == hipSuccess &&
-              hipMalloc(&a.frc, sizeof(double) * (size_t)a.L * npp * 12) == hipSuccess &&
-              hipMalloc(&a.gbar, sizeof(double) * (size_t)Q * n) == hipSuccess &&
-              hipMalloc(&a.hbar, sizeof(double) * (size_t)Q * n) == hipSuccess &&
-              hipMalloc(&a.pbar, sizeof(double) * npp * PB) == hipSuccess &&
-              hipMalloc(&a.sbar, sizeof(double) * npp) == hipSuccess &&
-              hipMalloc(&a.work, sizeof(double) * adjoint_work_doubles(c)) == hipSuccess;
-    if (!ok) return fail(c, HLBM_E_NOMEM, "adjoint work arrays (segment of %d steps)", a.L);
-  }
+  if (!a.fst && !adjoint_block(c, 1, [&](Arena& m) { lay_store(c, a, m); }))
+    return fail(c, HLBM_E_NOMEM, "adjoint work arrays (segment of %d steps)", a.L);
   // seed: J = sum_p dJ_dU[p] . U_p(K)
   std::vector<double> pb(npp * PB, 0.0);
   for (int p = 0; p < np; ++p)
@@ -1488,29 +1597,30 @@ hlbm_status hlbm_adjoint_gradient(hlbm_ctx* h, const double* dJ_dU, double* dJ_d
   HIPCHECK(hipMemcpyAsync(a.pbar, pb.data(), sizeof(double) * npp * PB,
                           hipMemcpyHostToDevice, c.stream));
   HIPCHECK(launch_fill_zero(c, a.sbar, (long long)npp));
-  HIPCHECK(launch_fill_zero(c, a.gbar, (long long)Q * n));
-  const size_t fs = (size_t)Q * n;
+  // J depends on U(K) alone: dJ/df and the acceleration's adjoint start at 0
+  HIPCHECK(launch_fill_zero(c, a.hbar[0], (long long)Q * n));
+  HIPCHECK(launch_fill_zero(c, a.work, (long long)adjoint_work_doubles(c)));
+  const size_t fs = (size_t)Q * n, ps = npp * PR, rs = npp * 12;
+  int in = 0;   // a.hbar[in]: dJ/df of the step last reversed
   for (int seg = a.nseg - 1; seg >= 0; --seg) {
-    HIPCHECK(snapshot_copy(c, a.ck[seg], 1));
     const int L = std::min(a.L, a.K - seg * a.L);
-    // recompute the segment, recording what the reverse steps read
-    for (int k = 0; k <= L; ++k) {
-      if (k < L)
-        HIPCHECK(hipMemcpyAsync(a.fst + (size_t)k * fs, c.fbuf[c.cur],
-                                sizeof(double) * fs, hipMemcpyDeviceToDevice, c.stream));
-      HIPCHECK(hipMemcpyAsync(a.ost + (size_t)k * n, c.owner, sizeof(int) * n,
-                              hipMemcpyDeviceToDevice, c.stream));
-      HIPCHECK(launch_rec_particles(c, a.pst + (size_t)k * npp * PR));
-      if (k == L) break;
-      HIPCHECK(run_step(c, nullptr));
-      HIPCHECK(launch_rec_forces(c, a.frc + (size_t)k * npp * 12));
+    if (a.stored != seg) HIPCHECK(run_stored(c, seg, L, true));
+    auto node = [&](int k) {
+      const hipError_t e = launch_adjoint_node(
+          c, a.hbar[in], k > 0 ? a.hbar[1 - in] : nullptr, a.fst + (size_t)k * fs,
+          k > 0 ? a.fst + (size_t)(k - 1) * fs : nullptr, a.ost + (size_t)k * n,
+          a.pst + (size_t)k * ps, a.pbar, a.work);
+      in = 1 - in;
+      return e;
+    };
+    // (the nodes of a segment's last state, the first of the next one, need
+    // the populations before it)
+    if (seg < a.nseg - 1) HIPCHECK(node(L));
+    for (int k = L; k >= 1; --k) {
+      HIPCHECK(launch_adjoint_move(c, a.pst + (size_t)k * ps, a.frc + (size_t)(k - 1) * rs,
+                                   a.pbar, a.sbar, a.work));
+      if (k > 1 || seg == 0) HIPCHECK(node(k - 1));
     }
-    for (int k = L - 1; k >= 0; --k)
-      HIPCHECK(launch_adjoint_step(c, a.gbar, a.hbar, a.fst + (size_t)k * fs,
-                                   a.ost + (size_t)k * n, a.ost + (size_t)(k + 1) * n,
-                                   a.pst + (size_t)k * npp * PR,
-                                   a.pst + (size_t)(k + 1) * npp * PR,
-                                   a.frc + (size_t)k * npp * 12, a.pbar, a.sbar, a.work));
   }
   // initial orientations, from the particle block of checkpoint 0
   std::vector<double> q0(4 * npp);

@@ -153,6 +153,21 @@ __host__ __device__ inline unsigned fdiv(unsigned n, FastDiv f) {
   return (unsigned)(((((unsigned long long)n * f.m) >> 32) + n) >> f.s);
 }
 
+// Loads and stores at byte offset b of an array as raw buffer operations: a
+// scalar resource over the array from p (no range check is relied on; every
+// offset lies inside the array) and a 32-bit per-lane byte offset, which the
+// hardware adds without vector address arithmetic.
+__device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00020000);
+}
+// Logical block id with consecutive ids kept on one XCD (workgroups are
+// dispatched round-robin over the 8 XCDs, each with its own L2).
+__device__ inline unsigned xcd_block(unsigned bid, unsigned nblocks) {
+  const unsigned m = nblocks / 8, r = nblocks % 8;
+  const unsigned xcd = bid % 8, k = bid / 8;
+  return xcd * m + (xcd < r ? xcd : r) + k;
+}
+
 // Scalar parameters handed to every kernel by value.
 struct Geom {
   int nx, ny, nz;
@@ -235,6 +250,10 @@ struct Snapshot {
 struct Adjoint {
   bool recorded = false;
   int K = 0, L = 0;                  // steps, steps per checkpoint
+  // one block (lent, see Ctx::adj_mem, or allocated) for the snapshots, the
+  // store and the work arrays, or (memory short at the record) one for the
+  // snapshots and one, at the gradient, for the rest
+  void* block[2] = {nullptr, nullptr};   // those allocated here
   Snapshot* ck = nullptr;            // checkpoint at the start of each segment
   int nseg = 0;
   Snapshot end;                      // state after the K steps
@@ -242,11 +261,11 @@ struct Adjoint {
   int* ost = nullptr;                // (L + 1) x ncell: owner maps
   double* pst = nullptr;             // (L + 1) x np x 22: particle states
   double* frc = nullptr;             // L x np x 12: forces of each step
-  double* gbar = nullptr;            // dJ/df* (Q x ncell)
-  double* hbar = nullptr;            // dJ/df  (Q x ncell)
+  int stored = -1;                   // the segment that these four hold
+  double* hbar[2] = {nullptr, nullptr};   // dJ/df (Q x ncell), in and out
   double* pbar = nullptr;            // np x 12 particle adjoints
   double* sbar = nullptr;            // np: dJ/ds
-  double* work = nullptr;
+  double* work = nullptr;            // adjoint_work_doubles
 };
 
 struct Ctx {
@@ -310,6 +329,9 @@ struct Ctx {
   // sizes of the state blocks (for snapshots)
   size_t part_bytes = 0, tile_bytes = 0, psum_bytes = 0;
   Adjoint adj;
+  // device memory lent for the adjoint (hlbm_bind_adjoint), never freed here
+  void* adj_mem = nullptr;
+  size_t adj_mem_bytes = 0;
   // graphs: one per (population parity, contact-table parity) for a single
   // step and one for GRAPH_STEPS steps
   bool use_graph;
@@ -385,13 +407,17 @@ hipError_t noalloc_scratch(double** out);
 int adjoint_record_doubles();
 int adjoint_slots();
 size_t adjoint_work_doubles(const Ctx& c);
-hipError_t launch_rec_particles(Ctx& c, double* out);
-hipError_t launch_rec_forces(Ctx& c, double* out);
+// particle records and (frc given) the forces of the last step
+hipError_t launch_record(Ctx& c, double* prec, double* frc);
 hipError_t launch_fill_zero(Ctx& c, double* p, long long n);
-hipError_t launch_adjoint_step(Ctx& c, double* gbar, double* hbar,
-                               const double* fprev, const int* owner_prev,
-                               const int* owner_t, const double* prec_prev,
-                               const double* prec_t, const double* frc,
-                               double* pbar, double* sbar, double* work);
+// reverse of the motion of a step: prec its particle records, frc its forces
+hipError_t launch_adjoint_move(Ctx& c, const double* prec, const double* frc, double* pbar,
+                               double* sbar, double* work);
+// reverse of the momentum exchange of the next step and of the collision of
+// this one (hin: dJ/df of the next step; hout null, the initial state: no
+// collision; fown: f* of this step, fprev: of the one before)
+hipError_t launch_adjoint_node(Ctx& c, double* hin, double* hout, const double* fown,
+                               const double* fprev, const int* owner, const double* prec,
+                               double* pbar, double* work);
 
 }  // namespace hlbm

@@ -83,13 +83,6 @@ struct Store<__half> {
 __device__ inline int owner_at(const int* owner, unsigned b) {
   return owner_id(*(const int*)((const char*)owner + b));
 }
-// Loads and stores at byte offset b of an array as raw buffer operations: a
-// scalar resource over the array from p (no range check is relied on; every
-// offset lies inside the array) and a 32-bit per-lane byte offset, which the
-// hardware adds without vector address arithmetic.
-__device__ inline __amdgpu_buffer_rsrc_t rsrc_of(const void* p) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00020000);
-}
 // Access policy of the populations.  A pass reads what the pass before it
 // wrote: where both buffers fit the Infinity Cache (256 MB, on the memory
 // side) together, plain accesses find most of it there.  A larger lattice
@@ -139,14 +132,6 @@ __device__ inline C cdot(int i, C a, C b, C c) {
 template <typename S>
 __device__ inline double full_f(typename Store<S>::C h, int i) {
   return Store<S>::shifted ? wgt(i) + (double)h : (double)h;
-}
-
-// Logical block id with consecutive ids kept on one XCD (workgroups are
-// dispatched round-robin over the 8 XCDs, each with its own L2).
-__device__ inline unsigned xcd_block(unsigned bid, unsigned nblocks) {
-  const unsigned m = nblocks / 8, r = nblocks % 8;
-  const unsigned xcd = bid % 8, k = bid / 8;
-  return xcd * m + (xcd < r ? xcd : r) + k;
 }
 
 // Lattice block of the workgroup (LX x LY x LZ nodes, one x-row per

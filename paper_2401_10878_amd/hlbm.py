@@ -109,6 +109,8 @@ def load():
     L.hlbm_fluid_acceleration.argtypes = [v, P(d)]
     L.hlbm_get_state.argtypes = [v, v, P(C.c_size_t)]
     L.hlbm_set_state.argtypes = [v, v, C.c_size_t]
+    L.hlbm_adjoint_bytes.argtypes = [v, i, i, P(C.c_size_t)]
+    L.hlbm_bind_adjoint.argtypes = [v, v, C.c_size_t]
     L.hlbm_adjoint_record.argtypes = [v, i, i]
     L.hlbm_adjoint_gradient.argtypes = [v] + [P(d)] * 7
     L.hlbm_adjoint.argtypes = [v, i, i, P(d), P(d), P(d)]
@@ -177,6 +179,7 @@ class Simulation:
                                        C.c_void_p(self.stream.cuda_stream),
                                        C.byref(h)), None)
         self.h = h
+        self.adj_mem = None
         nbytes = Q * self.ncell * BYTES[params.precision]
         self.fa = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         self.fb = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
@@ -211,8 +214,9 @@ class Simulation:
 
     def close(self):
         if getattr(self, "h", None):
-            self.L.hlbm_destroy(self.h)
+            self.L.hlbm_destroy(self.h)      # (waits for the library's stream)
             self.h = None
+            self.adj_mem = None
 
     def __del__(self):
         try:
@@ -347,8 +351,31 @@ class Simulation:
         self._check(self.L.hlbm_set_state(self.h, buf, len(blob)))
 
     # ---- adjoint ------------------------------------------------------------
+    def _lend_adjoint(self, ksteps, ckpt_every):
+        """Lend the library the memory of a window from torch's allocator, which
+        keeps it between gradients: allocating and freeing gigabytes in each
+        one has the driver clear them in between (96^3, 20 steps: 8 ms a
+        gradient, but 55 ms on average over hundreds).  Without room (or on
+        arguments that the record refuses) the library allocates itself."""
+        n = C.c_size_t()
+        if self.L.hlbm_adjoint_bytes(self.h, int(ksteps), int(ckpt_every), C.byref(n)):
+            return
+        mem = self.adj_mem
+        if mem is not None and mem.numel() >= n.value:
+            return
+        torch = self.torch
+        try:
+            mem = torch.empty(n.value, dtype=torch.uint8, device=self.device)
+        except RuntimeError:
+            return
+        # what torch has queued on this memory comes first
+        self.stream.wait_stream(torch.cuda.current_stream(self.device))
+        self._check(self.L.hlbm_bind_adjoint(self.h, C.c_void_p(mem.data_ptr()), n.value))
+        self.adj_mem = mem
+
     def adjoint_record(self, ksteps, ckpt_every):
         """Run ksteps steps keeping checkpoints every ckpt_every steps."""
+        self._lend_adjoint(ksteps, ckpt_every)
         self._check(self.L.hlbm_adjoint_record(self.h, ksteps, ckpt_every))
 
     def adjoint_gradient(self, dJ_dU):
@@ -370,6 +397,7 @@ class Simulation:
         seed = np.zeros((n, 3))
         seed[:self.np] = np.asarray(dJ_dU, np.float64).reshape(self.np, 3)
         ds, dq = np.zeros(n), np.zeros((n, 4))
+        self._lend_adjoint(ksteps, ckpt_every)
         self._check(self.L.hlbm_adjoint(self.h, int(ksteps), int(ckpt_every),
                                         _dp(seed), _dp(ds), _dp(dq)))
         return ds[:self.np], dq[:self.np]
