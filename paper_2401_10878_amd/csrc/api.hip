@@ -551,6 +551,9 @@ hlbm_status hlbm_create(const hlbm_params* params, void* stream, hlbm_ctx** out)
   c.g.ltx = (P.nx + LX - 1) / LX;
   c.g.lty = (P.ny + LY - 1) / LY;
   c.g.ltz = (P.nz + LZ - 1) / LZ;
+  c.g.inv_l[0] = 1.0f / (float)P.nx;
+  c.g.inv_l[1] = 1.0f / (float)P.ny;
+  c.g.inv_l[2] = P.periodic_z ? 1.0f / (float)P.nz : 0.0f;
   c.g.fdtx = make_fastdiv((unsigned)c.g.dtx);
   c.g.fdty = make_fastdiv((unsigned)c.g.dty);
   c.g.fltx = make_fastdiv((unsigned)c.g.ltx);

@@ -178,6 +178,7 @@ struct Geom {
   FastDiv fltx, flty;     // divisions by ltx, lty
   int tile_cap;           // particles per candidate list (both tilings)
   int maxent;             // lattice blocks per particle (partial-sum slots)
+  float inv_l[3];         // 1 / period per axis in FP32, 0 on a bounded axis
   int cached;             // both population buffers fit the Infinity Cache
   long long ncell;
 };

@@ -30,9 +30,9 @@ constexpr int MAXC = 32;        // contacts per particle in one step
 constexpr int BAL_PARTS = 256;  // first-stage workgroups of the balance sums
 // FP32 screening record of a particle, per particle: centre (3), rotation
 // (9), then the detection thresholds with the particle's FP32 error bound
-// tol: eps/2 + tol, eps/2 - tol, sqrt(0.75) + delta_c + tol,
-// sqrt(0.75) + delta_c - tol, the larger upper threshold, the size and
-// the shape code (its bits)
+// tol, squared (screen_sq): eps/2 + tol, eps/2 - tol, sqrt(0.75) + delta_c +
+// tol, sqrt(0.75) + delta_c - tol; the larger upper threshold, the size, the
+// shape code (its bits) and the smaller lower threshold (as distances)
 constexpr int SREC = 20;
 // FP32 kinematic record of a particle for the lattice pass (FP32 and
 // binary16 storage), 128 bytes (a record address is a shift of the id): the
@@ -858,6 +858,43 @@ __device__ inline float sdf32_r(int shape, float size, const float* R, float r0,
   const float m0 = fmaxf(q0, 0.0f), m1 = fmaxf(q1, 0.0f), m2 = fmaxf(q2, 0.0f);
   return __builtin_amdgcn_sqrtf(m0 * m0 + m1 * m1 + m2 * m2) +
          fminf(fmaxf(fmaxf(q0, q1), q2), 0.0f);
+}
+
+// Offset to the nearest periodic image: v - L rint(v / L) (inv = 1 / L, 0 on
+// a bounded axis).  Beyond half a period either image is out of reach.
+__device__ inline float wrap_f(float v, float L, float inv) {
+#pragma clang fp contract(fast)
+  return v - L * __builtin_rintf(v * inv);
+}
+
+// Squared FP32 distance for the detection's screen: of a point outside the
+// body from its surface, 0 inside; for a sphere of the point from its centre.
+// It is compared with the squared thresholds that screen_sq writes into the
+// particle's record.
+template <bool POLY, bool ELL>
+__device__ inline float screen32(int shape, float size, const float* R, float r0, float r1,
+                                 float r2, const PolyDev* poly, float far, float inner) {
+#pragma clang fp contract(fast)
+  if (shape == 0) return r0 * r0 + r1 * r1 + r2 * r2;
+  if (shape == 1) {
+    const float h = 0.5f * size;
+    const float p0 = R[0] * r0 + R[3] * r1 + R[6] * r2;
+    const float p1 = R[1] * r0 + R[4] * r1 + R[7] * r2;
+    const float p2 = R[2] * r0 + R[5] * r1 + R[8] * r2;
+    const float m0 = fmaxf(fabsf(p0) - h, 0.0f), m1 = fmaxf(fabsf(p1) - h, 0.0f),
+                m2 = fmaxf(fabsf(p2) - h, 0.0f);
+    return m0 * m0 + m1 * m1 + m2 * m2;
+  }
+  const float d = fmaxf(sdf32_r<ELL>(shape, size, R, r0, r1, r2, POLY ? poly : nullptr, far, inner),
+                        0.0f);
+  return d * d;
+}
+// The squared form of threshold t for a particle; below zero (a band narrower
+// than the error bound) nothing is certain: -1, which every square exceeds.
+__device__ inline float screen_sq(int shape, float size, float t) {
+  if (t <= 0.0f) return -1.0f;
+  const float r = shape == 0 ? size + t : t;
+  return r * r;
 }
 
 // Signed distance with its world-frame gradient.  Inside a cube the

@@ -109,22 +109,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? (ELL
   const double own_t = 0.5 * ph.eps;              // owner:     d < eps/2
 
   // Pass 1, FP32: classify each candidate against both thresholds with a
-  // bound tol on the FP32 error (the thresholds +- tol come with the
-  // candidate's screening record).  Per lane: mask = candidates that may
-  // be flagged (d < sqrt(0.75) + delta_c + tol; when eps/2 is the smaller
-  // threshold, a superset of those that may own the node), nown = how many
-  // may own it (d < eps/2 + tol) and bp
-  // the last of them; near_own / any_dun = one of them lies within tol of
-  // its threshold, so FP32 cannot decide.  Over the wavefront (ballots):
-  // det_w = candidates some lane may flag.
+  // bound tol on the FP32 error.  The screen works on squares: the squared
+  // distance of a node outside the body (0 inside; a sphere: of the node from
+  // the centre) against the squared thresholds +- tol of the candidate's
+  // record, which takes no square root and no distance inside.  Per lane:
+  // mask = candidates that may be flagged (d < sqrt(0.75) + delta_c + tol;
+  // when eps/2 is the smaller threshold, a superset of those that may own the
+  // node) and bp the last that may own it (d < eps/2 + tol).  Over the
+  // wavefront, as lane masks in scalar registers: once / twice = lanes with
+  // one / several candidates that may own the node, near = lanes where one of
+  // them lies within tol of the threshold, so FP32 cannot decide, dun the same
+  // for the flags; det_w = candidates some lane may flag.
   //
   // tol = 1e-3 + 1e-5 (|r|_1 + size) is taken with |r|_1 at its largest for
   // a node within reach of either threshold, sqrt 3 (R + 2) with R the
   // circumradius, so it is uniform per candidate: a node farther out has d
   // far above both thresholds, where the bound is not needed.
-  int bp = -1, nown = 0;
-  bool near_own = false, any_dun = false;
-  uint64_t mask = 0, det_w = 0;
+  //
+  // A tile with one candidate and no wall flags nothing: the owner alone is
+  // screened there (about half of the occupied tiles of a dense box).
+  const bool wall_tile = !perz && (tz == 0 || tz == g.dtz - 1);
+  const bool flags = cnt > 1 || wall_tile;        // uniform
+  int bp = -1;
+  uint64_t once = 0, twice = 0, near = 0, dun = 0, det_w = 0;
+  uint64_t mask = 0;
+  const uint64_t vm = __ballot(valid);
   // with a coupling band wider than the detection reach (eps/2 > sqrt(0.75)
   // + delta_c) a candidate may own a node it cannot flag: those are kept
   // apart for pass 2 (uniform branch)
@@ -132,30 +141,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? (ELL
   uint64_t mown = 0;
   for (int c = 0; c < cnt; ++c) {
     const int p = __builtin_amdgcn_readlane(pid, c);
-    // the whole record at once (uniform: scalar loads issued together),
-    // and bookkeeping without short-circuit branches, so that one wait
-    // serves the candidate
+    // the whole record at once (uniform: scalar loads issued together), so
+    // that one wait serves the candidate
     const float* src = P.XR32 + SREC * p;
     float xr[19];
 #pragma unroll
     for (int k = 0; k < 19; ++k) xr[k] = src[k];
     __builtin_amdgcn_sched_barrier(0);
     const int shape = __float_as_int(xr[18]);
-    const float f0 = minimg_f(fxf - xr[0], Lxf, true);
-    const float f1 = minimg_f(fyf - xr[1], Lyf, true);
-    const float f2 = minimg_f(fzf - xr[2], Lzf, perz);
+    const float f0 = wrap_f(fxf - xr[0], Lxf, g.inv_l[0]);
+    const float f1 = wrap_f(fyf - xr[1], Lyf, g.inv_l[1]);
+    const float f2 = wrap_f(fzf - xr[2], Lzf, g.inv_l[2]);
     // a polyhedron's plane lower bound beyond both thresholds ends its search
-    const float d = sdf32_r<ELL>(shape, xr[17], xr + 3, f0, f1, f2, POLY ? P.poly : nullptr,
-                                 xr[16], ELL ? src[19] : -1e30f);
-    const bool may_own = valid & (d < xr[12]), may_det = valid & (d < xr[14]);
-    nown += may_own ? 1 : 0;
+    const float d2 = screen32<POLY, ELL>(shape, xr[17], xr + 3, f0, f1, f2, P.poly, xr[16],
+                                         ELL ? src[19] : -1e30f);
+    const bool may_own = d2 < xr[12];
+    const uint64_t m_own = vm & __ballot(may_own);
+    twice |= once & m_own;
+    once |= m_own;
+    near |= m_own & __ballot(d2 > xr[13]);
     bp = may_own ? p : bp;
-    near_own = near_own | (may_own & (d > xr[13]));
-    any_dun = any_dun | (may_det & (d > xr[15]));
-    mask |= may_det ? 1ull << c : 0ull;
-    if (own_wider) mown |= may_own ? 1ull << c : 0ull;
-    if (__ballot(may_det)) det_w |= 1ull << c;
+    if (flags) {
+      const bool may_det = d2 < xr[14];
+      const uint64_t m_det = vm & __ballot(may_det);
+      dun |= m_det & __ballot(d2 > xr[15]);
+      mask |= may_det ? 1ull << c : 0ull;
+      if (m_det) det_w |= 1ull << c;
+    }
+    if (own_wider || !flags) mown |= may_own ? 1ull << c : 0ull;
   }
+  if (!valid) mask = 0;                           // (a lane past the lattice)
   // Pass 2, FP64, only for lanes pass 1 did not settle: the owner when two
   // or more candidates may own the node or one lies within tol of eps/2
   // (smallest (d, id) among the candidates with d < eps/2), and the
@@ -164,10 +179,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? (ELL
   // oracle's exact expressions (for a candidate clearly inside or outside a
   // threshold the exact decision is the FP32 one).  The wavefront loops over
   // the union of those candidates.
-  const bool own_open = near_own || nown > 1;
+  const bool own_open = __builtin_amdgcn_inverse_ballot_w64(near | twice);
+  const bool any_dun = __builtin_amdgcn_inverse_ballot_w64(dun);
   const bool open = own_open || any_dun;
   uint64_t orm = det_w;
-  if (__ballot(open)) {
+  if (near | twice | dun) {
     const double fx = (double)x, fy = (double)y, fz = (double)z;
     const double Lx = (double)g.nx, Ly = (double)g.ny, Lz = (double)g.nz;
     const uint64_t m1 = open ? (mask | mown) : 0ull;

@@ -252,10 +252,10 @@ __global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
                                  : (sh == 1 ? 0.8660254f * fs : fs);
     const float tol = 1e-3f + 1e-5f * (1.7320508f * (rc + 2.0f) + fs);
     const float ot = (float)(0.5 * ph.eps), dt = (float)(DETECT + ph.delta_c);
-    rec[12] = ot + tol;
-    rec[13] = ot - tol;
-    rec[14] = dt + tol;
-    rec[15] = dt - tol;
+    rec[12] = screen_sq(sh, fs, ot + tol);
+    rec[13] = screen_sq(sh, fs, ot - tol);
+    rec[14] = screen_sq(sh, fs, dt + tol);
+    rec[15] = screen_sq(sh, fs, dt - tol);
     rec[16] = fmaxf(ot, dt) + tol;
     rec[17] = fs;
     rec[18] = __int_as_float(sh);
