@@ -1,13 +1,24 @@
 // Particle motion (eqs. (2)-(3)) and tile binning for the node kernels.
 //
-// One wavefront per particle:
+// A workgroup of PW wavefronts per particle:
 //  1. (moving steps) gather the hydrodynamic force and torque of the last
 //     lattice pass: the sum of this particle's per-tile partial sums, in the
-//     fixed order of its tile enumeration (deterministic, no atomics);
-//  2. every lane evaluates the same FP64 Newton-Euler update (the result is
-//     wave-uniform) and lane 0 stores it;
-//  3. the lanes enumerate the tiles the particle's reach box touches and
+//     fixed order of its tile enumeration (deterministic, no atomics), divided
+//     among the wavefronts;
+//  2. every lane of the first wavefront evaluates the same FP64 Newton-Euler
+//     update (the result is wave-uniform), lane 0 stores it, and the others
+//     take the new position, rotation and reach from LDS;
+//  3. all lanes enumerate the tiles the particle's reach box touches and
 //     append (particle id, enumeration index) to each tile's candidate list.
+//
+// Bound by the latency of its chain (sums, motion, one atomic per listed tile)
+// and, with many particles, by those atomics.  One, two and four wavefronts per
+// particle, us: 256^3 with 1834 cubes 35.1, 30.2, 32.6; 1500 boxes (a polyhedron
+// distance per tile) 78.0, 54.5, 55.8; 734 ellipsoids 19.8, 18.5, 17.1; 120^3
+// with spheres settling 14.5, 14.0, 14.2.  Two it is: with four, not all workgroups of a
+// dense run fit the chip at once.  FP32 tile distances and earlier loads (144
+// registers, three wavefronts per SIMD) gave 37.9 and 39.5 with the cubes, and
+// held to 128 registers 31.4 and 32.8.
 #include "balance.h"
 #include "context.h"
 
@@ -73,10 +84,12 @@ __device__ TileSpan axis_tiles(double c, double e, int n, int nt, int ts,
   return s;
 }
 
-constexpr int UB = 4;   // binning: tiles per lane and round
-constexpr unsigned KEEP_BLOCKS = 64;   // workgroups of the contact carry-over
+constexpr int PW = 2;                  // wavefronts per particle
+constexpr int PT = PW * WAVE;
+constexpr int UB = 4;                  // binning: tiles per thread and round
+constexpr unsigned KEEP_BLOCKS = 64 / PW;   // workgroups of the contact carry-over
 
-__global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
+__global__ __launch_bounds__(PT) void k_particles(Particles P, Geom g, Phys ph,
                                                   double* __restrict__ Fh,
                                                   double* __restrict__ Th,
                                                   double* __restrict__ Fc,
@@ -90,7 +103,7 @@ __global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
     // blocks past the particles (independent of this kernel's particle work)
     const int k = ip - P.n;
     if (k >= keep_blocks) {
-      balance_stage2(bal_parts, ctr, ph, 0);
+      if (threadIdx.x < WAVE) balance_stage2(bal_parts, ctr, ph, 0);
       return;
     }
     // the contact carry-over of the pair table, one listed slot per thread
@@ -100,200 +113,227 @@ __global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
     const int n = *keep_from.nlist;
     int cells = 0;
     long long samples = 0;
-    for (int i = k * WAVE + (int)threadIdx.x; i < n; i += keep_blocks * WAVE) {
+    for (int i = k * PT + (int)threadIdx.x; i < n; i += keep_blocks * PT) {
       const int s = keep_from.list[i];
       samples += keep_from.rec[s].samples;
       cells += keep_from.rec[s].count;
       keep_slot(keep_from, keep_to, s, ctr);
       clear_slot(keep_from, s);
     }
-    if (k * WAVE >= n) return;                    // uniform over the wavefront
+    if (k * PT + ((int)threadIdx.x & ~(WAVE - 1)) >= n) return;   // uniform over the wavefront
     // the treatment's samples (below 2^53: exact) and the cells of the
     // detection that filled this table
     const double sum = wave_sum((double)samples);
     const int csum = wave_sum_i(cells);
-    if (threadIdx.x == 0) {
+    if (threadIdx.x % WAVE == 0) {
       atomicAdd(&ctr->samples, (unsigned long long)sum);
       atomicAdd(&ctr->total_cells, (unsigned long long)csum);
     }
     return;
   }
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
   const bool perz = g.periodic_z != 0;
   const double L[3] = {(double)g.nx, (double)g.ny, (double)g.nz};
   const bool per[3] = {true, true, perz};
-
-  double X[3], U[3], W[3], q[4], R[9];
-  for (int k = 0; k < 3; ++k) {
-    X[k] = P.X[3 * ip + k];
-    U[k] = P.U[3 * ip + k];
-    W[k] = P.W[3 * ip + k];
-  }
-  for (int k = 0; k < 4; ++k) q[k] = P.q[4 * ip + k];
-
-  if (move) {
-    // 1. F_p = sum of the per-tile partials (eqs. (17)-(18)); later
-    // sub-steps of the step keep the force of the first
-    double F[3], T[3];
-    if (move == 1) {
-      const int ne = tl.nent[ip];
-      double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-      for (int k = lane; k < ne; k += WAVE) {
-        const double* pp = tl.part + ((size_t)ip * g.maxent + k) * 6;
-        for (int m = 0; m < 6; ++m) v[m] += pp[m];
-      }
-      for (int m = 0; m < 3; ++m) {
-        F[m] = wave_sum(v[m]) + tl.ovf[6 * ip + m];
-        T[m] = wave_sum(v[3 + m]) + tl.ovf[6 * ip + 3 + m];
-      }
-    } else {
-      for (int m = 0; m < 3; ++m) {
-        F[m] = Fh[3 * ip + m];
-        T[m] = Th[3 * ip + m];
-      }
-    }
-    // contact force and torque: the particle's slots summed in the order
-    // of the partner id (lane k holds slot k; partners are distinct)
-    double Fcp[3] = {0.0, 0.0, 0.0}, Tcp[3] = {0.0, 0.0, 0.0};
-    {
-      int nc = tl.ccount[ip];
-      // (read by this wavefront alone: empty again for the next treatment)
-      if (nc && lane == 0) tl.ccount[ip] = 0;
-      nc = nc < MAXC ? nc : MAXC;
-      const size_t e0 = (size_t)ip * MAXC;
-      // every slot's values are loaded at once (lane k: slot k) and then
-      // read from registers in rank order
-      const int key = lane < nc ? tl.ckey[e0 + lane] : 0x7fffffff;
-      double cv[6];
-      for (int m = 0; m < 6; ++m) cv[m] = lane < nc ? tl.cval[6 * (e0 + lane) + m] : 0.0;
-      int rank = 0;
-      for (int j = 0; j < nc; ++j) rank += __builtin_amdgcn_readlane(key, j) < key ? 1 : 0;
-      for (int r = 0; r < nc; ++r) {
-        const int j = __ffsll((long long)__ballot(lane < nc && rank == r)) - 1;
-        for (int m = 0; m < 3; ++m) {
-          Fcp[m] += readlane_f64(cv[m], j);
-          Tcp[m] += readlane_f64(cv[3 + m], j);
-        }
-      }
-    }
-    // 2. Newton-Euler, symplectic Euler over the sub-step dt (eqs. (2)-(3));
-    // gravity minus buoyancy (rho_p - rho_f) V g with rho_f = 1 (Sec. 5.1).
-    const double V = P.vol[ip], m = P.mass[ip], I = P.inert[ip];
-    const double s = P.dens[ip];
-    const double dt = ph.dt_sub;
-    double Tt[3];
-    for (int k = 0; k < 3; ++k) {
-      const double Fg = (s - 1.0) * V * ph.gravity[k];
-      const double Ft = F[k] + Fcp[k] + Fg;
-      Tt[k] = T[k] + Tcp[k];
-      U[k] += Ft / m * dt;
-      X[k] += U[k] * dt;
-      if (per[k]) {
-        if (X[k] >= L[k]) X[k] -= L[k];
-        else if (X[k] < 0.0) X[k] += L[k];
-      }
-    }
-    if (P.shape[ip] >= POLY0) {
-      // eq. (3) with the world-frame tensor at the current orientation:
-      // w += R I_b^-1 R^T T dt
-      double Rc[9], tb[3], wb[3];
-      quat_to_rot(q, Rc);
-      const double* Ii = P.Iinv + 9 * ip;
-      for (int k = 0; k < 3; ++k) tb[k] = (Rc[0 + k] * Tt[0] + Rc[3 + k] * Tt[1]) + Rc[6 + k] * Tt[2];
-      for (int k = 0; k < 3; ++k) wb[k] = (Ii[3 * k] * tb[0] + Ii[3 * k + 1] * tb[1]) + Ii[3 * k + 2] * tb[2];
-      for (int k = 0; k < 3; ++k)
-        W[k] += ((Rc[3 * k] * wb[0] + Rc[3 * k + 1] * wb[1]) + Rc[3 * k + 2] * wb[2]) * dt;
-    } else {
-      for (int k = 0; k < 3; ++k) W[k] += Tt[k] / I * dt;
-    }
-    // orientation: exact rotation through |w| dt about w, q <- dq (x) q
-    const double th = sqrt(W[0] * W[0] + W[1] * W[1] + W[2] * W[2]) * dt;
-    if (th > 0.0) {
-      const double c = cos(0.5 * th), sn = sin(0.5 * th) / th * dt;
-      const double d0 = c, d1 = sn * W[0], d2 = sn * W[1], d3 = sn * W[2];
-      double r[4];
-      r[0] = d0 * q[0] - (d1 * q[1] + d2 * q[2] + d3 * q[3]);
-      r[1] = d0 * q[1] + q[0] * d1 + (d2 * q[3] - d3 * q[2]);
-      r[2] = d0 * q[2] + q[0] * d2 + (d3 * q[1] - d1 * q[3]);
-      r[3] = d0 * q[3] + q[0] * d3 + (d1 * q[2] - d2 * q[1]);
-      const double nn = sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2] + r[3] * r[3]);
-      for (int k = 0; k < 4; ++k) q[k] = r[k] / nn;
-    }
-    if (lane == 0) {
-      for (int k = 0; k < 3; ++k) {
-        Fh[3 * ip + k] = F[k];
-        Th[3 * ip + k] = T[k];
-        Fc[3 * ip + k] = Fcp[k];
-        Tc[3 * ip + k] = Tcp[k];
-      }
-      if (move == 1)
-        for (int k = 0; k < 6; ++k) tl.ovf[6 * ip + k] = 0.0;
-    }
-  }
-  quat_to_rot(q, R);
-  if (lane == 0) {
-    for (int k = 0; k < 3; ++k) {
-      P.X[3 * ip + k] = X[k];
-      P.U[3 * ip + k] = U[k];
-      P.W[3 * ip + k] = W[k];
-    }
-    for (int k = 0; k < 4; ++k) P.q[4 * ip + k] = q[k];
-    for (int k = 0; k < 9; ++k) P.R[9 * ip + k] = R[k];
-    float* rec = P.XR32 + SREC * ip;
-    for (int k = 0; k < 3; ++k) rec[k] = (float)X[k];
-    for (int k = 0; k < 9; ++k) rec[3 + k] = (float)R[k];
-    // the detection screen's thresholds with this particle's FP32 error
-    // bound: 1e-3 + 1e-5 (|r|_1 + size) at |r|_1 = sqrt 3 (R_c + 2), the
-    // largest for a node within reach of either threshold (R_c the
-    // circumradius)
-    const int sh = P.shape[ip];
-    const float fs = (float)P.size[ip];
-    const float rc = sh >= POLY0 ? (float)P.poly[sh - POLY0].rc * fs
-                                 : (sh == 1 ? 0.8660254f * fs : fs);
-    const float tol = 1e-3f + 1e-5f * (1.7320508f * (rc + 2.0f) + fs);
-    const float ot = (float)(0.5 * ph.eps), dt = (float)(DETECT + ph.delta_c);
-    rec[12] = screen_sq(sh, fs, ot + tol);
-    rec[13] = screen_sq(sh, fs, ot - tol);
-    rec[14] = screen_sq(sh, fs, dt + tol);
-    rec[15] = screen_sq(sh, fs, dt - tol);
-    rec[16] = fmaxf(ot, dt) + tol;
-    rec[17] = fs;
-    rec[18] = __int_as_float(sh);
-    rec[19] = fminf(ot, dt) - tol;   // below both (the ellipsoid screen's bound)
-    // the lattice pass's kinematic record: centre split into an integer part
-    // and its fraction (exact in FP64, the fraction then rounded to FP32)
-    float* lr = P.LR32 + LREC * ip;
-    for (int k = 0; k < 3; ++k) {
-      const double fl = floor(X[k]);
-      lr[k] = __int_as_float((int)fl);
-      lr[3 + k] = (float)(X[k] - fl);
-      lr[6 + k] = (float)U[k];
-      lr[9 + k] = (float)W[k];
-    }
-    for (int k = 0; k < 9; ++k) lr[12 + k] = (float)R[k];
-    lr[21] = fs;
-    lr[22] = __int_as_float(sh);
-    for (int k = 23; k < LREC; ++k) lr[k] = 0.0f;
-  }
-
-  // 3. Reach box: axis-aligned half extent of the body plus the largest
-  // distance at which a node can be owned by it (eps/2) or flagged by the
-  // rough detection (sqrt(0.75) + enlargement).
-  const double margin = fmax(0.5 * ph.eps, DETECT + ph.delta_c) + 0.25;
   const int shape = P.shape[ip];
   const double size = P.size[ip];
   const int n3[3] = {g.nx, g.ny, g.nz};
-  double ext[3];
-  // lattice blocks list the particles owning a node within one node of the
-  // block (the lattice pass pushes momentum-exchange terms to the owners of
-  // each node's neighbours): half extent + eps/2 + 1 node
-  const double margin_l = fmax(margin, 0.5 * ph.eps + 1.25);
-  double extl[3];
-  for (int k = 0; k < 3; ++k) {
-    const double e = half_extent(shape, size, R, k, P.poly);
-    ext[k] = e + margin;
-    extl[k] = e + margin_l;
+  __shared__ double sums[PW][6];               // hydrodynamic sums per wavefront
+  __shared__ double moved[18];                 // X, R, ext, extl of the moved particle
+
+  if (move == 1) {
+    // 1. F_p = sum of the per-tile partials (eqs. (17)-(18)); later
+    // sub-steps of the step keep the force of the first
+    const int ne = tl.nent[ip];
+    double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int k = threadIdx.x; k < ne; k += PT) {
+      const double* pp = tl.part + ((size_t)ip * g.maxent + k) * 6;
+      for (int m = 0; m < 6; ++m) v[m] += pp[m];
+    }
+    for (int m = 0; m < 6; ++m) v[m] = wave_sum(v[m]);
+    if (lane == 0)
+      for (int m = 0; m < 6; ++m) sums[wave][m] = v[m];
+    __syncthreads();
   }
+  if (wave == 0) {
+    double X[3], U[3], W[3], q[4], R[9];
+    for (int k = 0; k < 3; ++k) {
+      X[k] = P.X[3 * ip + k];
+      U[k] = P.U[3 * ip + k];
+      W[k] = P.W[3 * ip + k];
+    }
+    for (int k = 0; k < 4; ++k) q[k] = P.q[4 * ip + k];
+
+    if (move) {
+      double F[3], T[3];
+      if (move == 1) {
+        double v[6];
+        for (int m = 0; m < 6; ++m) {
+          v[m] = sums[0][m];
+          for (int w = 1; w < PW; ++w) v[m] += sums[w][m];
+          v[m] += tl.ovf[6 * ip + m];
+        }
+        for (int m = 0; m < 3; ++m) {
+          F[m] = v[m];
+          T[m] = v[3 + m];
+        }
+      } else {
+        for (int m = 0; m < 3; ++m) {
+          F[m] = Fh[3 * ip + m];
+          T[m] = Th[3 * ip + m];
+        }
+      }
+      // contact force and torque: the particle's slots summed in the order
+      // of the partner id (lane k holds slot k; partners are distinct)
+      double Fcp[3] = {0.0, 0.0, 0.0}, Tcp[3] = {0.0, 0.0, 0.0};
+      {
+        int nc = tl.ccount[ip];
+        // (read by this wavefront alone: empty again for the next treatment)
+        if (nc && lane == 0) tl.ccount[ip] = 0;
+        nc = nc < MAXC ? nc : MAXC;
+        const size_t e0 = (size_t)ip * MAXC;
+        // every slot's values are loaded at once (lane k: slot k) and then
+        // read from registers in rank order
+        const int key = lane < nc ? tl.ckey[e0 + lane] : 0x7fffffff;
+        double cv[6];
+        for (int m = 0; m < 6; ++m) cv[m] = lane < nc ? tl.cval[6 * (e0 + lane) + m] : 0.0;
+        int rank = 0;
+        for (int j = 0; j < nc; ++j) rank += __builtin_amdgcn_readlane(key, j) < key ? 1 : 0;
+        for (int r = 0; r < nc; ++r) {
+          const int j = __ffsll((long long)__ballot(lane < nc && rank == r)) - 1;
+          for (int m = 0; m < 3; ++m) {
+            Fcp[m] += readlane_f64(cv[m], j);
+            Tcp[m] += readlane_f64(cv[3 + m], j);
+          }
+        }
+      }
+      // 2. Newton-Euler, symplectic Euler over the sub-step dt (eqs. (2)-(3));
+      // gravity minus buoyancy (rho_p - rho_f) V g with rho_f = 1 (Sec. 5.1).
+      const double V = P.vol[ip], m = P.mass[ip], I = P.inert[ip];
+      const double s = P.dens[ip];
+      const double dt = ph.dt_sub;
+      double Tt[3];
+      for (int k = 0; k < 3; ++k) {
+        const double Fg = (s - 1.0) * V * ph.gravity[k];
+        const double Ft = F[k] + Fcp[k] + Fg;
+        Tt[k] = T[k] + Tcp[k];
+        U[k] += Ft / m * dt;
+        X[k] += U[k] * dt;
+        if (per[k]) {
+          if (X[k] >= L[k]) X[k] -= L[k];
+          else if (X[k] < 0.0) X[k] += L[k];
+        }
+      }
+      if (P.shape[ip] >= POLY0) {
+        // eq. (3) with the world-frame tensor at the current orientation:
+        // w += R I_b^-1 R^T T dt
+        double Rc[9], tb[3], wb[3];
+        quat_to_rot(q, Rc);
+        const double* Ii = P.Iinv + 9 * ip;
+        for (int k = 0; k < 3; ++k) tb[k] = (Rc[0 + k] * Tt[0] + Rc[3 + k] * Tt[1]) + Rc[6 + k] * Tt[2];
+        for (int k = 0; k < 3; ++k) wb[k] = (Ii[3 * k] * tb[0] + Ii[3 * k + 1] * tb[1]) + Ii[3 * k + 2] * tb[2];
+        for (int k = 0; k < 3; ++k)
+          W[k] += ((Rc[3 * k] * wb[0] + Rc[3 * k + 1] * wb[1]) + Rc[3 * k + 2] * wb[2]) * dt;
+      } else {
+        for (int k = 0; k < 3; ++k) W[k] += Tt[k] / I * dt;
+      }
+      // orientation: exact rotation through |w| dt about w, q <- dq (x) q
+      const double th = sqrt(W[0] * W[0] + W[1] * W[1] + W[2] * W[2]) * dt;
+      if (th > 0.0) {
+        const double c = cos(0.5 * th), sn = sin(0.5 * th) / th * dt;
+        const double d0 = c, d1 = sn * W[0], d2 = sn * W[1], d3 = sn * W[2];
+        double r[4];
+        r[0] = d0 * q[0] - (d1 * q[1] + d2 * q[2] + d3 * q[3]);
+        r[1] = d0 * q[1] + q[0] * d1 + (d2 * q[3] - d3 * q[2]);
+        r[2] = d0 * q[2] + q[0] * d2 + (d3 * q[1] - d1 * q[3]);
+        r[3] = d0 * q[3] + q[0] * d3 + (d1 * q[2] - d2 * q[1]);
+        const double nn = sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2] + r[3] * r[3]);
+        for (int k = 0; k < 4; ++k) q[k] = r[k] / nn;
+      }
+      if (lane == 0) {
+        for (int k = 0; k < 3; ++k) {
+          Fh[3 * ip + k] = F[k];
+          Th[3 * ip + k] = T[k];
+          Fc[3 * ip + k] = Fcp[k];
+          Tc[3 * ip + k] = Tcp[k];
+        }
+        if (move == 1)
+          for (int k = 0; k < 6; ++k) tl.ovf[6 * ip + k] = 0.0;
+      }
+    }
+    quat_to_rot(q, R);
+    if (lane == 0) {
+      for (int k = 0; k < 3; ++k) {
+        P.X[3 * ip + k] = X[k];
+        P.U[3 * ip + k] = U[k];
+        P.W[3 * ip + k] = W[k];
+      }
+      for (int k = 0; k < 4; ++k) P.q[4 * ip + k] = q[k];
+      for (int k = 0; k < 9; ++k) P.R[9 * ip + k] = R[k];
+      float* rec = P.XR32 + SREC * ip;
+      for (int k = 0; k < 3; ++k) rec[k] = (float)X[k];
+      for (int k = 0; k < 9; ++k) rec[3 + k] = (float)R[k];
+      // the detection screen's thresholds with this particle's FP32 error
+      // bound: 1e-3 + 1e-5 (|r|_1 + size) at |r|_1 = sqrt 3 (R_c + 2), the
+      // largest for a node within reach of either threshold (R_c the
+      // circumradius)
+      const int sh = P.shape[ip];
+      const float fs = (float)P.size[ip];
+      const float rc = sh >= POLY0 ? (float)P.poly[sh - POLY0].rc * fs
+                                   : (sh == 1 ? 0.8660254f * fs : fs);
+      const float tol = 1e-3f + 1e-5f * (1.7320508f * (rc + 2.0f) + fs);
+      const float ot = (float)(0.5 * ph.eps), dt = (float)(DETECT + ph.delta_c);
+      rec[12] = screen_sq(sh, fs, ot + tol);
+      rec[13] = screen_sq(sh, fs, ot - tol);
+      rec[14] = screen_sq(sh, fs, dt + tol);
+      rec[15] = screen_sq(sh, fs, dt - tol);
+      rec[16] = fmaxf(ot, dt) + tol;
+      rec[17] = fs;
+      rec[18] = __int_as_float(sh);
+      rec[19] = fminf(ot, dt) - tol;   // below both (the ellipsoid screen's bound)
+      // the lattice pass's kinematic record: centre split into an integer part
+      // and its fraction (exact in FP64, the fraction then rounded to FP32)
+      float* lr = P.LR32 + LREC * ip;
+      for (int k = 0; k < 3; ++k) {
+        const double fl = floor(X[k]);
+        lr[k] = __int_as_float((int)fl);
+        lr[3 + k] = (float)(X[k] - fl);
+        lr[6 + k] = (float)U[k];
+        lr[9 + k] = (float)W[k];
+      }
+      for (int k = 0; k < 9; ++k) lr[12 + k] = (float)R[k];
+      lr[21] = fs;
+      lr[22] = __int_as_float(sh);
+      for (int k = 23; k < LREC; ++k) lr[k] = 0.0f;
+    }
+
+    // Reach box: axis-aligned half extent of the body plus the largest
+    // distance at which a node can be owned by it (eps/2) or flagged by the
+    // rough detection (sqrt(0.75) + enlargement).
+    const double margin = fmax(0.5 * ph.eps, DETECT + ph.delta_c) + 0.25;
+    // lattice blocks list the particles owning a node within one node of the
+    // block (the lattice pass pushes momentum-exchange terms to the owners of
+    // each node's neighbours): half extent + eps/2 + 1 node
+    const double margin_l = fmax(margin, 0.5 * ph.eps + 1.25);
+    double e[3];
+    for (int k = 0; k < 3; ++k) e[k] = half_extent(shape, size, R, k, P.poly);
+    if (lane == 0) {
+      for (int k = 0; k < 3; ++k) {
+        moved[k] = X[k];
+        moved[12 + k] = e[k] + margin;
+        moved[15 + k] = e[k] + margin_l;
+      }
+      for (int k = 0; k < 9; ++k) moved[3 + k] = R[k];
+    }
+  }
+  __syncthreads();
+  double X[3], R[9], ext[3], extl[3];
+  for (int k = 0; k < 3; ++k) {
+    X[k] = moved[k];
+    ext[k] = moved[12 + k];
+    extl[k] = moved[15 + k];
+  }
+  for (int k = 0; k < 9; ++k) R[k] = moved[3 + k];
   // detection tiles
   {
     const int nt3[3] = {g.dtx, g.dty, g.dtz};
@@ -310,11 +350,11 @@ __global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
                          0.5 * sqrt((double)(DX - 1) * (DX - 1) + (DY - 1) * (DY - 1) +
                                     (DZ - 1) * (DZ - 1)) + 0.01;
     // UB tiles per lane and round, their slot atomics in flight together
-    for (int t0 = lane; t0 < total; t0 += UB * WAVE) {
+    for (int t0 = threadIdx.x; t0 < total; t0 += UB * PT) {
       long long tile[UB];
 #pragma unroll
       for (int u = 0; u < UB; ++u) {
-        const int t = t0 + u * WAVE;
+        const int t = t0 + u * PT;
         tile[u] = -1;
         if (t >= total) continue;
         const int ix = t % cxn, iy = (t / cxn) % cyn, iz = t / (cxn * cyn);
@@ -365,15 +405,15 @@ __global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
     const int cxn = sp[0].count(), cyn = sp[1].count(), czn = sp[2].count();
     int total = cxn * cyn * czn;
     if (total > g.maxent) {
-      if (lane == 0) atomicOr(&ctr->tile_overflow, 1);
+      if (threadIdx.x == 0) atomicOr(&ctr->tile_overflow, 1);
       total = g.maxent;
     }
-    if (lane == 0) tl.nent[ip] = total;
-    for (int t0 = lane; t0 < total; t0 += UB * WAVE) {
+    if (threadIdx.x == 0) tl.nent[ip] = total;
+    for (int t0 = threadIdx.x; t0 < total; t0 += UB * PT) {
       long long tile[UB];
 #pragma unroll
       for (int u = 0; u < UB; ++u) {
-        const int t = t0 + u * WAVE;
+        const int t = t0 + u * PT;
         tile[u] = -1;
         if (t >= total) continue;
         const int ix = t % cxn, iy = (t / cxn) % cyn, iz = t / (cxn * cyn);
@@ -385,7 +425,7 @@ __global__ __launch_bounds__(64) void k_particles(Particles P, Geom g, Phys ph,
 #pragma unroll
       for (int u = 0; u < UB; ++u) {
         if (tile[u] < 0) continue;
-        const int t = t0 + u * WAVE;
+        const int t = t0 + u * PT;
         if (slot[u] < g.tile_cap) {
           tl.llist[tile[u] * g.tile_cap + slot[u]] = ip;
           tl.lent[tile[u] * g.tile_cap + slot[u]] = t;
@@ -417,12 +457,12 @@ hipError_t launch_particles(Ctx& c, int move, bool bin_blocks, const PairTable* 
   PairTable none = {nullptr, nullptr, 0, nullptr, nullptr};
   const PairTable from = keep_from ? *keep_from : none;
   const PairTable to = keep_to ? *keep_to : none;
-  unsigned kb = (unsigned)((from.cap + WAVE - 1) / WAVE);
+  unsigned kb = (unsigned)((from.cap + PT - 1) / PT);
   if (kb > KEEP_BLOCKS) kb = KEEP_BLOCKS;
   const unsigned bb = balance ? 1 : 0;
   if (c.np + kb + bb == 0) return hipSuccess;
   const unsigned nlt = (unsigned)c.g.ltx * (unsigned)c.g.lty * (unsigned)c.g.ltz;
-  hipLaunchKernelGGL(k_particles, dim3(c.np + kb + bb), dim3(64), 0, c.stream, c.part, c.g,
+  hipLaunchKernelGGL(k_particles, dim3(c.np + kb + bb), dim3(PT), 0, c.stream, c.part, c.g,
                      c.ph, c.Fh, c.Th, c.Fc, c.Tc, move, bin_blocks ? 1 : 0, c.tl, c.counters,
                      from, to, (int)kb, c.bal_part ? c.bal_part + 4 * (size_t)nlt : nullptr);
   return hipGetLastError();
