@@ -1130,28 +1130,69 @@ __device__ inline double wave_sum6_scatter_f(const float* v) {
   return n;
 }
 
-// As wave_sum6_scatter_f with the first three levels (sums of eight lanes)
-// in FP32 and the last three in FP64: for per-node contributions that carry
-// FP32 rounding already, at about half the instructions of FP64 levels.
-__device__ inline double wave_sum6_scatter_f3(const float* v) {
+// The commit's form of the reduce-scatter, for a (force, torque) pair of
+// triples: the lanes of the upper half of a row end with the torque, so the
+// halves each lane keeps and gives away at the first level do not depend on
+// the particle and are chosen once per wavefront (halves); per particle 5
+// selects and adds at the first level are saved against wave_sum6_scatter.
+// Component k of the pair ends in the lanes that scatter_comp names k.  FP32
+// triples add their first three levels (eight lanes) in FP32 and the rest in
+// FP64.
+template <typename V>
+struct Halves {
+  V keep[3], give[3];
+};
+template <typename V>
+__device__ inline Halves<V> halves(const V* f, const V* t) {
+  const bool b3 = (threadIdx.x & 8) != 0;
+  Halves<V> h;
+  for (int k = 0; k < 3; ++k) {
+    h.keep[k] = b3 ? t[k] : f[k];
+    h.give[k] = b3 ? f[k] : t[k];
+  }
+  return h;
+}
+template <int CTRL>
+__device__ inline double dpp_v(double v) { return dpp_d<CTRL>(v); }
+template <int CTRL>
+__device__ inline float dpp_v(float v) { return dpp_f<CTRL>(v); }
+template <typename V>
+__device__ inline double wave_sum_halves(const V* keep, const V* give) {
   const int i = threadIdx.x & 15;
-  const bool b3 = (i & 8) != 0, b2 = (i & 4) != 0, b1 = (i & 2) != 0;
-  const float s0 = b3 ? v[0] : v[4], s1 = b3 ? v[1] : v[5];
-  const float s2 = b3 ? v[2] : 0.0f, s3 = b3 ? v[3] : 0.0f;
-  float k0 = b3 ? v[4] : v[0], k1 = b3 ? v[5] : v[1];
-  float k2 = b3 ? 0.0f : v[2], k3 = b3 ? 0.0f : v[3];
-  k0 += dpp_f<0x140>(s0);
-  k1 += dpp_f<0x140>(s1);
-  k2 += dpp_f<0x140>(s2);
-  k3 += dpp_f<0x140>(s3);
-  const float t0 = b2 ? k0 : k2, t1 = b2 ? k1 : k3;
-  float m0 = b2 ? k2 : k0, m1 = b2 ? k3 : k1;
-  m0 += dpp_f<0x141>(t0);
-  m1 += dpp_f<0x141>(t1);
-  const float t = b1 ? m0 : m1;
-  float nf = b1 ? m1 : m0;
-  nf += dpp_f<0x1b>(t);
-  double n = nf;
+  const bool b2 = (i & 4) != 0, b1 = (i & 2) != 0;
+  const V k0 = keep[0] + dpp_v<0x140>(give[0]);
+  const V k1 = keep[1] + dpp_v<0x140>(give[1]);
+  const V k2 = keep[2] + dpp_v<0x140>(give[2]);
+  const V t0 = b2 ? k0 : k2;
+  const V m0 = (b2 ? k2 : k0) + dpp_v<0x141>(t0);
+  const V m1 = k1 + dpp_v<0x141>(k1);
+  const V t1 = b1 ? m0 : m1;
+  double n = (double)((b1 ? m1 : m0) + dpp_v<0x1b>(t1));
+  n += dpp_d<0xb1>(n);
+  n += xor16_d(n);
+  n += xor32_d(n);
+  return n;
+}
+// component of the pair in lane l of wave_sum_halves (lanes 0, 2, 4, 8, 10
+// and 12 hold one each, 6 and 14 repeat)
+__device__ inline int scatter_comp(int l) {
+  return ((l & 8) ? 3 : 0) + ((l & 2) ? 1 : ((l & 4) ? 2 : 0));
+}
+__device__ inline bool scatter_holds(int l) { return l < 16 && (l & 1) == 0 && (l & 6) != 6; }
+
+// Reduce-scatter of four wavefront sums: value k ends in lane 4k.  FP32
+// values add their first level (two lanes) in FP32 and the rest in FP64.
+template <typename V>
+__device__ inline double wave_sum4_scatter(V a, V b, V c, V d) {
+  const int i = threadIdx.x & 15;
+  const bool b3 = (i & 8) != 0, b2 = (i & 4) != 0;
+  const V s0 = b3 ? a : c, s1 = b3 ? b : d;
+  const double k0 = (double)((b3 ? c : a) + dpp_v<0x140>(s0));
+  const double k1 = (double)((b3 ? d : b) + dpp_v<0x140>(s1));
+  const double t = b2 ? k0 : k1;
+  double n = b2 ? k1 : k0;
+  n += dpp_d<0x141>(t);
+  n += dpp_d<0x1b>(n);
   n += dpp_d<0xb1>(n);
   n += xor16_d(n);
   n += xor32_d(n);

@@ -221,14 +221,9 @@ __device__ void store_block(double (*red)[LCAP_MAX][6], const int* list,
 template <typename C>
 __device__ void block_sums4s(C a, C b, C c, C d, const BlockNode& nd, double* out) {
   __shared__ double rows[4][4];
-  const C v[6] = {a, b, c, d, (C)0, (C)0};
-  double sum;
-  if constexpr (sizeof(C) == 4)
-    sum = wave_sum6_scatter_f(v);
-  else
-    sum = wave_sum6_scatter(v);
+  const double sum = wave_sum4_scatter<C>(a, b, c, d);
   const int lane = threadIdx.x % WAVE;
-  if (lane < 8 && (lane & 1) == 0) rows[nd.wave][lane >> 1] = sum;
+  if (lane < 16 && (lane & 3) == 0) rows[nd.wave][lane >> 2] = sum;
   __syncthreads();
   if (threadIdx.x < 4) {
     const int k = threadIdx.x;
@@ -780,10 +775,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   }
   // one commit for A and B: each distinct particle of the wavefront in
   // turn, the lanes adding the entries that name it (FP64 wave sums into
-  // the block's LDS rows, which hold -sum)
+  // the block's LDS rows)
   // (pending entries as wavefront masks, the lane predicates taken from
   // them without per-lane bookkeeping; B only in wavefronts that have one)
   {
+    const Halves<C> ha = halves<C>(Ga, Ta), hb = halves<C>(Gb, Tb);
     uint64_t pa = __ballot(qa >= 0);
     uint64_t pb = multi ? __ballot(qb >= 0) : 0ull;
     while ((pa | pb) != 0) {
@@ -796,23 +792,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
       const uint64_t mb = pb & __ballot(qb == pick);
       const bool tb = __builtin_amdgcn_inverse_ballot_w64(mb);
       pb &= ~mb;
-      C vv[6];
+      C keep[3], give[3];
       for (int k = 0; k < 3; ++k) {
-        vv[k] = ta ? -Ga[k] : (tb ? -Gb[k] : (C)0);
-        vv[3 + k] = ta ? -Ta[k] : (tb ? -Tb[k] : (C)0);
+        keep[k] = ta ? ha.keep[k] : (tb ? hb.keep[k] : (C)0);
+        give[k] = ta ? ha.give[k] : (tb ? hb.give[k] : (C)0);
       }
-      double sum;
-      if constexpr (sizeof(C) == 4)
-        sum = wave_sum6_scatter_f3(vv);
-      else
-        sum = wave_sum6_scatter(vv);
+      const double sum = wave_sum_halves<C>(keep, give);
       const uint64_t hit = __ballot(lid == pick);
-      if (lane < 12 && (lane & 1) == 0) {
-        const int k = lane >> 1;
+      if (scatter_holds(lane)) {
+        const int k = scatter_comp(lane);
         if (hit) {
-          red[nd.wave][__ffsll((long long)hit) - 1][k] -= sum;
+          red[nd.wave][__ffsll((long long)hit) - 1][k] += sum;
         } else {
-          atomic_add_f64(&tl.ovf[6 * pick + k], -sum);
+          atomic_add_f64(&tl.ovf[6 * pick + k], sum);
         }
       }
     }
