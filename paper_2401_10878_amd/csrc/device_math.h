@@ -1099,6 +1099,13 @@ __device__ inline double wave_sum6_scatter(const double* v) {
   return n;
 }
 
+// A 32-bit value from the next lane of the wavefront (0x130) or from the one
+// before (0x138); the lane at the end takes `end`.
+template <int CTRL>
+__device__ inline int dpp_shift(int end, int v) {
+  return __builtin_amdgcn_update_dpp(end, v, CTRL, 0xf, 0xf, false);
+}
+
 // As wave_sum6_scatter for FP32 inputs: the first level (pairs of lanes)
 // adds in FP32, one rounding of a two-lane sum, and the rest in FP64.
 template <int CTRL>

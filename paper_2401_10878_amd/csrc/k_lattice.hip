@@ -140,6 +140,7 @@ __device__ inline double full_f(typename Store<S>::C h, int i) {
 static_assert(LX == WAVE && LY * LZ == 4 && (LY == 1 || LZ == 1), "block shape");
 struct BlockNode {
   long long block;
+  int bx;                // block index along x
   int x, y, z, wave;
   bool valid;
 };
@@ -151,7 +152,7 @@ __device__ inline BlockNode block_node(const Geom& g) {
   r.block = lb;
   const unsigned yz = fdiv(lb, g.fltx);
   const unsigned bz = fdiv(yz, g.flty);
-  const int bx = (int)(lb - yz * (unsigned)g.ltx);
+  const int bx = r.bx = (int)(lb - yz * (unsigned)g.ltx);
   const int by = (int)(yz - bz * (unsigned)g.lty);
   r.wave = (int)((unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x) / WAVE);
   r.x = bx * LX + (int)(threadIdx.x % WAVE);
@@ -445,25 +446,11 @@ __device__ inline void kinematics(const Particles& P, int q, int x, int y, int z
   }
 }
 
-// Commit of one round of per-lane (force G, torque T) contributions to the
-// block's LDS rows (commit_group adds -sum, so the values go in negated and
-// widened to FP64).
-template <typename C>
-__device__ inline void commit_round(int q, const C* G, const C* T, int lid,
-                                    double (*row)[6], double* ovf) {
-  double s[3], t[3];
-  for (int k = 0; k < 3; ++k) {
-    s[k] = -(double)G[k];
-    t[k] = -(double)T[k];
-  }
-  commit_group(q, s, t, lid, row, ovf);
-}
-
 // Register budget without spills: FP64 at most 128 VGPRs (four wavefronts
 // per SIMD), FP32 and binary16 at most 72 (seven: the pass is faster at
 // seven wavefronts than at six or five), 80 with both the polyhedron
-// distance and the balance sums.  POLY: built
-// with the polyhedron signed distance (scenes without polyhedra run the
+// distance and the balance sums, or, in FP32, without walls (72 spilled).
+// POLY: built with the polyhedron signed distance (scenes without polyhedra run the
 // form without it, which needs fewer registers).  BAL: with the block sums
 // and device acceleration of the zero-net-flux balance force.  WALL: z
 // bounded by walls (half-way bounce-back).
@@ -485,7 +472,7 @@ __device__ inline void commit_round(int q, const C* G, const C* T, int lid,
 // node or a neighbour of one, skip it.
 template <typename S, int POLICY, bool POLY, bool BAL, bool WALL, bool ELL = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
-    sizeof(S) == 8 ? 4 : (ELL ? 5 : (POLY && BAL ? 6 : 7)), 8))) void k_lattice(const S* __restrict__ src,
+    sizeof(S) == 8 ? 4 : (ELL ? 5 : (POLY && (BAL || (sizeof(S) == 4 && !WALL)) ? 6 : 7)), 8))) void k_lattice(const S* __restrict__ src,
                                                  S* __restrict__ dst,
                                                  const int* __restrict__ owner,
                                                  Particles P, Geom g, Phys ph,
@@ -504,8 +491,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   const int n = (int)g.ncell;
   // Every lane loads: a lane outside the lattice reads the nearest node
   // (clamped coordinates) and then stores nothing and adds to no sum.
-  const Nbr nb = neighbours(g, x < g.nx ? x : g.nx - 1, y < g.ny ? y : g.ny - 1,
-                            z < g.nz ? z : g.nz - 1);
+  // (the lane after the end of a row: node 0, see the neighbours' owners)
+  const Nbr nb = neighbours(g, x < g.nx ? x : (x == g.nx ? 0 : g.nx - 1),
+                            y < g.ny ? y : g.ny - 1, z < g.nz ? z : g.nz - 1);
   // walls exist only on a bounded z axis (WALL): elsewhere the wall terms
   // drop out at compile time
   const bool wallm = WALL && nb.wall_m, wallp = WALL && nb.wall_p;
@@ -524,7 +512,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
                           (unsigned)nb.xs[2] << SB};
   const unsigned xw[3] = {(unsigned)nb.xs[0] << 2, (unsigned)nb.xs[1] << 2,
                           (unsigned)nb.xs[2] << 2};
-  const int o = valid ? owner_at(owner + rowpl(0, 0), xw[1]) : -1;
+  // (a lane outside the lattice works on the node that it reads)
+  const int o = owner_at(owner + rowpl(0, 0), xw[1]);
 
   C f[Q];
   {
@@ -673,7 +662,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   // ---- momentum exchange of the next step, pushed link by link ----------
   const int* list = tl.llist + nd.block * g.tile_cap;
   const int* ent = tl.lent + nd.block * g.tile_cap;
-  const int lid = lane < cnt ? list[lane] : -1;   // candidate list, one per lane
+  // candidate list, one per lane (binary16, which is short of registers here,
+  // loads it when it is needed: 386 -> 381 us; FP32 early: 613 -> 606 with boxes)
+  constexpr bool LATE_LIST = sizeof(S) == 2;
+  int lid = !LATE_LIST && lane < cnt ? list[lane] : -1;
   for (int c = lane; c < cnt; c += WAVE)
     for (int k = 0; k < 6; ++k) red[nd.wave][c][k] = 0.0;
   // Owners of the 18 neighbours (-2: beyond a wall) and the lane's entries:
@@ -687,10 +679,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   nbo[0] = -1;
   int mx = -1;
   unsigned mn = ~0u;        // smallest id owning a neighbour (negative: none)
+  // Rows are loaded at the lanes' own x; their neighbours along x come from
+  // the next lanes, and for the first and the last lane by scalar loads of
+  // the nodes beyond, whose addresses are uniform (a row that ends before the
+  // last lane: the lane after the end holds node 0).  Each vector load cost
+  // about 2 us of the pass at 256^3; 8 are left of 18: FP32 with cubes 541 ->
+  // 531 us, with boxes 628 -> 606, FP64 1040 -> 1018, binary16 396 -> 382;
+  // 128^3 between walls 74.2 -> 70.6.
+  // (FP64 with ellipsoids has no registers left for it and loads them all.)
+  constexpr bool SHIFT = !(sizeof(S) == 8 && ELL);
+  typedef const __attribute__((address_space(4))) char* OwnerBytes;
+  auto beside = [&](int i, unsigned xb) {
+    const OwnerBytes p = (OwnerBytes)(uintptr_t)owner;
+    return *(const __attribute__((address_space(4))) int*)(
+        p + (((unsigned)rowpl(cy(i), cz(i)) << 2) + xb));
+  };
+  const int x0 = nd.bx * LX;
+  const unsigned xl = (unsigned)(x0 == 0 ? g.nx - 1 : x0 - 1) << 2;
+  const unsigned xr = (unsigned)(x0 + LX >= g.nx ? 0 : x0 + LX) << 2;
+  int cen[Q];               // owner at the lane's x in the row of direction i
+  cen[1] = cen[2] = o;
+#pragma unroll
+  for (int i = 3; i < Q; ++i)
+    if (cx(i) == 0) cen[i] = ld_owner_buf(owner + rowpl(cy(i), cz(i)), xw[1]);
+#pragma unroll
+  for (int i = 3; i < Q; ++i)
+    if (cx(i) != 0) cen[i] = cen[cy(i) > 0 ? 3 : (cy(i) < 0 ? 4 : (cz(i) > 0 ? 5 : 6))];
 #pragma unroll
   for (int i = 1; i < Q; ++i) {
     // (a link beyond a wall reads its clamped neighbour, then replaced)
-    const int v = ld_owner_buf(owner + rowpl(cy(i), cz(i)), xw[1 + cx(i)]);
+    int v = cen[i];
+    if (!SHIFT) {
+      if (cx(i)) v = ld_owner_buf(owner + rowpl(cy(i), cz(i)), xw[1 + cx(i)]);
+    } else if (cx(i) > 0) {
+      v = dpp_shift<0x130>(beside(i, xr), v);
+    } else if (cx(i) < 0) {
+      v = dpp_shift<0x138>(beside(i, xl), v);
+    }
     nbo[i] = beyond(cz(i)) ? -2 : v;
     mx = max(mx, nbo[i]);
     mn = min(mn, (unsigned)nbo[i]);
@@ -773,6 +798,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     kinematics<C>(P, qb, x, y, z, g, rb, ub, wb);
     link_force<C>(Lb, rb, ub, wb, Gb, Tb);
   }
+  if (LATE_LIST) lid = lane < cnt ? list[lane] : -1;
   // one commit for A and B: each distinct particle of the wavefront in
   // turn, the lanes adding the entries that name it (FP64 wave sums into
   // the block's LDS rows)
