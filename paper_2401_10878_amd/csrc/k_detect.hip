@@ -57,8 +57,13 @@ __device__ void commit_pair(PairTable t, Counters* ctr, int a, int b,
   }
 }
 
-template <bool POLY, bool ELL = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? (ELL ? 4 : 5) : 8, 8))) void k_detect(Particles P, Geom g, Phys ph,
+// POLY: with polyhedron and ellipsoid types.  Bound by vector instructions and,
+// with POLY, by the latency of the types' tables: at 72 registers (seven
+// wavefronts per SIMD) against 82 to 87 (five) 256^3 with 1500 boxes 260 ->
+// 222 us, with 734 ellipsoids 215 -> 198.  (A form without the ellipsoids'
+// branch spills at 72; with the spill 215 us for the boxes, at 82 260.)
+template <bool POLY>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? 7 : 8, 8))) void k_detect(Particles P, Geom g, Phys ph,
                                                 Tiles tl, int* __restrict__ owner,
                                                 PairTable tab, Counters* ctr) {
   const int lane = threadIdx.x % WAVE;
@@ -153,8 +158,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? (ELL
     const float f1 = wrap_f(fyf - xr[1], Lyf, g.inv_l[1]);
     const float f2 = wrap_f(fzf - xr[2], Lzf, g.inv_l[2]);
     // a polyhedron's plane lower bound beyond both thresholds ends its search
-    const float d2 = screen32<POLY, ELL>(shape, xr[17], xr + 3, f0, f1, f2, P.poly, xr[16],
-                                         ELL ? src[19] : -1e30f);
+    const float d2 = screen32<POLY, POLY>(shape, xr[17], xr + 3, f0, f1, f2, P.poly, xr[16],
+                                         POLY ? src[19] : -1e30f);
     const bool may_own = d2 < xr[12];
     const uint64_t m_own = vm & __ballot(may_own);
     twice |= once & m_own;
@@ -200,7 +205,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? (ELL
         const double r0 = minimg(fx - X0, Lx, true);
         const double r1 = minimg(fy - X1, Ly, true);
         const double r2 = minimg(fz - X2, Lz, perz);
-        const double d = sdf_exact<ELL>(P.shape[p], P.size[p], R, r0, r1, r2, POLY ? P.poly : nullptr);
+        const double d = sdf_exact<POLY>(P.shape[p], P.size[p], R, r0, r1, r2, POLY ? P.poly : nullptr);
         if (own_open && d < own_t && (d < bd || (d == bd && p < ep))) {
           bd = d;
           ep = p;
@@ -266,10 +271,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? (ELL
 hipError_t launch_detect(Ctx& c, PairTable to) {
   const long long ntiles = (long long)c.g.dtx * c.g.dty * c.g.dtz;
   const dim3 nb((unsigned)((ntiles + 3) / 4)), nt(256);
-  if (c.has_ellipsoid)
-    hipLaunchKernelGGL((k_detect<true, true>), nb, nt, 0, c.stream, c.part, c.g, c.ph, c.tl,
-                       c.owner, to, c.counters);
-  else if (c.has_poly)
+  if (c.has_poly)
     hipLaunchKernelGGL(k_detect<true>, nb, nt, 0, c.stream, c.part, c.g, c.ph, c.tl, c.owner, to,
                        c.counters);
   else
