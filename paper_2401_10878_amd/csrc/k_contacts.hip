@@ -145,16 +145,19 @@ __device__ void add_contact(Tiles tl, Counters* ctr, int p, int other,
 // One workgroup of four wavefronts per record: wavefronts 0 and 1 evaluate
 // the first member's distance, 2 and 3 the second's, 128 samples at a time,
 // and exchange them through LDS.  The treatment of a record is a chain of
-// dependent evaluations (six faces, then the integration samples of a lane)
-// and not a matter of throughput: two bodies at once and 128 samples a round
-// leave 10 single evaluations in the chain at n_c = 8 where one wavefront
-// per record had 28, and the rolled face loop (run-time axis, coordinates by
-// selects) keeps one copy of the distance in the instruction cache instead
-// of twelve.  Every wavefront forms the same minima and sums, so the box
+// dependent evaluations (three axes, then the integration samples of a lane)
+// and not a matter of throughput: two bodies at once, both faces of an axis
+// at once and 128 samples a round leave 7 single evaluations in the chain at
+// n_c = 8 where one wavefront per record had 28, and the rolled loop over the
+// axes (coordinates by selects) keeps one copy of the distance in the
+// instruction cache instead of twelve.  One face at a time, both faces, us:
+// 256^3 with 1834 cubes 25.5, 22.7; 1500 boxes 74.7, 59.8; 45 x 37 x 29 with 12
+// bodies 13.5, 12.3.  (Eight wavefronts per record: 45.3, 60.1, 12.2.)  Every wavefront forms the same minima and sums, so the box
 // corrections and exits are uniform over the workgroup; wavefront 0 forms
 // the forces.
 constexpr int TREAT_WAVES = 4;
-constexpr int TREAT_ROUND = 128;   // samples evaluated between two barriers
+constexpr int TREAT_HALF = TREAT_WAVES / 2;    // wavefronts per member
+constexpr int TREAT_ROUND = TREAT_HALF * WAVE;   // samples evaluated between two barriers
 struct TreatShared {
   double d[2][2][TREAT_ROUND];     // [round parity][member][sample]
   double red[TREAT_WAVES][8];      // sums of the integration per wavefront
@@ -166,8 +169,8 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
                            int slot, TreatShared& sh, int& round) {
   const int lane = threadIdx.x % WAVE;
   const int wave = (int)((unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x) / WAVE);
-  const int member = wave >> 1;                   // 0: particle a, 1: particle or wall b
-  const int at = (wave & 1) * WAVE + lane;        // sample of a round
+  const int member = wave / TREAT_HALF;           // 0: particle a, 1: particle or wall b
+  const int at = (wave % TREAT_HALF) * WAVE + lane;   // sample of a round
   PairRec* rec = &t.rec[slot];
   const int a = __builtin_amdgcn_readfirstlane(rec->a);
   const int b = __builtin_amdgcn_readfirstlane(rec->b);
@@ -223,22 +226,24 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
   // ---- box correction, one pass -----------------------------------------
   bool ok = true;
   int nfaces = 0;   // faces sampled (the box can empty on the way)
+  const int nn = nc * nc;
 #pragma unroll 1
-  for (int face = 0; face < 6; ++face) {
+  for (int k = 0; k < 3; ++k) {
     ok = ok && hi[0] > lo[0] && hi[1] > lo[1] && hi[2] > lo[2];
     if (!ok) break;
     ++nfaces;
-    const int k = face >> 1;
-    const bool plus = face & 1;
+    // the two faces of an axis together: the correction of the lower moves
+    // no sample of the upper (samples 0 .. nn-1 and nn .. 2 nn-1)
     const double h0 = (hi[0] - lo[0]) / (double)nc, h1 = (hi[1] - lo[1]) / (double)nc,
                  h2 = (hi[2] - lo[2]) / (double)nc;
-    double smin = DBL_MAX;
+    double smin = DBL_MAX, smax = DBL_MAX;        // of the lower, of the upper face
 #pragma unroll 1
-    for (int base = 0; base < nc * nc; base += TREAT_ROUND) {
+    for (int base = 0; base < 2 * nn; base += TREAT_ROUND) {
       double (*d)[TREAT_ROUND] = sh.d[round & 1];
       ++round;
-      const int idx = base + at;
-      if (idx < nc * nc) {
+      if (base + at < 2 * nn) {
+        const bool plus = base + at >= nn;
+        const int idx = base + at - (plus ? nn : 0);
         // sample (j, l) of the face: j along the first of its two axes
         const int j = (int)fdiv((unsigned)idx, fnc), l = idx - j * nc;
         const double sj = (double)j + 0.5, sl = (double)l + 0.5;
@@ -249,15 +254,23 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
         d[member][at] = member_sdf<ELL>(M, id, poly, delta, L[2], y, nullptr);
       }
       __syncthreads();
-      if (base + lane < nc * nc) smin = fmin(smin, fmax(d[0][lane], d[1][lane]));
-      if (base + WAVE + lane < nc * nc)
-        smin = fmin(smin, fmax(d[0][WAVE + lane], d[1][WAVE + lane]));
+#pragma unroll
+      for (int u = 0; u < TREAT_ROUND; u += WAVE) {
+        const int i = base + u + lane;
+        if (i < 2 * nn) {
+          const double m = fmax(d[0][u + lane], d[1][u + lane]);
+          if (i < nn) smin = fmin(smin, m);
+          else smax = fmin(smax, m);
+        }
+      }
     }
     smin = wave_min(smin);
-    for (int m = 0; m < 3; ++m) {
-      hi[m] = (k == m && plus) ? hi[m] - smin : hi[m];
-      lo[m] = (k == m && !plus) ? lo[m] + smin : lo[m];
-    }
+    smax = wave_min(smax);
+    for (int m = 0; m < 3; ++m) lo[m] = k == m ? lo[m] + smin : lo[m];
+    ok = ok && hi[0] > lo[0] && hi[1] > lo[1] && hi[2] > lo[2];
+    if (!ok) break;
+    ++nfaces;
+    for (int m = 0; m < 3; ++m) hi[m] = k == m ? hi[m] - smax : hi[m];
   }
   ok = ok && hi[0] > lo[0] && hi[1] > lo[1] && hi[2] > lo[2];
   // midpoint samples of this record (each evaluates both members)
@@ -299,7 +312,7 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
         for (int m = 0; m < 3; ++m) sy[m] += y[m];
       }
     }
-    // the two wavefronts of each member hold the same samples: counts,
+    // the wavefronts of both members hold the same samples: counts,
     // positions and depths from the first member's, gradients from all
     const double v[8] = {(double)wave_sum_i(n_in), wave_max(dmax), wave_sum(sy[0]),
                          wave_sum(sy[1]),          wave_sum(sy[2]), wave_sum(gs[0]),
@@ -307,11 +320,17 @@ __device__ void treat_slot(const PairTable& t, const Particles& P, const Geom& g
     if (lane == 0)
       for (int k = 0; k < 8; ++k) sh.red[wave][k] = v[k];
     __syncthreads();
-    n_in = (int)(sh.red[0][0] + sh.red[1][0]);
-    dmax = fmax(sh.red[0][1], sh.red[1][1]);
+    double w[8];
+    for (int k = 0; k < 8; ++k) {
+      w[k] = sh.red[0][k];
+      for (int i = 1; i < (k < 5 ? TREAT_HALF : TREAT_WAVES); ++i)
+        w[k] = k == 1 ? fmax(w[k], sh.red[i][k]) : w[k] + sh.red[i][k];
+    }
+    n_in = (int)w[0];
+    dmax = w[1];
     for (int m = 0; m < 3; ++m) {
-      sy[m] = sh.red[0][2 + m] + sh.red[1][2 + m];
-      gs[m] = (sh.red[0][5 + m] + sh.red[1][5 + m]) + (sh.red[2][5 + m] + sh.red[3][5 + m]);
+      sy[m] = w[2 + m];
+      gs[m] = w[5 + m];
     }
   }
   // (the other wavefronts go on to the next record; they write sh.red only
