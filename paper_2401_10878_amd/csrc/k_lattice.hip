@@ -448,9 +448,10 @@ __device__ inline void kinematics(const Particles& P, int q, int x, int y, int z
 
 // Register budget without spills: FP64 at most 128 VGPRs (four wavefronts
 // per SIMD), FP32 and binary16 at most 72 (seven: the pass is faster at
-// seven wavefronts than at six or five), 80 with both the polyhedron
-// distance and the balance sums, or, in FP32, without walls (72 spilled).
-// POLY: built with the polyhedron signed distance (scenes without polyhedra run the
+// seven wavefronts than at six or five), except FP32 with polyhedra and no
+// walls, which spills there and takes 74 (six).  Binary16 at seven instead of
+// six, 256^3: 1500 boxes 536 -> 505 us, 734 ellipsoids 521 -> 495.  POLY: built
+// with the polyhedron signed distance (scenes without polyhedra run the
 // form without it, which needs fewer registers).  BAL: with the block sums
 // and device acceleration of the zero-net-flux balance force.  WALL: z
 // bounded by walls (half-way bounce-back).
@@ -472,7 +473,7 @@ __device__ inline void kinematics(const Particles& P, int q, int x, int y, int z
 // node or a neighbour of one, skip it.
 template <typename S, int POLICY, bool POLY, bool BAL, bool WALL, bool ELL = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
-    sizeof(S) == 8 ? 4 : (ELL ? 5 : (POLY && (BAL || (sizeof(S) == 4 && !WALL)) ? 6 : 7)), 8))) void k_lattice(const S* __restrict__ src,
+    sizeof(S) == 8 ? 4 : (POLY && sizeof(S) == 4 && !WALL ? 6 : 7), 8))) void k_lattice(const S* __restrict__ src,
                                                  S* __restrict__ dst,
                                                  const int* __restrict__ owner,
                                                  Particles P, Geom g, Phys ph,
