@@ -7,9 +7,8 @@ seeded scene.  A step is the whole time step: contact treatment, particle
 motion and tile binning, contact carry-over, coupling map with rough
 detection, and the stream-collide pass with the coupling, which also sums
 the momentum exchange of the populations it writes.  The timed steps are replayed as
-captured HIP graphs (8 steps per graph, the contact treatment of each step
-on a second stream beside the previous step's lattice passes); --stream
-times plain stream launches instead, and the line reports the other mode's
+captured HIP graphs (8 steps per graph); --stream times plain stream
+launches instead, and the line reports the other mode's
 time beside the value.
 
 Prints ONE JSON line with the metric, the roofline of the dominant kernel
@@ -109,8 +108,7 @@ def run_gpu(wl, prec, steps, warmup, graph):
     t1 = time.perf_counter()
     c1 = sim.counters()
     # per-kernel times from a second window of the same length, with HIP
-    # events around every launch (those steps run their kernels one after
-    # another: the contact treatment does not overlap the lattice passes)
+    # events around every launch
     sim.timing_begin(steps)
     sim.step(steps)
     sim.sync()

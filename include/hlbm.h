@@ -130,9 +130,7 @@ typedef struct hlbm_ctx hlbm_ctx;
    or NULL for a private stream.  Validates the parameters (lattice size,
    tau, capacities); allocates the population buffers unless they are lent
    later.  *out is NULL on error; with no context to hold it, the message of
-   a rejected parameter goes to stderr.  The context also creates a second
-   stream (default priority) for the overlapped contact treatment of
-   hlbm_step. */
+   a rejected parameter goes to stderr. */
 hlbm_status hlbm_create(const hlbm_params *params, void *stream,
                         hlbm_ctx **out);
 
@@ -210,20 +208,15 @@ hlbm_status hlbm_set_populations(hlbm_ctx *ctx, const double *f);
    (Sec. 3.3.1, eqs. (4)-(9)), gravity and Newton-Euler update (eqs.
    (2)-(3)), particle-to-fluid coupling with rough detection (Sec. 3.2,
    Sec. 3.3.1), collide-and-stream (eqs. (10)-(15)) with the fluid-to-
-   particle momentum exchange (eqs. (16)-(18)).  With one contact sub-step
-   and no timing in use, the contact treatment of every step after the
-   first of a call runs on a second stream of the context beside the
-   previous step's lattice pass (it reads nothing that pass writes); the
-   call ends with no such work pending, and the results are those of
-   strictly ordered steps, bit for bit. */
+   particle momentum exchange (eqs. (16)-(18)).  The call ends with no
+   work of a step pending, and n steps in one call give the results of n
+   calls, bit for bit. */
 hlbm_status hlbm_step(hlbm_ctx *ctx, int nsteps);
 
 /* Use (1) or stop using (0) captured HIP graphs for hlbm_step (the step of
-   Algorithm 1 as one launch).  With one contact sub-step, a call of two or
-   more steps replays 8-step graphs (the overlapped contact treatment
-   captured inside, and carried across graph boundaries) while at least 8
-   steps remain, and runs the rest as overlapped stream launches; a single
-   step replays a single-step graph.  A graph's first replay carries a
+   Algorithm 1 as one launch).  A call of two or more steps replays 8-step
+   graphs while at least 8 steps remain, and runs the rest as stream
+   launches; a single step replays a single-step graph.  A graph's first replay carries a
    one-time setup, so a call of fewer than 64 steps replays only graphs
    that have run before (else it keeps to stream launches).  Results are
    those of stream launches, bit for bit.  The graphs of the parities the
@@ -234,13 +227,12 @@ hlbm_status hlbm_use_graph(hlbm_ctx *ctx, int on);
 
 /* Per-kernel timing of the next steps (measurement, no paper passage):
    hlbm_step records HIP events on the context stream around each of its
-   kernel launches (bookkeeping clear, contact treatment, particle motion +
-   tile binning + contact carry-over, an empty slot, coupling map + rough
-   detection, stream-collide lattice pass with the momentum exchange of the
-   next step, and a seventh slot that stays zero: the separate
-   momentum-exchange pass runs only at initialisation) for up to max_steps
-   steps (graphs and the overlapped contact treatment are bypassed
-   meanwhile).  hlbm_timing_end
+   kernel launches (an empty slot: no launch clears anything any more, contact
+   treatment, particle motion + tile binning + contact carry-over, an empty
+   slot, coupling map + rough detection, stream-collide lattice pass with the
+   momentum exchange of the next step, and a seventh slot that stays zero: the
+   separate momentum-exchange pass runs only at initialisation) for up to
+   max_steps steps (graphs are bypassed meanwhile).  hlbm_timing_end
    synchronises and returns the summed milliseconds per kernel in that
    order, kernel_ms[7], and the number of timed steps. */
 hlbm_status hlbm_timing_begin(hlbm_ctx *ctx, int max_steps);
