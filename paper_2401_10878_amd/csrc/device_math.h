@@ -584,12 +584,13 @@ __device__ inline T poly_sdf_unit(CPoly* P, const T* p, T* gb, T far) {
     const int b0 = P->fs[f], cnt = P->fs[f + 1] - b0;
     bool inside = true;
     for (int j = 0; j < cnt; ++j) {
+      const HLBM_CONST T* sp = poly_side(P, b0 + j, T());
+      if ((sp[0] * p[0] + sp[1] * p[1]) + sp[2] * p[2] >= sp[3]) continue;
+      inside = false;
       const HLBM_CONST T* a = poly_vert(P, P->fv[b0 + j], T());
       const HLBM_CONST T* e = poly_edge(P, b0 + j, T());
-      const HLBM_CONST T* sp = poly_side(P, b0 + j, T());
       const T e0 = e[0], e1 = e[1], e2 = e[2];
       const T w0 = p[0] - a[0], w1 = p[1] - a[1], w2 = p[2] - a[2];
-      inside = inside && ((sp[0] * p[0] + sp[1] * p[1]) + sp[2] * p[2] >= sp[3]);
       // nearest point of the segment a -> a + e
       T t = ((w0 * e0 + w1 * e1) + w2 * e2) * e[3];
       t = t < (T)0 ? (T)0 : (t > (T)1 ? (T)1 : t);
