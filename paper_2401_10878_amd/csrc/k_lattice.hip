@@ -685,7 +685,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   // the nodes beyond, whose addresses are uniform (a row that ends before the
   // last lane: the lane after the end holds node 0).  Each vector load cost
   // about 2 us of the pass at 256^3; 8 are left of 18: FP32 with cubes 541 ->
-  // 531 us, with boxes 628 -> 606, FP64 1040 -> 1018, binary16 396 -> 382;
+  // 531 us, with boxes 628 -> 606 (563 with the shorter polyhedron distance), FP64 1040 -> 1018, binary16 396 -> 382;
   // 128^3 between walls 74.2 -> 70.6.
   // (FP64 with ellipsoids has no registers left for it and loads them all.)
   constexpr bool SHIFT = !(sizeof(S) == 8 && ELL);
