@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <mutex>
 #include <new>
 #include <thread>
 #include <vector>
@@ -98,29 +99,38 @@ hlbm_status flags_of(Ctx& c, const Counters& h) {
 // is 15 to 40 us of host time each; the state came in four and the flags in a
 // fifth with a wait of its own: 32^3 nodes, two particles, a step and a
 // read-out 185 us).
-hlbm_status read_back(Ctx& c, const double* src, long long n) {
+//
+// The pinned block is one per context: it stays locked from the launch to the
+// end of the copy to the caller, so that several threads can read one context
+// (without it particles() had returned what another thread's forces() wrote).
+template <typename Copy>
+hlbm_status read_back(Ctx& c, const double* src, long long n, Copy copy) {
   if (!c.host_ctr) {                               // no particles yet
     Counters h;
     HIPCHECK(hipMemcpyAsync(&h, c.counters, sizeof h, hipMemcpyDeviceToHost, c.stream));
     HIPCHECK(hipStreamSynchronize(c.stream));
     return flags_of(c, h);
   }
+  const std::lock_guard<std::mutex> lock(c.read_mu);
   HIPCHECK(launch_export(c, src, n, c.host_part, c.host_ctr));
   HIPCHECK(hipStreamSynchronize(c.stream));
+  if (n > 0) copy(c.host_part);
   return flags_of(c, *c.host_ctr);
 }
-hlbm_status check_flags(Ctx& c) { return read_back(c, nullptr, 0); }
+hlbm_status check_flags(Ctx& c) { return read_back(c, nullptr, 0, [](const double*) {}); }
 
 // Read `total` units (nodes or values) of `unit` bytes through pinned chunks:
 // launch(begin, count, chunk) has the device fill a chunk, copy(begin, count,
 // chunk) moves it to the caller's arrays.  Up to READ_WORKERS threads, each
 // with a chunk of its own, take the chunks in turn: the copies into (often
-// untouched) caller memory are the longest part and run side by side.
+// untouched) caller memory are the longest part and run side by side.  The
+// chunks are the context's: one read-out at a time has them.
 template <typename Launch, typename Copy>
 hlbm_status read_chunks(Ctx& c, long long total, size_t unit, Launch launch, Copy copy) {
   const long long per = (long long)(READ_CHUNK / unit) / 256 * 256;
   const long long nch = (total + per - 1) / per;
   const int nw = (int)std::min<long long>(READ_WORKERS, nch);
+  std::unique_lock<std::mutex> lock(c.chunk_mu);
   for (int w = 0; w < nw; ++w) {
     if (c.chunk[w]) continue;
     if (!c.chunk_ev[w])
@@ -152,6 +162,7 @@ hlbm_status read_chunks(Ctx& c, long long total, size_t unit, Launch launch, Cop
   work(0);
   for (int w = started; w < nw; ++w) work(w);      // (hipSetDevice: this context's)
   for (int w = 1; w < started; ++w) th[w].join();
+  lock.unlock();
   if (err != (int)hipSuccess)
     return fail(c, HLBM_E_DEVICE, "read-out: %s", hipGetErrorString((hipError_t)err.load()));
   return check_flags(c);
@@ -1190,12 +1201,11 @@ hlbm_status hlbm_read_forces(hlbm_ctx* h, double* Fh, double* Th, double* Fc, do
   if (!c.particles_ready) return fail(c, HLBM_E_STATE, "no particles");
   // F_h, T_h, F_c, T_c lie one after another in the particle block
   const size_t np = c.np, nn = c.np > 0 ? c.np : 1;
-  const hlbm_status st = read_back(c, c.Fh, c.np > 0 ? (long long)(FORCE_OUT * nn) : 0);
   double* out[4] = {Fh, Th, Fc, Tc};
-  for (int k = 0; k < 4; ++k)
-    if (out[k] && np && st != HLBM_E_DEVICE)
-      memcpy(out[k], c.host_part + 3 * nn * k, sizeof(double) * 3 * np);
-  return st;
+  return read_back(c, c.Fh, np > 0 ? (long long)(FORCE_OUT * nn) : 0, [&](const double* o) {
+    for (int k = 0; k < 4; ++k)
+      if (out[k]) memcpy(out[k], o + 3 * nn * k, sizeof(double) * 3 * np);
+  });
 }
 
 hlbm_status hlbm_read_particles(hlbm_ctx* h, double* X, double* q, double* U, double* W) {
@@ -1204,15 +1214,12 @@ hlbm_status hlbm_read_particles(hlbm_ctx* h, double* X, double* q, double* U, do
   if (!c.particles_ready) return fail(c, HLBM_E_STATE, "no particles");
   // X, q, U, omega lie one after another in the particle block
   const size_t np = c.np, nn = c.np > 0 ? c.np : 1;
-  const hlbm_status st = read_back(c, c.part.X, c.np > 0 ? (long long)(PART_OUT * nn) : 0);
-  if (np && st != HLBM_E_DEVICE) {
-    const double* o = c.host_part;
+  return read_back(c, c.part.X, np > 0 ? (long long)(PART_OUT * nn) : 0, [&](const double* o) {
     if (X) memcpy(X, o, sizeof(double) * 3 * np);
     if (q) memcpy(q, o + 3 * nn, sizeof(double) * 4 * np);
     if (U) memcpy(U, o + 7 * nn, sizeof(double) * 3 * np);
     if (W) memcpy(W, o + 10 * nn, sizeof(double) * 3 * np);
-  }
-  return st;
+  });
 }
 
 hlbm_status hlbm_read_contacts(hlbm_ctx* h, int capacity, hlbm_contact* out, int* n_out) {

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <string>
 
 #include "../../include/hlbm.h"
@@ -314,11 +315,13 @@ struct Ctx {
   int device = 0;
   // pinned host memory of the read-outs: the counters and a particle
   // read-out (allocated with the particles), and the chunks of the field
-  // read-outs (allocated by the first that needs them), one per worker
+  // read-outs (allocated by the first that needs them), one per worker; each
+  // locked by the read-out that uses it
   Counters* host_ctr = nullptr;
   double* host_part = nullptr;
   void* chunk[READ_WORKERS] = {};
   hipEvent_t chunk_ev[READ_WORKERS] = {};
+  std::mutex read_mu, chunk_mu;
   double* bal_part = nullptr;  // per-block (mass, momentum) sums, balance mode 2
   // state
   bool particles_ready, fluid_ready;
