@@ -186,7 +186,8 @@ hlbm_status hlbm_define_ellipsoid(hlbm_ctx *ctx, int type, double a, double b,
    ratio.  Quaternions are normalised (HLBM_E_ARG for zero or non-finite
    ones).  Positions on periodic axes are wrapped into [0, n).  Periodic
    axes must exceed twice the particle reach (circumradius + detection
-   margin). */
+   margin).  A set replaces the earlier one; if its memory cannot be had
+   (HLBM_E_DEVICE), the context is left without particles. */
 hlbm_status hlbm_init_particles(hlbm_ctx *ctx, int n, const int *shape,
                                 const double *size, const double *density,
                                 const double *X, const double *q,

@@ -27,6 +27,8 @@ hlbm_status fail(Ctx& c, hlbm_status st, const char* fmt, ...) {
   va_start(ap, fmt);
   vsnprintf(c.err, sizeof c.err, fmt, ap);
   va_end(ap);
+  // (an error that is reported here is not the next launch's)
+  (void)hipGetLastError();
   return st;
 }
 
@@ -947,7 +949,9 @@ hlbm_status hlbm_init_particles(hlbm_ctx* h, int n, const int* shape, const doub
     inert[i] = shape[i] == 0 ? 0.4 * mass[i] * a * a
                              : (shape[i] == 2 ? 0.2 * mass[i] * a * a : mass[i] * a * a / 6.0);
   }
+  // the earlier set goes first: until the new one is complete there is none
   drop_graphs(c);
+  c.particles_ready = c.fluid_ready = false;
   free_particles(c);
   const size_t nn = n > 0 ? n : 1;
   // layout of the one particle allocation (doubles, then ints)
@@ -1053,7 +1057,6 @@ hlbm_status hlbm_init_particles(hlbm_ctx* h, int n, const int* shape, const doub
   }
   HIPCHECK(hipStreamSynchronize(c.stream));
   c.particles_ready = true;
-  c.fluid_ready = false;
   return HLBM_OK;
 }
 
