@@ -335,16 +335,23 @@ hlbm_status hlbm_set_state(hlbm_ctx *ctx, const void *blob, size_t bytes);
    a device snapshot of the whole state every `ckpt_every` steps (plus the
    end state); the context then stands at the end of the window, as after
    hlbm_step(ksteps).  Memory: ceil(ksteps / ckpt_every) + 1 snapshots of
-   about 19 x 8 B per node each, and, if there is room for them, the
-   gradient's ckpt_every + 3 population fields, which then hold the last
-   segment already (else the gradient allocates them and runs it again).
+   about 19 x 8 B per node each.  The gradient's store (ckpt_every + 3
+   population fields) is taken by the first gradient, so a program that
+   records many windows before it holds the snapshots alone; where memory for
+   the store is lent already, the record leaves the last segment in it, and
+   the gradient need not run that one again.
 
-   hlbm_adjoint_bytes, hlbm_bind_adjoint: the device memory of such a window,
-   snapshots and fields together, and lending it.  A caller that takes many
-   gradients lends one block instead of having gigabytes allocated and freed
-   in each; the context never frees it, and it must stay until the context is
-   destroyed or another (or none: NULL) is bound.  Binding drops a recorded
-   window; a window that does not fit the block is allocated.
+   hlbm_adjoint_parts: the device memory of such a window in two parts,
+   *snapshots from the record on and *store in the gradient (ksteps = 0: of
+   the recorded window, HLBM_E_STATE without one, with *store = 0 if it has
+   its store); hlbm_adjoint_bytes: their sum.
+   hlbm_bind_adjoint, hlbm_bind_adjoint_store: lending device memory, for a
+   whole window or its snapshots, and for its store.  A caller that takes many
+   gradients lends the same memory again and again instead of having gigabytes
+   allocated and freed in each; the context never frees it, and it must stay
+   until the context is destroyed or another (or none: NULL) is bound.
+   hlbm_bind_adjoint drops a recorded window, hlbm_bind_adjoint_store keeps
+   it.  What does not fit the lent memory is allocated.
 
    hlbm_adjoint_gradient: for J = sum_p dJ_dU[p] . U_p (the particle
    velocities at the end of the window; dJ_dU is 3n, host), recomputes each
@@ -369,7 +376,10 @@ hlbm_status hlbm_set_state(hlbm_ctx *ctx, const void *blob, size_t bytes);
    J = sum_p dJ_dU[p] . U_p. */
 hlbm_status hlbm_adjoint_bytes(hlbm_ctx *ctx, int ksteps, int ckpt_every,
                                size_t *bytes);
+hlbm_status hlbm_adjoint_parts(hlbm_ctx *ctx, int ksteps, int ckpt_every,
+                               size_t *snapshots, size_t *store);
 hlbm_status hlbm_bind_adjoint(hlbm_ctx *ctx, void *dev, size_t bytes);
+hlbm_status hlbm_bind_adjoint_store(hlbm_ctx *ctx, void *dev, size_t bytes);
 hlbm_status hlbm_adjoint_record(hlbm_ctx *ctx, int ksteps, int ckpt_every);
 hlbm_status hlbm_adjoint_gradient(hlbm_ctx *ctx, const double *dJ_dU,
                                   double *dJ_ds, double *dJ_dtheta0,

@@ -455,24 +455,47 @@ void lay_store(const Ctx& c, Adjoint& a, Arena& m) {
   m.take(&a.work, adjoint_work_doubles(c));
 }
 
-// Place what `lay` lays out as the adjoint's block k: in the lent memory if it
-// is large enough (the first block only), else in an allocation.
+// Lay out block k of the adjoint (0 snapshots, 1 store) in p, or (p null) in
+// an allocation.
 template <typename Lay>
-bool adjoint_block(Ctx& c, int k, Lay lay) {
-  Arena m;
-  lay(m);
-  void* p = k == 0 && m.used <= c.adj_mem_bytes ? c.adj_mem : nullptr;
+bool adjoint_block(Ctx& c, int k, void* p, size_t bytes, Lay lay) {
   if (!p) {
-    if (hipMalloc(&p, m.used) != hipSuccess) {
+    if (hipMalloc(&p, bytes) != hipSuccess) {
       (void)hipGetLastError();
       return false;
     }
     c.adj.block[k] = p;
   }
+  Arena m;
   m.base = (char*)p;
-  m.used = 0;
   lay(m);
   return true;
+}
+
+bool place_snapshots(Ctx& c) {
+  Arena m;
+  lay_snapshots(c, m);
+  return adjoint_block(c, 0, m.used <= c.adj_mem_bytes ? c.adj_mem : nullptr, m.used,
+                       [&](Arena& at) { lay_snapshots(c, at); });
+}
+
+// The store goes into memory lent for it, or into what is lent beyond the
+// snapshots, or (allocate) into an allocation of its own.
+bool place_store(Ctx& c, bool allocate) {
+  Adjoint& a = c.adj;
+  Arena snaps, m;
+  lay_snapshots(c, snaps);
+  lay_store(c, a, m);
+  void* p = nullptr;
+  if (m.used <= c.adj_store_bytes) {
+    p = c.adj_store;
+    a.store_lent = true;
+  } else if (!a.block[0] && snaps.used + m.used <= c.adj_mem_bytes) {
+    p = (char*)c.adj_mem + snaps.used;
+  } else if (!allocate) {
+    return false;
+  }
+  return adjoint_block(c, 1, p, m.used, [&](Arena& at) { lay_store(c, a, at); });
 }
 
 // Run the n steps of segment seg from its checkpoint (restore) or from the
@@ -1509,20 +1532,36 @@ hlbm_status hlbm_set_state(hlbm_ctx* h, const void* blob, size_t bytes) {
   return st != HLBM_OK ? st : prepare_graphs(c);
 }
 
-hlbm_status hlbm_adjoint_bytes(hlbm_ctx* h, int ksteps, int ckpt_every, size_t* bytes) {
-  if (!h || !bytes) return HLBM_E_ARG;
+hlbm_status hlbm_adjoint_parts(hlbm_ctx* h, int ksteps, int ckpt_every, size_t* snapshots,
+                               size_t* store) {
+  if (!h || !snapshots || !store) return HLBM_E_ARG;
   Ctx& c = h->c;
-  if (!c.particles_ready) return fail(c, HLBM_E_STATE, "initialise the particles first");
-  if (ksteps < 1 || ckpt_every < 1)
-    return fail(c, HLBM_E_ARG, "ksteps and ckpt_every must be >= 1");
   Adjoint a;
-  adjoint_window(a, ksteps, ckpt_every);
-  Arena one, store;
+  if (ksteps == 0) {
+    if (!c.adj.recorded) return fail(c, HLBM_E_STATE, "no recorded forward window");
+    adjoint_window(a, c.adj.K, c.adj.L);
+  } else {
+    if (!c.particles_ready) return fail(c, HLBM_E_STATE, "initialise the particles first");
+    if (ksteps < 1 || ckpt_every < 1)
+      return fail(c, HLBM_E_ARG, "ksteps and ckpt_every must be >= 1");
+    adjoint_window(a, ksteps, ckpt_every);
+  }
+  Arena one, st;
   Snapshot snap;
   lay_snapshot(c, snap, one);
-  lay_store(c, a, store);
-  *bytes = one.used * (size_t)(a.nseg + 1) + store.used;
+  lay_store(c, a, st);
+  *snapshots = one.used * ((size_t)a.nseg + 1);
+  *store = ksteps == 0 && c.adj.fst ? 0 : st.used;
   return HLBM_OK;
+}
+
+hlbm_status hlbm_adjoint_bytes(hlbm_ctx* h, int ksteps, int ckpt_every, size_t* bytes) {
+  if (!h || !bytes) return HLBM_E_ARG;
+  if (ksteps < 1) return fail(h->c, HLBM_E_ARG, "ksteps and ckpt_every must be >= 1");
+  size_t snapshots = 0, store = 0;
+  const hlbm_status st = hlbm_adjoint_parts(h, ksteps, ckpt_every, &snapshots, &store);
+  if (st == HLBM_OK) *bytes = snapshots + store;
+  return st;
 }
 
 hlbm_status hlbm_bind_adjoint(hlbm_ctx* h, void* dev, size_t bytes) {
@@ -1534,9 +1573,27 @@ hlbm_status hlbm_bind_adjoint(hlbm_ctx* h, void* dev, size_t bytes) {
   return HLBM_OK;
 }
 
-hlbm_status hlbm_adjoint_record(hlbm_ctx* h, int ksteps, int ckpt_every) {
+hlbm_status hlbm_bind_adjoint_store(hlbm_ctx* h, void* dev, size_t bytes) {
   if (!h) return HLBM_E_ARG;
   Ctx& c = h->c;
+  HIPCHECK(hipStreamSynchronize(c.stream));
+  Adjoint& a = c.adj;
+  if (a.store_lent) {
+    // (the next gradient runs the last segment again)
+    a.store_lent = false;
+    a.fst = nullptr;
+    a.stored = -1;
+  }
+  c.adj_store = bytes ? dev : nullptr;
+  c.adj_store_bytes = dev ? bytes : 0;
+  return HLBM_OK;
+}
+
+namespace {
+// Record a window.  keep: the gradient follows at once, so its store may be
+// allocated here already; else the store is the gradient's, and the record
+// holds the snapshots alone, unless memory for the store is lent.
+hlbm_status adjoint_record(Ctx& c, int ksteps, int ckpt_every, bool keep) {
   if (!c.fluid_ready) return fail(c, HLBM_E_STATE, "initialise particles and fluid first");
   if (c.precision != HLBM_FP64)
     return fail(c, HLBM_E_ARG, "the adjoint runs on the FP64 form only");
@@ -1561,17 +1618,14 @@ hlbm_status hlbm_adjoint_record(hlbm_ctx* h, int ksteps, int ckpt_every) {
   adjoint_window(a, ksteps, ckpt_every);
   a.ck = new (std::nothrow) Snapshot[a.nseg];
   if (!a.ck) return fail(c, HLBM_E_NOMEM, "checkpoint table");
-  // the last segment goes straight into the store if there is memory for it
-  // (the gradient then need not run it again)
-  const bool store = adjoint_block(c, 0, [&](Arena& m) {
-    lay_snapshots(c, m);
-    lay_store(c, a, m);
-  });
-  if (!store && !adjoint_block(c, 0, [&](Arena& m) { lay_snapshots(c, m); })) {
+  if (!place_snapshots(c)) {
     const int nseg = a.nseg;
     free_adjoint(c);
     return fail(c, HLBM_E_NOMEM, "%d checkpoints and the end state", nseg);
   }
+  // with a store at hand the last segment goes straight into it (the gradient
+  // then need not run it again)
+  const bool store = place_store(c, keep);
   for (int seg = 0; seg < a.nseg; ++seg) {
     HIPCHECK(snapshot_copy(c, a.ck[seg], 0));
     const int n = std::min(a.L, a.K - seg * a.L);
@@ -1587,6 +1641,12 @@ hlbm_status hlbm_adjoint_record(hlbm_ctx* h, int ksteps, int ckpt_every) {
   a.recorded = true;
   return HLBM_OK;
 }
+}  // namespace
+
+hlbm_status hlbm_adjoint_record(hlbm_ctx* h, int ksteps, int ckpt_every) {
+  if (!h) return HLBM_E_ARG;
+  return adjoint_record(h->c, ksteps, ckpt_every, false);
+}
 
 hlbm_status hlbm_adjoint_gradient(hlbm_ctx* h, const double* dJ_dU, double* dJ_ds,
                                   double* dJ_dtheta0, double* dJ_dq0,
@@ -1601,7 +1661,7 @@ hlbm_status hlbm_adjoint_gradient(hlbm_ctx* h, const double* dJ_dU, double* dJ_d
   const size_t npp = np > 0 ? np : 1;
   const long long n = c.g.ncell;
   const int PR = adjoint_record_doubles(), PB = adjoint_slots();
-  if (!a.fst && !adjoint_block(c, 1, [&](Arena& m) { lay_store(c, a, m); }))
+  if (!a.fst && !place_store(c, true))
     return fail(c, HLBM_E_NOMEM, "adjoint work arrays (segment of %d steps)", a.L);
   // seed: J = sum_p dJ_dU[p] . U_p(K)
   std::vector<double> pb(npp * PB, 0.0);
@@ -1672,7 +1732,8 @@ hlbm_status hlbm_adjoint_gradient(hlbm_ctx* h, const double* dJ_dU, double* dJ_d
 
 hlbm_status hlbm_adjoint(hlbm_ctx* h, int ksteps, int ckpt_every, const double* dJ_dU,
                          double* dJ_ds, double* dJ_dq0) {
-  hlbm_status st = hlbm_adjoint_record(h, ksteps, ckpt_every);
+  if (!h) return HLBM_E_ARG;
+  const hlbm_status st = adjoint_record(h->c, ksteps, ckpt_every, true);
   if (st != HLBM_OK) return st;
   return hlbm_adjoint_gradient(h, dJ_dU, dJ_ds, nullptr, dJ_dq0, nullptr, nullptr, nullptr);
 }

@@ -252,10 +252,12 @@ struct Snapshot {
 struct Adjoint {
   bool recorded = false;
   int K = 0, L = 0;                  // steps, steps per checkpoint
-  // one block (lent, see Ctx::adj_mem, or allocated) for the snapshots, the
-  // store and the work arrays, or (memory short at the record) one for the
-  // snapshots and one, at the gradient, for the rest
+  // a block for the snapshots, from the record on, and one for the store and
+  // the work arrays, from the first gradient on (or from the record, where its
+  // memory is at hand already); each lent (Ctx::adj_mem, Ctx::adj_store) or
+  // allocated
   void* block[2] = {nullptr, nullptr};   // those allocated here
+  bool store_lent = false;               // the store stands in Ctx::adj_store
   Snapshot* ck = nullptr;            // checkpoint at the start of each segment
   int nseg = 0;
   Snapshot end;                      // state after the K steps
@@ -333,9 +335,10 @@ struct Ctx {
   // sizes of the state blocks (for snapshots)
   size_t part_bytes = 0, tile_bytes = 0, psum_bytes = 0;
   Adjoint adj;
-  // device memory lent for the adjoint (hlbm_bind_adjoint), never freed here
-  void* adj_mem = nullptr;
-  size_t adj_mem_bytes = 0;
+  // device memory lent for the adjoint (hlbm_bind_adjoint,
+  // hlbm_bind_adjoint_store), never freed here
+  void *adj_mem = nullptr, *adj_store = nullptr;
+  size_t adj_mem_bytes = 0, adj_store_bytes = 0;
   // graphs: one per (population parity, contact-table parity) for a single
   // step and one for GRAPH_STEPS steps
   bool use_graph;

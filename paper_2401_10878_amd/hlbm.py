@@ -8,6 +8,7 @@ raises immediately, and there is no CPU fallback.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes as C
 import os
 import re
@@ -110,7 +111,9 @@ def load():
     L.hlbm_get_state.argtypes = [v, v, P(C.c_size_t)]
     L.hlbm_set_state.argtypes = [v, v, C.c_size_t]
     L.hlbm_adjoint_bytes.argtypes = [v, i, i, P(C.c_size_t)]
+    L.hlbm_adjoint_parts.argtypes = [v, i, i, P(C.c_size_t), P(C.c_size_t)]
     L.hlbm_bind_adjoint.argtypes = [v, v, C.c_size_t]
+    L.hlbm_bind_adjoint_store.argtypes = [v, v, C.c_size_t]
     L.hlbm_adjoint_record.argtypes = [v, i, i]
     L.hlbm_adjoint_gradient.argtypes = [v] + [P(d)] * 7
     L.hlbm_adjoint.argtypes = [v, i, i, P(d), P(d), P(d)]
@@ -350,31 +353,57 @@ class Simulation:
         self._check(self.L.hlbm_set_state(self.h, buf, len(blob)))
 
     # ---- adjoint ------------------------------------------------------------
-    def _lend_adjoint(self, ksteps, ckpt_every):
-        """Lend the library the memory of a window from torch's allocator, which
-        keeps it between gradients: allocating and freeing gigabytes in each
-        one has the driver clear them in between (96^3, 20 steps: 8 ms a
-        gradient, but 55 ms on average over hundreds).  Without room (or on
-        arguments that the record refuses) the library allocates itself."""
-        n = C.c_size_t()
-        if self.L.hlbm_adjoint_bytes(self.h, int(ksteps), int(ckpt_every), C.byref(n)):
-            return
-        mem = self.adj_mem
-        if mem is not None and mem.numel() >= n.value:
-            return
+    # The memory of a window comes from torch's allocator, which keeps it between
+    # gradients: allocating and freeing gigabytes in each one has the driver
+    # clear them in between (96^3, 20 steps: 8 ms a gradient, but 55 ms on
+    # average over hundreds).  Without room (or on arguments that the record
+    # refuses) the library allocates itself.
+    def _adjoint_parts(self, ksteps, ckpt_every):
+        """Bytes of a window's snapshots and of its store (0 if refused)."""
+        n = C.c_size_t(), C.c_size_t()
+        if self.L.hlbm_adjoint_parts(self.h, int(ksteps), int(ckpt_every),
+                                     C.byref(n[0]), C.byref(n[1])):
+            return 0, 0
+        return n[0].value, n[1].value
+
+    def _device_block(self, nbytes):
         torch = self.torch
         try:
-            mem = torch.empty(n.value, dtype=torch.uint8, device=self.device)
-        except RuntimeError:
-            return
+            mem = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        except (RuntimeError, TypeError):    # no room, or past 64 bits
+            return None
         # what torch has queued on this memory comes first
         self.stream.wait_stream(torch.cuda.current_stream(self.device))
-        self._check(self.L.hlbm_bind_adjoint(self.h, C.c_void_p(mem.data_ptr()), n.value))
+        return mem
+
+    def _lend_snapshots(self, nbytes):
+        """Memory of a window's snapshots, lent until the next record or the end."""
+        mem = self.adj_mem
+        if nbytes == 0 or (mem is not None and mem.numel() >= nbytes):
+            return
+        mem = self._device_block(nbytes)
+        if mem is None:
+            return
+        self._check(self.L.hlbm_bind_adjoint(self.h, C.c_void_p(mem.data_ptr()), nbytes))
         self.adj_mem = mem
+
+    @contextlib.contextmanager
+    def _lent_store(self, nbytes):
+        """Memory of the reverse sweep, lent for one gradient."""
+        mem = self._device_block(nbytes) if nbytes else None
+        if mem is None:
+            yield
+            return
+        self._check(self.L.hlbm_bind_adjoint_store(self.h, C.c_void_p(mem.data_ptr()), nbytes))
+        try:
+            yield
+        finally:
+            # (waits for the library's stream)
+            self._check(self.L.hlbm_bind_adjoint_store(self.h, None, 0))
 
     def adjoint_record(self, ksteps, ckpt_every):
         """Run ksteps steps keeping checkpoints every ckpt_every steps."""
-        self._lend_adjoint(ksteps, ckpt_every)
+        self._lend_snapshots(self._adjoint_parts(ksteps, ckpt_every)[0])
         self._check(self.L.hlbm_adjoint_record(self.h, ksteps, ckpt_every))
 
     def adjoint_gradient(self, dJ_dU):
@@ -384,9 +413,10 @@ class Simulation:
         seed[:self.np] = np.asarray(dJ_dU, np.float64).reshape(self.np, 3)
         out = dict(s=np.zeros(n), theta0=np.zeros((n, 3)), q0=np.zeros((n, 4)),
                    X0=np.zeros((n, 3)), U0=np.zeros((n, 3)), omega0=np.zeros((n, 3)))
-        self._check(self.L.hlbm_adjoint_gradient(
-            self.h, _dp(seed), _dp(out["s"]), _dp(out["theta0"]), _dp(out["q0"]),
-            _dp(out["X0"]), _dp(out["U0"]), _dp(out["omega0"])))
+        with self._lent_store(self._adjoint_parts(0, 0)[1]):
+            self._check(self.L.hlbm_adjoint_gradient(
+                self.h, _dp(seed), _dp(out["s"]), _dp(out["theta0"]), _dp(out["q0"]),
+                _dp(out["X0"]), _dp(out["U0"]), _dp(out["omega0"])))
         return {k: v[:self.np] for k, v in out.items()}
 
     def adjoint(self, ksteps, ckpt_every, dJ_dU):
@@ -396,9 +426,11 @@ class Simulation:
         seed = np.zeros((n, 3))
         seed[:self.np] = np.asarray(dJ_dU, np.float64).reshape(self.np, 3)
         ds, dq = np.zeros(n), np.zeros((n, 4))
-        self._lend_adjoint(ksteps, ckpt_every)
-        self._check(self.L.hlbm_adjoint(self.h, int(ksteps), int(ckpt_every),
-                                        _dp(seed), _dp(ds), _dp(dq)))
+        snapshots, store = self._adjoint_parts(ksteps, ckpt_every)
+        self._lend_snapshots(snapshots)
+        with self._lent_store(store):
+            self._check(self.L.hlbm_adjoint(self.h, int(ksteps), int(ckpt_every),
+                                            _dp(seed), _dp(ds), _dp(dq)))
         return ds[:self.np], dq[:self.np]
 
 
