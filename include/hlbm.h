@@ -342,9 +342,10 @@ hlbm_status hlbm_set_state(hlbm_ctx *ctx, const void *blob, size_t bytes);
    the gradient need not run that one again.
 
    hlbm_adjoint_parts: the device memory of such a window in two parts,
-   *snapshots from the record on and *store in the gradient (ksteps = 0: of
-   the recorded window, HLBM_E_STATE without one, with *store = 0 if it has
-   its store); hlbm_adjoint_bytes: their sum.
+   *snapshots from the record on and *store in the gradient, refused where
+   the record would be, so that a caller takes memory for windows that can be
+   recorded only (ksteps = 0: of the recorded window, HLBM_E_STATE without
+   one, with *store = 0 if it has its store); hlbm_adjoint_bytes: their sum.
    hlbm_bind_adjoint, hlbm_bind_adjoint_store: lending device memory, for a
    whole window or its snapshots, and for its store.  A caller that takes many
    gradients lends the same memory again and again instead of having gigabytes

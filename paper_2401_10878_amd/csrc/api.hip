@@ -432,7 +432,7 @@ hipError_t snapshot_copy(Ctx& c, Snapshot& s, int dir) {
 void adjoint_window(Adjoint& a, int ksteps, int ckpt_every) {
   a.K = ksteps;
   a.L = ckpt_every < ksteps ? ckpt_every : ksteps;
-  a.nseg = (a.K + a.L - 1) / a.L;
+  a.nseg = (a.K - 1) / a.L + 1;
 }
 
 void lay_snapshots(Ctx& c, Arena& m) {
@@ -1532,36 +1532,67 @@ hlbm_status hlbm_set_state(hlbm_ctx* h, const void* blob, size_t bytes) {
   return st != HLBM_OK ? st : prepare_graphs(c);
 }
 
-hlbm_status hlbm_adjoint_parts(hlbm_ctx* h, int ksteps, int ckpt_every, size_t* snapshots,
-                               size_t* store) {
-  if (!h || !snapshots || !store) return HLBM_E_ARG;
-  Ctx& c = h->c;
+namespace {
+// The checks of a window's arguments and of what the adjoint supports.
+hlbm_status adjoint_supported(Ctx& c, int ksteps, int ckpt_every) {
+  if (c.precision != HLBM_FP64)
+    return fail(c, HLBM_E_ARG, "the adjoint runs on the FP64 form only");
+  if (!c.g.periodic_z) return fail(c, HLBM_E_ARG, "the adjoint needs a fully periodic box");
+  if (c.n_sub != 1) return fail(c, HLBM_E_ARG, "the adjoint runs without contact sub-steps");
+  if (c.ph.bal_mode == 2)
+    return fail(c, HLBM_E_ARG, "the adjoint supports balance modes 0 and 1 only");
+  if (c.has_poly)
+    return fail(c, HLBM_E_ARG, "the adjoint supports spheres, cubes and octahedra only");
+  if (ksteps < 1 || ckpt_every < 1)
+    return fail(c, HLBM_E_ARG, "ksteps and ckpt_every must be >= 1");
+  return HLBM_OK;
+}
+// The checks of a record, all before it takes or drops anything.
+hlbm_status adjoint_check(Ctx& c, int ksteps, int ckpt_every) {
+  if (!c.fluid_ready) return fail(c, HLBM_E_STATE, "initialise particles and fluid first");
+  const hlbm_status st = adjoint_supported(c, ksteps, ckpt_every);
+  if (st != HLBM_OK) return st;
+  if (c.timing) return fail(c, HLBM_E_STATE, "finish the timing window first");
+  return HLBM_OK;
+}
+
+void adjoint_sizes(Ctx& c, int ksteps, int ckpt_every, size_t* snapshots, size_t* store) {
   Adjoint a;
-  if (ksteps == 0) {
-    if (!c.adj.recorded) return fail(c, HLBM_E_STATE, "no recorded forward window");
-    adjoint_window(a, c.adj.K, c.adj.L);
-  } else {
-    if (!c.particles_ready) return fail(c, HLBM_E_STATE, "initialise the particles first");
-    if (ksteps < 1 || ckpt_every < 1)
-      return fail(c, HLBM_E_ARG, "ksteps and ckpt_every must be >= 1");
-    adjoint_window(a, ksteps, ckpt_every);
-  }
+  adjoint_window(a, ksteps, ckpt_every);
   Arena one, st;
   Snapshot snap;
   lay_snapshot(c, snap, one);
   lay_store(c, a, st);
   *snapshots = one.used * ((size_t)a.nseg + 1);
-  *store = ksteps == 0 && c.adj.fst ? 0 : st.used;
-  return HLBM_OK;
+  *store = st.used;
+}
+}  // namespace
+
+hlbm_status hlbm_adjoint_parts(hlbm_ctx* h, int ksteps, int ckpt_every, size_t* snapshots,
+                               size_t* store) {
+  if (!h || !snapshots || !store) return HLBM_E_ARG;
+  Ctx& c = h->c;
+  if (ksteps == 0) {
+    if (!c.adj.recorded) return fail(c, HLBM_E_STATE, "no recorded forward window");
+    adjoint_sizes(c, c.adj.K, c.adj.L, snapshots, store);
+    if (c.adj.fst) *store = 0;
+    return HLBM_OK;
+  }
+  const hlbm_status st = adjoint_check(c, ksteps, ckpt_every);
+  if (st == HLBM_OK) adjoint_sizes(c, ksteps, ckpt_every, snapshots, store);
+  return st;
 }
 
 hlbm_status hlbm_adjoint_bytes(hlbm_ctx* h, int ksteps, int ckpt_every, size_t* bytes) {
   if (!h || !bytes) return HLBM_E_ARG;
-  if (ksteps < 1) return fail(h->c, HLBM_E_ARG, "ksteps and ckpt_every must be >= 1");
+  Ctx& c = h->c;
+  if (!c.particles_ready) return fail(c, HLBM_E_STATE, "initialise the particles first");
+  const hlbm_status st = adjoint_supported(c, ksteps, ckpt_every);
+  if (st != HLBM_OK) return st;
   size_t snapshots = 0, store = 0;
-  const hlbm_status st = hlbm_adjoint_parts(h, ksteps, ckpt_every, &snapshots, &store);
-  if (st == HLBM_OK) *bytes = snapshots + store;
-  return st;
+  adjoint_sizes(c, ksteps, ckpt_every, &snapshots, &store);
+  *bytes = snapshots + store;
+  return HLBM_OK;
 }
 
 hlbm_status hlbm_bind_adjoint(hlbm_ctx* h, void* dev, size_t bytes) {
@@ -1594,25 +1625,8 @@ namespace {
 // allocated here already; else the store is the gradient's, and the record
 // holds the snapshots alone, unless memory for the store is lent.
 hlbm_status adjoint_record(Ctx& c, int ksteps, int ckpt_every, bool keep) {
-  if (!c.fluid_ready) return fail(c, HLBM_E_STATE, "initialise particles and fluid first");
-  if (c.precision != HLBM_FP64)
-    return fail(c, HLBM_E_ARG, "the adjoint runs on the FP64 form only");
-  if (!c.g.periodic_z) return fail(c, HLBM_E_ARG, "the adjoint needs a fully periodic box");
-  if (c.n_sub != 1) return fail(c, HLBM_E_ARG, "the adjoint runs without contact sub-steps");
-  if (c.ph.bal_mode == 2)
-    return fail(c, HLBM_E_ARG, "the adjoint supports balance modes 0 and 1 only");
-  {
-    std::vector<int> sh(c.np > 0 ? c.np : 1);
-    if (c.np > 0) {
-      HIPCHECK(hipMemcpy(sh.data(), c.part.shape, sizeof(int) * c.np, hipMemcpyDeviceToHost));
-      for (int i = 0; i < c.np; ++i)
-        if (sh[i] >= POLY0)
-          return fail(c, HLBM_E_ARG, "the adjoint supports spheres, cubes and octahedra only");
-    }
-  }
-  if (c.timing) return fail(c, HLBM_E_STATE, "finish the timing window first");
-  if (ksteps < 1 || ckpt_every < 1)
-    return fail(c, HLBM_E_ARG, "ksteps and ckpt_every must be >= 1");
+  const hlbm_status refused = adjoint_check(c, ksteps, ckpt_every);
+  if (refused != HLBM_OK) return refused;
   free_adjoint(c);
   Adjoint& a = c.adj;
   adjoint_window(a, ksteps, ckpt_every);

@@ -1,5 +1,6 @@
 """Device memory of the adjoint's window: what a record holds until its
-gradient, and where the gradient's store stands."""
+gradient, where the gradient's store stands, and what a refused record leaves
+as it was."""
 import ctypes
 
 import numpy as np
@@ -7,6 +8,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
+E_ARG = -1
 MB = 1 << 20
 
 
@@ -112,3 +114,39 @@ def test_stores_lent_and_allocated_agree(W, H, every):
             for other in (r, again):
                 assert np.abs(other[k] - first[k]).max() <= 1e-11 * scale, (how, k)
         g.close()
+
+
+@pytest.mark.parametrize("kw", [dict(precision=1), dict(periodic_z=0), dict(n_sub=2),
+                                dict(balance=2)])
+def test_refused_window_takes_no_memory(W, H, kw):
+    """A window of a configuration that the adjoint does not support."""
+    print("adjoint memory: refused", kw, flush=True)
+    g = _sim(W, H, **kw)
+    free = _free(g)
+    for call in (lambda: g.adjoint_record(40, 40),
+                 lambda: g.adjoint(40, 40, np.zeros((4, 3)))):
+        with pytest.raises(H.HlbmError) as e:
+            call()
+        assert e.value.code == E_ARG
+        assert free - _free(g) <= 4 * MB
+    size = ctypes.c_size_t()
+    assert g.L.hlbm_adjoint_bytes(g.h, 40, 40, ctypes.byref(size)) == E_ARG
+    g.close()
+
+
+def test_refused_record_keeps_the_window(W, H):
+    """A record refused because a timing window is open leaves the recorded
+    window to its gradient."""
+    print("adjoint memory: window kept", flush=True)
+    g = _sim(W, H, dims=(33, 26, 21))
+    seed = np.random.default_rng(5).normal(size=(4, 3))
+    g.adjoint_record(4, 2)
+    r = g.adjoint_gradient(seed)
+    g.timing_begin(4)
+    with pytest.raises(H.HlbmError):
+        g.adjoint_record(8, 1)
+    g.timing_end()
+    again = g.adjoint_gradient(seed)
+    for k in r:
+        assert np.abs(again[k] - r[k]).max() <= 1e-11 * np.abs(r[k]).max(), k
+    g.close()
