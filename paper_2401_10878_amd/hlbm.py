@@ -351,6 +351,7 @@ class Simulation:
     def set_state(self, blob: bytes):
         buf = C.create_string_buffer(blob, len(blob))
         self._check(self.L.hlbm_set_state(self.h, buf, len(blob)))
+        self._take_back_snapshots()      # (the window is dropped)
 
     # ---- adjoint ------------------------------------------------------------
     # The memory of a window comes from torch's allocator, which keeps it between
@@ -377,15 +378,22 @@ class Simulation:
         return mem
 
     def _lend_snapshots(self, nbytes):
-        """Memory of a window's snapshots, lent until the next record or the end."""
-        mem = self.adj_mem
-        if nbytes == 0 or (mem is not None and mem.numel() >= nbytes):
+        """Memory of a window's snapshots, lent until the next record of another
+        size; the earlier block goes back first."""
+        if nbytes == 0 or (self.adj_mem is not None and self.adj_mem.numel() == nbytes):
             return
+        self._take_back_snapshots()
         mem = self._device_block(nbytes)
         if mem is None:
             return
         self._check(self.L.hlbm_bind_adjoint(self.h, C.c_void_p(mem.data_ptr()), nbytes))
         self.adj_mem = mem
+
+    def _take_back_snapshots(self):
+        if self.adj_mem is not None:
+            # (drops the window and waits for the library's stream)
+            self._check(self.L.hlbm_bind_adjoint(self.h, None, 0))
+            self.adj_mem = None
 
     @contextlib.contextmanager
     def _lent_store(self, nbytes):

@@ -1,6 +1,6 @@
 """Device memory of the adjoint's window: what a record holds until its
-gradient, where the gradient's store stands, and what a refused record leaves
-as it was."""
+gradient, where the gradient's store stands, what a refused record leaves as
+it was, and what a larger window needs beside the one it replaces."""
 import ctypes
 
 import numpy as np
@@ -149,4 +149,26 @@ def test_refused_record_keeps_the_window(W, H):
     again = g.adjoint_gradient(seed)
     for k in r:
         assert np.abs(again[k] - r[k]).max() <= 1e-11 * np.abs(r[k]).max(), k
+    g.close()
+
+
+def test_larger_window_replaces_the_smaller(W, H):
+    """The memory of the earlier window goes back before a larger one is taken:
+    the two never stand side by side, and none stays without a window."""
+    print("adjoint memory: larger window", flush=True)
+    g = _sim(W, H)
+    field = 19 * 8 * 64 ** 3
+    cuda = g.torch.cuda
+    g.adjoint_record(8, 1)                    # nine snapshots
+    _free(g)
+    cuda.reset_peak_memory_stats(g.device)
+    base = cuda.memory_allocated(g.device) - g.adj_mem.numel()
+    g.adjoint_record(10, 1)                   # eleven
+    assert cuda.max_memory_allocated(g.device) - base <= 11 * field + 64 * MB
+    # and a smaller one does not keep the larger block
+    g.adjoint_record(2, 1)
+    assert cuda.memory_allocated(g.device) - base <= 3 * field + 64 * MB
+    # a restored state drops the window, and its memory with it
+    g.set_state(g.get_state())
+    assert cuda.memory_allocated(g.device) - base <= MB
     g.close()
