@@ -137,7 +137,8 @@ hlbm_status hlbm_create(const hlbm_params *params, void *stream,
 /* Lend two DEVICE population buffers of `bytes` each (19 * nx*ny*nz *
    bytes-per-value of the precision: 8, 4 or 2) for the post-collision
    populations f* of eqs. (10)-(12) and their streamed copy (ping-pong).
-   Must be called before any init call.  The context never frees them. */
+   Must be called before the fluid is initialised.  The context never frees
+   them. */
 hlbm_status hlbm_bind_populations(hlbm_ctx *ctx, void *dev_a, void *dev_b,
                                   size_t bytes);
 

@@ -22,6 +22,7 @@ HEADER = os.path.join(os.path.dirname(HERE), "include", "hlbm.h")
 Q = 19
 STATUS = {0: "OK", -1: "E_ARG", -2: "E_NOMEM", -3: "E_DEVICE", -4: "E_CAPACITY",
           -5: "E_UNSTABLE", -6: "E_STATE"}
+E_NOMEM, E_DEVICE = -2, -3
 BYTES = {0: 8, 1: 4, 2: 2}
 
 
@@ -178,18 +179,10 @@ class Simulation:
         self.stream = torch.cuda.Stream(self.device)
         self.P = make_params(params)
         h = C.c_void_p()
-        self._check(self.L.hlbm_create(C.byref(self.P),
-                                       C.c_void_p(self.stream.cuda_stream),
-                                       C.byref(h)), None)
+        self._check(self._with_memory(lambda: self.L.hlbm_create(
+            C.byref(self.P), C.c_void_p(self.stream.cuda_stream), C.byref(h))), None)
         self.h = h
         self.adj_mem = None
-        nbytes = Q * self.ncell * BYTES[params.precision]
-        self.fa = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
-        self.fb = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
-        torch.cuda.synchronize(self.device)
-        self._check(self.L.hlbm_bind_populations(
-            self.h, C.c_void_p(self.fa.data_ptr()), C.c_void_p(self.fb.data_ptr()),
-            nbytes))
         for k, poly in (polyhedra or {}).items():
             if hasattr(poly, "axes"):
                 a, b, c = (float(x) for x in poly.axes)
@@ -203,12 +196,31 @@ class Simulation:
         sh = np.ascontiguousarray(scene.shape, np.int32)
         arrs = [np.ascontiguousarray(a, np.float64) for a in
                 (scene.size, scene.density, scene.X, scene.q, scene.U, scene.omega)]
-        self._check(self.L.hlbm_init_particles(self.h, self.np, _ip(sh),
-                                               *[_dp(a) for a in arrs]))
+        self._check(self._with_memory(lambda: self.L.hlbm_init_particles(
+            self.h, self.np, _ip(sh), *[_dp(a) for a in arrs])))
+        # (after the library's own memory: a population buffer cut from an unused
+        # block of torch's would keep that block from being given back)
+        nbytes = Q * self.ncell * BYTES[params.precision]
+        self.fa = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        self.fb = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        torch.cuda.synchronize(self.device)
+        self._check(self.L.hlbm_bind_populations(
+            self.h, C.c_void_p(self.fa.data_ptr()), C.c_void_p(self.fb.data_ptr()),
+            nbytes))
         if graph:
             self._check(self.L.hlbm_use_graph(self.h, 1))
 
     # ---- lifecycle ------------------------------------------------------
+    def _with_memory(self, call):
+        """A call that allocates beside torch: without memory it is made again
+        once torch has given back the blocks that it keeps unused (populations
+        and adjoint windows of closed simulations)."""
+        rc = call()
+        if rc in (E_NOMEM, E_DEVICE):
+            self.torch.cuda.empty_cache()
+            rc = call()
+        return rc
+
     def _check(self, rc, h=...):
         if rc != 0:
             hh = self.h if h is ... else h
