@@ -353,7 +353,8 @@ hlbm_status hlbm_set_state(hlbm_ctx *ctx, const void *blob, size_t bytes);
    allocated and freed in each; the context never frees it, and it must stay
    until the context is destroyed or another (or none: NULL) is bound.
    hlbm_bind_adjoint drops a recorded window, hlbm_bind_adjoint_store keeps
-   it.  What does not fit the lent memory is allocated.
+   it.  What does not fit the lent memory is allocated; memory that is not
+   aligned to 8 bytes is refused (HLBM_E_ARG).
 
    hlbm_adjoint_gradient: for J = sum_p dJ_dU[p] . U_p (the particle
    velocities at the end of the window; dJ_dU is 3n, host), recomputes each

@@ -375,7 +375,10 @@ void free_particles(Ctx& c) {
 // ---- state snapshots (device-to-device copies on the context stream) ------
 size_t pop_bytes(const Ctx& c) { return (size_t)Q * (size_t)c.g.ncell * c.bytes_per_value; }
 
-// Rows of one allocation, 256-byte aligned: with a null base only the size.
+// Rows of one allocation, 256 bytes apart: with a null base only the size.
+// Lent memory has to be aligned for the FP64 accesses to the rows.
+constexpr size_t ADJOINT_ALIGN = sizeof(double);
+bool adjoint_aligned(const void* p) { return (uintptr_t)p % ADJOINT_ALIGN == 0; }
 struct Arena {
   char* base = nullptr;
   size_t used = 0;
@@ -1598,6 +1601,8 @@ hlbm_status hlbm_adjoint_bytes(hlbm_ctx* h, int ksteps, int ckpt_every, size_t* 
 hlbm_status hlbm_bind_adjoint(hlbm_ctx* h, void* dev, size_t bytes) {
   if (!h) return HLBM_E_ARG;
   Ctx& c = h->c;
+  if (!adjoint_aligned(dev))
+    return fail(c, HLBM_E_ARG, "lent memory must be aligned to %zu bytes", ADJOINT_ALIGN);
   free_adjoint(c);                                 // (waits for the stream)
   c.adj_mem = bytes ? dev : nullptr;
   c.adj_mem_bytes = dev ? bytes : 0;
@@ -1607,6 +1612,8 @@ hlbm_status hlbm_bind_adjoint(hlbm_ctx* h, void* dev, size_t bytes) {
 hlbm_status hlbm_bind_adjoint_store(hlbm_ctx* h, void* dev, size_t bytes) {
   if (!h) return HLBM_E_ARG;
   Ctx& c = h->c;
+  if (!adjoint_aligned(dev))
+    return fail(c, HLBM_E_ARG, "lent memory must be aligned to %zu bytes", ADJOINT_ALIGN);
   HIPCHECK(hipStreamSynchronize(c.stream));
   Adjoint& a = c.adj;
   if (a.store_lent) {

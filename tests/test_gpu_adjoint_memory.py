@@ -1,6 +1,7 @@
 """Device memory of the adjoint's window: what a record holds until its
 gradient, where the gradient's store stands, what a refused record leaves as
-it was, and what a larger window needs beside the one it replaces."""
+it was, what a larger window needs beside the one it replaces, and what may be
+lent."""
 import ctypes
 
 import numpy as np
@@ -172,3 +173,27 @@ def test_larger_window_replaces_the_smaller(W, H):
     g.set_state(g.get_state())
     assert cuda.memory_allocated(g.device) - base <= MB
     g.close()
+
+
+def test_lent_memory_has_to_be_aligned(W, H):
+    """Aligned for FP64 accesses: else refused; at 8 bytes past a larger
+    alignment the same gradient (to the order of its FP64 atomic sums)."""
+    print("adjoint memory: alignment", flush=True)
+    seed = np.random.default_rng(5).normal(size=(4, 3))
+    size = ctypes.c_size_t()
+    r = []
+    for off in (0, 8):
+        g = _sim(W, H, dims=(33, 26, 21))
+        assert g.L.hlbm_adjoint_bytes(g.h, 7, 3, ctypes.byref(size)) == 0
+        n = size.value
+        mem = g.torch.empty(n + 256, dtype=g.torch.uint8, device=g.device)
+        for bind in (g.L.hlbm_bind_adjoint_store, g.L.hlbm_bind_adjoint):
+            for odd in (1, 4):
+                assert bind(g.h, ctypes.c_void_p(mem.data_ptr() + odd), n) == E_ARG
+            assert bind(g.h, None, 0) == 0
+        assert g.L.hlbm_bind_adjoint(g.h, ctypes.c_void_p(mem.data_ptr() + off), n) == 0
+        assert g.L.hlbm_adjoint_record(g.h, 7, 3) == 0
+        r.append(g.adjoint_gradient(seed))
+        g.close()
+    for k in r[0]:
+        assert np.abs(r[1][k] - r[0][k]).max() <= 1e-11 * np.abs(r[0][k]).max(), k
