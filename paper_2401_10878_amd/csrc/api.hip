@@ -599,8 +599,8 @@ hlbm_status hlbm_create(const hlbm_params* params, void* stream, hlbm_ctx** out)
   c.g.flty = make_fastdiv((unsigned)c.g.lty);
   c.g.tile_cap = P.tile_capacity;
   c.g.ncell = ncell;
-  // both population buffers within the 256 MB Infinity Cache (see k_lattice)
-  c.g.cached = 2.0 * Q * (double)ncell * (double)c.bytes_per_value <= 270e6;
+  // (the access policy of the populations, see k_lattice)
+  c.g.cached = 2 * Q * (size_t)ncell * c.bytes_per_value <= INFINITY_CACHE;
   c.ph.tau = P.tau;
   c.ph.omega = 1.0 / P.tau;
   for (int w = 0; w < 2; ++w)

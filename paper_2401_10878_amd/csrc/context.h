@@ -169,6 +169,8 @@ __device__ inline unsigned xcd_block(unsigned bid, unsigned nblocks) {
   return xcd * m + (xcd < r ? xcd : r) + k;
 }
 
+constexpr size_t INFINITY_CACHE = (size_t)256 << 20;   // bytes
+
 // Scalar parameters handed to every kernel by value.
 struct Geom {
   int nx, ny, nz;

@@ -83,16 +83,19 @@ struct Store<__half> {
 __device__ inline int owner_at(const int* owner, unsigned b) {
   return owner_id(*(const int*)((const char*)owner + b));
 }
-// Access policy of the populations.  A pass reads what the pass before it
-// wrote: where both buffers fit the Infinity Cache (256 MB, on the memory
-// side) together, plain accesses find most of it there.  A larger lattice
-// keeps nothing either way, and its accesses are non-temporal, so that they
-// do not displace what is used again: the owner map, the candidate lists and
-// the particle records.  Measured, us per launch, non-temporal against plain:
-// 120^3 FP32 (263 MB) 82.5, 72.5; 151 x 89 x 67 binary16 (68 MB) 35.4, 30.6;
-// 256^3 FP64 (5.1 GB) 1043, 1156, and detection 89, 105.  The policy is a
-// template parameter: a branch between the two forms inside one kernel cost
-// 256^3 binary16 401 -> 448 us.
+// Access policy of the populations (Geom::cached).  A pass reads what the pass
+// before it wrote: plain accesses find it in the Infinity Cache (256 MiB, on
+// the memory side) as long as both buffers fit there together.  Above that the
+// accesses are non-temporal, so that they do not displace what is used again:
+// the owner map, the candidate lists and the particle records.  The line lies at
+// the cache's size, where the two cross (cubes at 10%, us per launch,
+// non-temporal against plain): FP32 120^3 (263 MB) 88.7, 72.3, 128^3 (319 MB)
+// 76.8, 84.3; FP64 92^3 (237 MB) 76.2, 51.6, 96^3 (269 MB) 73.1, 73.0, 104^3
+// (342 MB) 90.1, 96.6; binary16 152^3 (267 MB) 132, 109, 160^3 (311 MB) 126, 123,
+// 192^3 (538 MB) 167, 180.  (Rows that end inside a cache line gain from plain
+// accesses up to about 600 MB: FP32 136^3 129, 111, binary16 168^3 179, 139.)  The
+// policy is a template parameter: a branch between the two forms inside one
+// kernel cost 256^3 binary16 401 -> 448 us.
 constexpr int BUF_NT = 2;
 template <typename S, int AUX>
 __device__ inline typename Store<S>::C ld_buf(const S* base, unsigned b) {
