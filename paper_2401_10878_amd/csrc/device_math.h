@@ -179,12 +179,6 @@ __device__ inline double minimg(double v, double L, bool periodic) {
   r = (periodic && v < -0.5 * L) ? lo : r;
   return r;
 }
-__device__ inline float minimg_f(float v, float L, bool periodic) {
-  const float lo = v + L, hi = v - L;
-  float r = (periodic && v >= 0.5f * L) ? hi : v;
-  r = (periodic && v < -0.5f * L) ? lo : r;
-  return r;
-}
 __device__ inline int image_shift(double v, double L, bool periodic) {
   if (!periodic) return 0;
   if (v >= 0.5 * L) return -1;
