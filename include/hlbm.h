@@ -39,6 +39,9 @@
  * overflow, non-finite or non-positive density) are raised at the next
  * read or hlbm_sync call as HLBM_E_CAPACITY / HLBM_E_UNSTABLE.  No C++
  * exception crosses the ABI.
+ *
+ * Several threads may call the read functions of one context and hlbm_sync at
+ * the same time (hlbm_read_coupling_noalloc excepted).
  */
 #ifndef HLBM_H
 #define HLBM_H

@@ -241,27 +241,6 @@ __device__ inline T octa_q(T a, T q0, T q1, T q2) {
   return octa_q<T>(a, q0, q1, q2, g0, g1, g2);
 }
 
-// Signed distance of a unit-scale polyhedron at body point p (T = double or
-// float, data in the same precision) and, if gb is given, its body-frame
-// gradient.  Inside (every plane distance <= 0): the largest plane distance,
-// gradient the normal of the first face attaining it.  Outside: the distance
-// to the nearest boundary point, which is unique for a convex body.  The
-// nearest point lies on a face the point is
-// above (positive plane distance) or on the boundary of such a face: at a
-// nearest point c, p - c is a non-negative combination of the normals of
-// the faces through c, so (p - c) . n > 0 for one of them.  Those faces'
-// interiors and boundary edges are searched: p projects into a face when it is
-// on the inner side of every side plane, s . p = (n x (b - a)) . p >= s . a for
-// each boundary edge a -> b (counter-clockwise seen from outside), and else
-// the face's nearest point is on an edge whose side p fails (at a vertex,
-// p - c is a sum of the two sides' outward normals, so p fails one of them);
-// the other edges are left out.  (All edges, after a test of the face of the
-// largest plane distance with per-lane face data, us at 256^3 with 1500 boxes:
-// lattice pass 607, detection 223, particles 55; failed edges only 599, 205, 50;
-// without that first test 563, 191, 46.)  Gradient the face normal or
-// (p - c) / d.  With far < inf an outside point whose largest plane
-// distance exceeds far returns that lower bound (screening: such a point is
-// beyond every threshold).
 // Signed distance of a unit-scale ellipsoid (semi-axes e) at body point p,
 // negative inside, with the body-frame gradient (unit outward normal at the
 // nearest surface point x), in the oracle's FP64 arithmetic.  Folded into
@@ -528,6 +507,25 @@ __device__ inline void ellip_bounds(CPoly* P, const T* p, T& dlo, T& dhi) {
   dhi = sm * (sm >= (T)0 ? emax : emin);
 }
 
+// Signed distance of a unit-scale polyhedron at body point p (T = double or
+// float, data in the same precision) and, if gb is given, its body-frame
+// gradient.  Inside (every plane distance <= 0): the largest plane distance,
+// gradient the normal of the first face attaining it.  Outside: the distance
+// to the nearest boundary point, which is unique for a convex body.  The
+// nearest point lies on a face the point is
+// above (positive plane distance) or on the boundary of such a face: at a
+// nearest point c, p - c is a non-negative combination of the normals of
+// the faces through c, so (p - c) . n > 0 for one of them.  Those faces'
+// interiors and boundary edges are searched: p projects into a face when it is
+// on the inner side of every side plane, s . p = (n x (b - a)) . p >= s . a for
+// each boundary edge a -> b (counter-clockwise seen from outside), and else
+// the face's nearest point is on an edge whose side p fails (at a vertex,
+// p - c is a sum of the two sides' outward normals, so p fails one of them);
+// the other edges are left out (lattice pass at 256^3 with 1500 boxes
+// 563 us, with all edges 607).  Gradient the face normal or
+// (p - c) / d.  With far < inf an outside point whose largest plane
+// distance exceeds far returns that lower bound (screening: such a point is
+// beyond every threshold).
 template <typename T, bool ELL = false>
 __device__ inline T poly_sdf_unit(CPoly* P, const T* p, T* gb, T far) {
   if (ELL && P->kind == KIND_ELLIPSOID) {

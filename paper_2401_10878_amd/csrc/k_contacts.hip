@@ -150,11 +150,10 @@ __device__ void add_contact(Tiles tl, Counters* ctr, int p, int other,
 // at once and 128 samples a round leave 7 single evaluations in the chain at
 // n_c = 8 where one wavefront per record had 28, and the rolled loop over the
 // axes (coordinates by selects) keeps one copy of the distance in the
-// instruction cache instead of twelve.  One face at a time, both faces, us:
-// 256^3 with 1834 cubes 25.5, 22.7; 1500 boxes 74.7, 59.8; 45 x 37 x 29 with 12
-// bodies 13.5, 12.3.  (Eight wavefronts per record: 45.3, 60.1, 12.2.)  Every wavefront forms the same minima and sums, so the box
-// corrections and exits are uniform over the workgroup; wavefront 0 forms
-// the forces.
+// instruction cache instead of twelve.  256^3 with 1834 cubes, us: 22.7; one face
+// at a time 25.5, eight wavefronts per record 45.3.  Every wavefront forms the
+// same minima and sums, so the box corrections and exits are uniform over the
+// workgroup; wavefront 0 forms the forces.
 constexpr int TREAT_WAVES = 4;
 constexpr int TREAT_HALF = TREAT_WAVES / 2;    // wavefronts per member
 constexpr int TREAT_ROUND = TREAT_HALF * WAVE;   // samples evaluated between two barriers

@@ -57,12 +57,11 @@ __device__ void commit_pair(PairTable t, Counters* ctr, int a, int b,
   }
 }
 
-// POLY: with polyhedron and ellipsoid types.  Bound by vector instructions and,
-// with POLY, by the latency of the types' tables: at 72 registers (seven
-// wavefronts per SIMD) against 82 to 87 (five) 256^3 with 1500 boxes 260 ->
-// 222 us (191 since the distance tests fewer edges), with 734 ellipsoids
-// 215 -> 198.  (A form without the ellipsoids'
-// branch spills at 72; with the spill 215 us for the boxes, at 82 260.)
+// POLY: with polyhedron and ellipsoid types.  Bound by vector instructions (50 us
+// of issue in 72 at 256^3 with 1834 cubes) and, with POLY, by the latency of the
+// types' tables, hence 72 registers (seven wavefronts per SIMD): 256^3 with 1500
+// boxes 191 us (at 82 to 87, five wavefronts, a sixth more).  (A form without the
+// ellipsoids' branch spills at 72.)
 template <bool POLY>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(POLY ? 7 : 8, 8))) void k_detect(Particles P, Geom g, Phys ph,
                                                 Tiles tl, int* __restrict__ owner,

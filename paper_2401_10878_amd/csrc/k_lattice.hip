@@ -451,9 +451,9 @@ __device__ inline void kinematics(const Particles& P, int q, int x, int y, int z
 
 // Register budget without spills: FP64 at most 128 VGPRs (four wavefronts
 // per SIMD), FP32 and binary16 at most 72 (seven: the pass is faster at
-// seven wavefronts than at six or five), except FP32 with polyhedra and no
-// walls, which spills there and takes 74 (six).  Binary16 at seven instead of
-// six, 256^3: 1500 boxes 536 -> 505 us, 734 ellipsoids 521 -> 495.  POLY: built
+// seven wavefronts than at six or five: binary16 with boxes at 256^3 505 us at
+// seven, 536 at six), except FP32 with polyhedra and no
+// walls, which spills there and takes 74 (six).  POLY: built
 // with the polyhedron signed distance (scenes without polyhedra run the
 // form without it, which needs fewer registers).  BAL: with the block sums
 // and device acceleration of the zero-net-flux balance force.  WALL: z
@@ -667,7 +667,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   const int* list = tl.llist + nd.block * g.tile_cap;
   const int* ent = tl.lent + nd.block * g.tile_cap;
   // candidate list, one per lane (binary16, which is short of registers here,
-  // loads it when it is needed: 386 -> 381 us; FP32 early: 613 -> 606 with boxes)
+  // loads it when it is needed: 381 us at 256^3, 386 early)
   constexpr bool LATE_LIST = sizeof(S) == 2;
   int lid = !LATE_LIST && lane < cnt ? list[lane] : -1;
   for (int c = lane; c < cnt; c += WAVE)
@@ -686,10 +686,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
   // Rows are loaded at the lanes' own x; their neighbours along x come from
   // the next lanes, and for the first and the last lane by scalar loads of
   // the nodes beyond, whose addresses are uniform (a row that ends before the
-  // last lane: the lane after the end holds node 0).  Each vector load cost
-  // about 2 us of the pass at 256^3; 8 are left of 18: FP32 with cubes 541 ->
-  // 531 us, with boxes 628 -> 606 (563 with the shorter polyhedron distance), FP64 1040 -> 1018, binary16 396 -> 382;
-  // 128^3 between walls 74.2 -> 70.6.
+  // last lane: the lane after the end holds node 0).  8 vector loads instead of
+  // 18, each about 2 us of the pass at 256^3 (FP32 with cubes 541 us with 18,
+  // 531 with 8).
   // (FP64 with ellipsoids has no registers left for it and loads them all.)
   constexpr bool SHIFT = !(sizeof(S) == 8 && ELL);
   typedef const __attribute__((address_space(4))) char* OwnerBytes;

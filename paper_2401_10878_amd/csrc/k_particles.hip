@@ -12,14 +12,9 @@
 //     append (particle id, enumeration index) to each tile's candidate list.
 //
 // Bound by the latency of its chain (sums, motion, one atomic per listed tile)
-// and, with many particles, by those atomics.  One, two and four wavefronts per
-// particle, us: 256^3 with 1834 cubes 35.1, 30.2, 32.6; 1500 boxes (a polyhedron
-// distance per tile) 78.0, 54.5, 55.8 (46.3 with two since that distance tests fewer
-// edges); 734 ellipsoids 19.8, 18.5, 17.1; 120^3
-// with spheres settling 14.5, 14.0, 14.2.  Two it is: with four, not all workgroups of a
-// dense run fit the chip at once.  FP32 tile distances and earlier loads (144
-// registers, three wavefronts per SIMD) gave 37.9 and 39.5 with the cubes, and
-// held to 128 registers 31.4 and 32.8.
+// and, with many particles, by those atomics.  Two wavefronts per particle: 256^3
+// with 1834 cubes 30.2 us, with one 35.1, with four 32.6 (not all workgroups fit
+// the chip at once).
 #include "balance.h"
 #include "context.h"
 
