@@ -3,6 +3,7 @@ gradient, where the gradient's store stands, what a refused record leaves as
 it was, what a larger window needs beside the one it replaces, and what may be
 lent."""
 import ctypes
+import gc
 
 import numpy as np
 import pytest
@@ -14,6 +15,10 @@ MB = 1 << 20
 
 
 def _sim(W, H, dims=(64, 64, 64), **kw):
+    # (nothing left of earlier simulations, whose unused blocks could serve here)
+    import torch
+    gc.collect()
+    torch.cuda.empty_cache()
     sc = W.random_small_scene(17, dims, 4, size_range=(1.8, 2.8), gap=1.5, speed=0.01,
                               spin=0.004)
     p = W.Params(nx=dims[0], ny=dims[1], nz=dims[2], tau=0.7, gravity=(1e-5, 0.0, -2e-4),

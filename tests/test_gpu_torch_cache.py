@@ -1,6 +1,8 @@
 """The library allocates beside torch's allocator, which keeps the blocks of
 closed simulations (populations, adjoint windows) for later use: where the
 library finds no memory, they are given back first."""
+import gc
+
 import numpy as np
 import pytest
 
@@ -12,6 +14,7 @@ GB = 1 << 30
 def test_simulation_beside_unused_torch_blocks(W, H):
     import torch
     print("simulation beside unused torch blocks", flush=True)
+    gc.collect()
     torch.cuda.empty_cache()
     free = torch.cuda.mem_get_info(0)[0]
     block = torch.empty(free - 6 * GB, dtype=torch.uint8, device="cuda:0")
@@ -26,6 +29,7 @@ def test_simulation_beside_unused_torch_blocks(W, H):
     g.step(2)
     g.sync()
     g.close()
+    del g
     # and the particles' blocks: 200 000 spheres of radius 25 in a box of 64^3
     # list up to 944 lattice blocks of 48 bytes each, 9 GB
     torch.cuda.empty_cache()
