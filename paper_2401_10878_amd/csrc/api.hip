@@ -27,8 +27,8 @@ hlbm_status fail(Ctx& c, hlbm_status st, const char* fmt, ...) {
   va_start(ap, fmt);
   vsnprintf(c.err, sizeof c.err, fmt, ap);
   va_end(ap);
-  // (an error that is reported here is not the next launch's)
-  (void)hipGetLastError();
+  // (a runtime error that is reported here is not the next launch's)
+  if (st == HLBM_E_DEVICE || st == HLBM_E_NOMEM) (void)hipGetLastError();
   return st;
 }
 
